@@ -65,6 +65,26 @@ using ptsbe::Arena;
 }  // namespace
 
 namespace ptsbe {
+std::vector<double2> site_ops64(const Plan& p) {
+  std::vector<double2> out((size_t)std::max(1, p.S) * p.max_kraus * 16, make_double2(0.0, 0.0));
+  std::vector<cd> op(16), e(16);
+  for (int s = 0; s < p.S; ++s) {
+    const int g = p.site_gate[(size_t)s];
+    std::vector<int> gq = {p.qubits[(size_t)g][0]}, sq = {p.site_qubits[(size_t)s][0]};
+    if (p.arity[(size_t)g] == 2) gq.push_back(p.qubits[(size_t)g][1]);
+    if (p.site_qubits[(size_t)s][1] >= 0) sq.push_back(p.site_qubits[(size_t)s][1]);
+    const auto& ops = p.ch_ops[(size_t)p.site_channel[(size_t)s]];
+    const int d = 1 << gq.size(), dk = 1 << sq.size();
+    for (size_t k = 0; k < ops.size(); ++k) {
+      for (int i = 0; i < dk * dk; ++i) op[(size_t)i] = cd(ops[k][2 * i], ops[k][2 * i + 1]);
+      embed_op(op.data(), sq, gq, e.data());
+      for (int i = 0; i < d * d; ++i)
+        out[((size_t)s * p.max_kraus + k) * 16 + i] = make_double2(e[(size_t)i].real(), e[(size_t)i].imag());
+    }
+  }
+  return out;
+}
+
 thread_local std::string g_last_error;
 ptsbe_status_t fail(ptsbe_status_t s, const std::string& msg) {
   g_last_error = msg;
@@ -1301,6 +1321,10 @@ void ptsbe_plan_destroy(ptsbe_plan_t plan) {
     if (o) (void)hipFree(o);
   for (auto* o : p->d_sv_wins_plain)
     if (o) (void)hipFree(o);
+  if (p->adj_cl.d_cls) (void)hipFree(p->adj_cl.d_cls);
+  if (p->adj_cl.d_ops) (void)hipFree(p->adj_cl.d_ops);
+  if (p->d_mats64) (void)hipFree(p->d_mats64);
+  if (p->d_site_ops64) (void)hipFree(p->d_site_ops64);
   delete p;
 }
 

@@ -4,7 +4,9 @@
 //
 // The ket network of every trajectory is contracted in circuit order into its
 // statevector through LDS gate windows of at most 11 qubits; the state after
-// every window is kept as a checkpoint.  The backward pass starts from
+// every window is kept as a checkpoint.  Values and angle gradients of circuits of
+// at least 8 qubits run on windows of gate clusters (run_clusters); gate-tensor
+// adjoints and smaller circuits on windows of single gates.  The backward pass starts from
 // lambda = w O psi (O diagonal: ZZ terms or the caller's array) or from the
 // caller's seed psi-bar = dL/d conj(psi), and walks the windows in reverse,
 // propagating lambda_{k-1} = A_k^dag lambda_k and accumulating per gate
@@ -17,7 +19,10 @@
 #include <algorithm>
 #include <cmath>
 #include <complex>
+#include <cstring>
+#include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -112,6 +117,231 @@ size_t adj_fixed_bytes(const Plan& p, int64_t E, size_t n_ops, size_t width_tota
   return b + ((size_t)1 << 20);
 }
 
+// ---------------------------------------------------------------- cluster form
+// Angle gradients and values of circuits of at least 8 qubits run on the cluster
+// windows (adj_cluster.hip); gate-tensor adjoints, which need every gate's own
+// amplitudes, and smaller circuits on the per-gate windows below.
+// The plan's cluster schedule, made by the first call on the host; with `device`, also
+// its device copy and the 64-bit gate operands.
+ptsbe_status_t cluster_schedule(Plan& p, bool device, const ptsbe::AdjClSchedule** out) {
+  std::lock_guard<std::mutex> lock(p.adj_mu);
+  ptsbe::AdjClSchedule& S = p.adj_cl;
+  if (!p.adj_cl_made) {
+    // with non-unitary operators three tiles and both forms of the matrices share 64 KB of LDS
+    ptsbe::build_adj_clusters(p, p.inserted_unitary ? kAdjWindowQubits : kAdjWindowQubits - 1, S);
+    p.adj_cl_made = true;
+  }
+  *out = &S;
+  if (!device || !S.ok) return PTSBE_OK;
+  auto put = [](auto** d, const auto& v) -> hipError_t {
+    if (*d) return hipSuccess;
+    void* m = nullptr;
+    hipError_t e = hipMalloc(&m, std::max<size_t>(v.size(), 1) * sizeof(v[0]));
+    if (e == hipSuccess) e = hipMemcpy(m, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice);
+    if (e == hipSuccess) *d = static_cast<std::remove_reference_t<decltype(**d)>*>(m);
+    else if (m) (void)hipFree(m);
+    return e;
+  };
+  HIP_TRY(put(&S.d_cls, S.cls));
+  HIP_TRY(put(&S.d_ops, S.ops));
+  if (!p.d_mats64) {
+    std::vector<double2> m((size_t)p.G * 16, make_double2(0.0, 0.0));
+    for (int g = 0; g < p.G; ++g)
+      for (int i = 0; i < (1 << (2 * p.arity[(size_t)g])); ++i)
+        m[(size_t)g * 16 + i] = make_double2(p.mats[(size_t)g][2 * i], p.mats[(size_t)g][2 * i + 1]);
+    HIP_TRY(put(&p.d_mats64, m));
+  }
+  if (!p.d_site_ops64) HIP_TRY(put(&p.d_site_ops64, ptsbe::site_ops64(p)));
+  return PTSBE_OK;
+}
+
+// Device bytes per trajectory of a chunk: states (every window's, and lambda), merged
+// gates, cluster matrices, and for a gradient one workgroup's sums and the derivatives.
+size_t cluster_per_traj(const Plan& p, const ptsbe::AdjClSchedule& S, bool grad) {
+  size_t b = adj_per_traj(p, S.wins.size(), grad) + S.cls.size() * (grad ? 2048 : 4096);
+  if (grad) b += (size_t)ptsbe::kAdjClMax * 4096 + S.ops.size() * (256 + 8);
+  return b + 2048;                     // alignment of the chunk's arrays
+}
+
+size_t cluster_table_bytes(const Plan& p, const AdjSpec& S, size_t n_ops) {
+  return align256(((size_t)2 * p.G + (size_t)S.n_params + 1 + n_ops + S.zq.size()) * 4 + S.zc.size() * 8 + 64);
+}
+
+size_t cluster_fixed_bytes(const Plan& p, const AdjSpec& S, int64_t E, size_t n_ops) {
+  return cluster_table_bytes(p, S, n_ops) + align256((size_t)E * 8) + align256((size_t)8 << p.n) +
+         align256((size_t)std::min<int64_t>(E, kAdjChunkMax) * 64 * 8) + ((size_t)1 << 20);
+}
+
+ptsbe_status_t run_clusters(Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedule& sched, const uint8_t* d_kraus,
+                            int64_t E, const double* d_weights, const double* d_theta, const void* d_psi_bar,
+                            double* d_traj_value, double* d_value, double* d_grad, void* d_workspace,
+                            size_t workspace_bytes, hipStream_t s) {
+  const int n = p.n, G = p.G, W = (int)sched.wins.size();
+  const int n_ops = (int)sched.ops.size(), n_cl = (int)sched.cls.size();
+  const bool grad = d_grad != nullptr && S.n_params > 0, recompute = grad && !p.inserted_unitary;
+  Arena ar;
+  ar.base = (char*)d_workspace;
+  ar.cap = workspace_bytes;
+  // one upload: ZZ coefficients, gate tables, ZZ qubits, and each parameter's rotations
+  std::vector<char> tab(cluster_table_bytes(p, S, (size_t)n_ops), 0);
+  char* d_tab = (char*)ar.take(tab.size());
+  double* vals = d_traj_value ? d_traj_value : (double*)ar.take((size_t)E * 8);
+  double* d_diag = S.obs_diag ? nullptr : (double*)ar.take((size_t)8 << n);
+  double* d_part = (double*)ar.take((size_t)std::min<int64_t>(E, kAdjChunkMax) * 64 * 8);
+  if (!d_tab || !vals || (!S.obs_diag && !d_diag) || !d_part)
+    return fail(PTSBE_ERR_OUT_OF_MEMORY, "workspace too small for the observable and tables");
+  size_t at = 0;
+  auto put = [&](const void* src, size_t bytes) {
+    std::memcpy(tab.data() + at, src, bytes);
+    char* d = d_tab + at;
+    at += bytes;
+    return d;
+  };
+  double* d_zc = (double*)put(S.zc.data(), S.zc.size() * 8);
+  int32_t* d_gp = (int32_t*)put(S.gate_param.data(), (size_t)G * 4);
+  int32_t* d_ga = (int32_t*)put(S.gate_axis.data(), (size_t)G * 4);
+  int32_t* d_zq = (int32_t*)put(S.zq.data(), S.zq.size() * 4);
+  std::vector<int32_t> poff((size_t)S.n_params + 1, 0), pops;
+  if (grad) {
+    for (const auto& op : sched.ops)
+      if (S.gate_param[(size_t)op.gate] >= 0) ++poff[(size_t)S.gate_param[(size_t)op.gate] + 1];
+    for (int k = 0; k < S.n_params; ++k) poff[(size_t)k + 1] += poff[(size_t)k];
+    pops.resize((size_t)poff.back());
+    std::vector<int32_t> fill(poff.begin(), poff.end() - 1);
+    for (int o = 0; o < n_ops; ++o) {
+      const int prm = S.gate_param[(size_t)sched.ops[(size_t)o].gate];
+      if (prm >= 0) pops[(size_t)fill[(size_t)prm]++] = o;
+    }
+  }
+  int32_t* d_poff = (int32_t*)put(poff.data(), poff.size() * 4);
+  int32_t* d_pops = (int32_t*)put(pops.data(), pops.size() * 4);
+  struct SyncOnExit {                  // the upload finishes before its host source is freed
+    hipStream_t s;
+    ~SyncOnExit() { (void)hipStreamSynchronize(s); }
+  } sync_on_exit{s};
+  HIP_TRY(hipMemcpyAsync(d_tab, tab.data(), at, hipMemcpyHostToDevice, s));
+  if (!S.obs_diag) HIP_TRY(ptsbe::launch_adj_zz_diag(n, d_zq, d_zc, S.has_obs ? (int)S.zc.size() : 0, d_diag, s));
+  const size_t per = cluster_per_traj(p, sched, grad);
+  const size_t avail = ar.left() > ((size_t)64 << 10) ? ar.left() - ((size_t)64 << 10) : 0;
+  const int64_t Ec = std::min<int64_t>({E, (int64_t)(avail / per), kAdjChunkMax});
+  if (Ec < 1) return fail(PTSBE_ERR_OUT_OF_MEMORY, "workspace too small for one trajectory's checkpoints");
+  const size_t SZ = (size_t)1 << n;
+  auto timed = [&](double bytes, auto&& launch) -> ptsbe_status_t {   // HIP events under profiling
+    std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
+    if (p.profile) {
+      HIP_TRY(hipEventCreate(&ev.first));
+      HIP_TRY(hipEventCreate(&ev.second));
+      HIP_TRY(hipEventRecord(ev.first, s));
+    }
+    HIP_TRY(launch());
+    if (p.profile) {
+      HIP_TRY(hipEventRecord(ev.second, s));
+      p.win_evs.push_back(ev);
+      ++p.win_launches;
+      p.win_bytes += bytes;
+    }
+    return PTSBE_OK;
+  };
+  for (int64_t t0 = 0; t0 < E; t0 += Ec) {
+    const int64_t nj = std::min<int64_t>(Ec, E - t0);
+    const size_t mark = ar.used;
+    double2* A = grad ? (double2*)ar.take((size_t)nj * n_ops * 256) : nullptr;
+    void* U = ar.take((size_t)nj * n_cl * (grad ? 2048 : 4096));
+    double* gop = grad ? (double*)ar.take((size_t)nj * n_ops * 8) : nullptr;
+    // states: ck[w] before window w (ck[0] = |0 .. 0> is not stored); two buffers for values only
+    std::vector<float2*> ck((size_t)(grad ? W + 1 : 3), nullptr);
+    for (size_t k = 1; k < ck.size(); ++k) ck[k] = (float2*)ar.take((size_t)nj * SZ * 8);
+    float2* lam = grad ? (float2*)ar.take((size_t)nj * SZ * 8) : nullptr;
+    if (!U || !ck.back() || (grad && (!A || !gop || !lam)))
+      return fail(PTSBE_ERR_OUT_OF_MEMORY, "workspace too small for the chunk");
+    // the sums of a backward window's workgroups: as many per trajectory as fit
+    const int64_t q_slots = (int64_t)(ar.left() / ((size_t)nj * ptsbe::kAdjClMax * 4096 + 256));
+    double* q = grad ? (double*)ar.take((size_t)nj * std::max<int64_t>(1, std::min<int64_t>(q_slots, 4096)) *
+                                        ptsbe::kAdjClMax * 4096)
+                     : nullptr;
+    if (grad && !q) return fail(PTSBE_ERR_OUT_OF_MEMORY, "workspace too small for the backward sums");
+    ptsbe::AdjClBuildArgs ba{};
+    ba.g.gates = p.d_gates;
+    ba.g.gate_site_list = p.d_gate_site_list;
+    ba.g.kraus = d_kraus;
+    ba.g.S = p.S;
+    ba.g.max_kraus = p.max_kraus;
+    ba.g.G = G;
+    ba.mats = p.d_mats64;
+    ba.site_ops = p.d_site_ops64;
+    ba.gate_param = d_gp;
+    ba.gate_axis = d_ga;
+    ba.theta = d_theta;
+    ba.n_jobs = nj;
+    ba.traj_base = (int32_t)t0;
+    ba.A = A;
+    ba.cls = sched.d_cls;
+    ba.ops = sched.d_ops;
+    ba.n_cl = n_cl;
+    ba.n_ops = n_ops;
+    ba.U = grad ? (float2*)U : nullptr;
+    ba.U64 = grad ? nullptr : (double2*)U;
+    HIP_TRY(ptsbe::launch_adj_cl_build(ba, s));
+    auto state = [&](int w) { return ck[grad || w == 0 ? (size_t)w : (size_t)(1 + (w & 1))]; };
+    auto args_for = [&](const ptsbe::AdjClWin& wd) {
+      ptsbe::AdjClArgs a{};
+      a.n = n;
+      a.cl_off = wd.cl_off;
+      a.n_cl = wd.n_cl;
+      a.n_cl_total = n_cl;
+      for (int k = 0; k < 12; ++k) a.P[k] = wd.P[k];
+      a.other = wd.other;
+      a.n_jobs = nj;
+      for (int c = 0; c < wd.n_cl; ++c) a.pos[c] = sched.cls[(size_t)(wd.cl_off + c)].pos;
+      a.U = (const float2*)U;
+      a.U64 = (const double2*)U;
+      return a;
+    };
+    for (int w = 0; w < W; ++w) {
+      const ptsbe::AdjClWin& wd = sched.wins[(size_t)w];
+      ptsbe::AdjClArgs a = args_for(wd);
+      a.psi_in = state(w);
+      a.psi_out = state(w + 1);
+      const ptsbe::AdjClPass pass = grad ? ptsbe::AdjClPass::forward : ptsbe::AdjClPass::value;
+      a.wpj = ptsbe::adj_cl_wpj(pass, wd.np, wd.n_cl, nj, n);
+      const ptsbe_status_t st = timed((double)nj * 16.0 * std::ldexp(1.0, n),
+                                      [&] { return ptsbe::launch_adj_cl_pass(pass, a, wd.np, s); });
+      if (st != PTSBE_OK) return st;
+    }
+    ptsbe::AdjSeedArgs sd{};
+    sd.psi = state(W);
+    sd.lam = lam;
+    sd.psi_bar = (const float2*)d_psi_bar;
+    sd.obs_diag = S.obs_diag ? S.obs_diag : d_diag;
+    sd.part = d_part;
+    sd.weights = d_weights;
+    sd.values = S.has_obs ? vals : nullptr;
+    sd.n = n;
+    sd.traj_base = (int32_t)t0;
+    HIP_TRY(ptsbe::launch_adj_seed(sd, nj, s));
+    if (grad) {
+      for (int w = W - 1; w >= 0; --w) {
+        const ptsbe::AdjClWin& wd = sched.wins[(size_t)w];
+        ptsbe::AdjClArgs a = args_for(wd);
+        a.psi_in = recompute ? ck[(size_t)w] : ck[(size_t)w + 1];
+        a.lam = lam;
+        a.q = q;
+        const ptsbe::AdjClPass pass = recompute ? ptsbe::AdjClPass::backward_recompute : ptsbe::AdjClPass::backward;
+        a.wpj = (int)std::min<int64_t>(ptsbe::adj_cl_wpj(pass, wd.np, wd.n_cl, nj, n), std::max<int64_t>(1, q_slots));
+        const ptsbe_status_t st = timed((double)nj * 24.0 * std::ldexp(1.0, n),
+                                        [&] { return ptsbe::launch_adj_cl_pass(pass, a, wd.np, s); });
+        if (st != PTSBE_OK) return st;
+        HIP_TRY(ptsbe::launch_adj_cl_grad(a, !recompute, sched.d_cls, sched.d_ops, n_ops, A, d_gp, d_ga, gop, s));
+      }
+      HIP_TRY(ptsbe::launch_adj_cl_params(gop, nj, n_ops, d_poff, d_pops, S.n_params, t0 > 0, d_grad, s));
+    }
+    ar.used = mark;
+  }
+  if (S.has_obs && d_value) HIP_TRY(ptsbe::launch_value_sum(vals, d_weights, E, d_value, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  return p.profile ? ptsbe::collect_window_events(p) : PTSBE_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -130,6 +360,15 @@ ptsbe_status_t ptsbe_adjoint_workspace_size(ptsbe_plan_t plan, const ptsbe_adjoi
   for (const auto& w : wins) max_ops = std::max<size_t>(max_ops, (size_t)w.n_ops);
   *bytes = adj_fixed_bytes(*p, E, ops.size(), ops.size() * 33, max_ops * 33) +
            (size_t)std::min<int64_t>(E, 256) * adj_per_traj(*p, wins.size(), true);
+  const ptsbe::AdjClSchedule* cl = nullptr;
+  st = cluster_schedule(*p, false, &cl);
+  if (st != PTSBE_OK) return st;
+  if (cl->ok) {
+    // sums of up to 2048 workgroups beside the chunk's arrays
+    const size_t b = cluster_fixed_bytes(*p, S, E, cl->ops.size()) + (size_t)2048 * ptsbe::kAdjClMax * 4096 +
+                     (size_t)std::min<int64_t>(E, 256) * cluster_per_traj(*p, *cl, true);
+    *bytes = std::max(*bytes, b);
+  }
   return PTSBE_OK;
 }
 
@@ -155,10 +394,18 @@ ptsbe_status_t ptsbe_contract_adjoint(ptsbe_plan_t plan, const ptsbe_adjoint_spe
   HIP_TRY(hipSetDevice(p->device));
   hipStream_t s = (hipStream_t)stream;
   const int n = p->n, G = p->G;
-  // windows and their ops (host, once per call)
   const bool want_grad = d_grad != nullptr && S.n_params > 0;
   const bool want_adj = d_gate_adj != nullptr;
   const bool backward = want_grad || want_adj;
+  if (!want_adj) {
+    const ptsbe::AdjClSchedule* cl = nullptr;
+    st = cluster_schedule(*p, true, &cl);
+    if (st != PTSBE_OK) return st;
+    if (cl->ok)
+      return run_clusters(*p, S, *cl, d_kraus_idx, E, d_weights, d_theta, d_psi_bar, d_traj_value, d_value, d_grad,
+                          d_workspace, workspace_bytes, s);
+  }
+  // windows and their ops (host, once per call)
   const bool recompute = !p->inserted_unitary;
   std::vector<ptsbe::AdjWin> wins;
   std::vector<ptsbe::AdjOp> ops;
@@ -174,12 +421,6 @@ ptsbe_status_t ptsbe_contract_adjoint(ptsbe_plan_t plan, const ptsbe_adjoint_spe
       ptsbe::AdjOp& op = ops[(size_t)(wd.op_off + k)];
       op.axis = (int8_t)(want_grad && S.gate_param[(size_t)op.gate] >= 0 ? S.gate_axis[(size_t)op.gate] : -1);
       op.nslot = want_adj ? k : -1;
-    }
-    for (int gi = 0; gi < wd.n_groups; ++gi) {
-      ptsbe::AdjGroup& gr = groups[(size_t)(wd.group_off + gi)];
-      gr.rot_mask = 0;
-      for (int j = 0; j < gr.n; ++j)
-        if (ops[(size_t)(wd.op_off + gr.first + j)].axis >= 0) gr.rot_mask |= 1u << j;
     }
     width[(size_t)w] = wd.n_ops + (want_adj ? 32 * wd.n_ops : 0);
     tot_off[(size_t)w + 1] = tot_off[(size_t)w] + width[(size_t)w];

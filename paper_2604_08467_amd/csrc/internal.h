@@ -6,6 +6,7 @@
 
 #include <array>
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -127,6 +128,18 @@ struct SvWin {
   uint32_t other;           // bit mask of the state's qubits outside the window
 };
 
+struct DeviceGate;
+// A trajectory set's gate operands: constants of the plan, error sets, merged gates.
+struct GateCtx {
+  const DeviceGate* gates;
+  const int32_t* gate_site_list;
+  const float2* site_ops;
+  const uint8_t* kraus;     // [E][S]
+  int32_t S, max_kraus;
+  const float2* merged;     // [E][G][16] merged gates of every trajectory
+  int32_t G;
+};
+
 // Op of an adjoint window (a plain gate in place on the tile): the gate's merged
 // matrix entry idx[a * d + b] is local entry (a, b); axis >= 0 marks a rotation
 // exp(-i theta P / 2) about P = X, Y, Z whose derivative is accumulated; nslot >= 0
@@ -149,8 +162,7 @@ constexpr int kAdjGroupMax = 8;
 struct AdjGroup {
   int8_t nq, pa, pb, n;           // positions used, the group's tile positions, op count
   int32_t first;                  // index of the group's first op in the window
-  uint32_t rot_mask;              // bit j: op first + j is a differentiated rotation
-  int32_t pad;
+  int32_t pad[2];
 };
 static_assert(sizeof(AdjGroup) == 16, "AdjGroup is read as four dwords");
 struct AdjArgs {
@@ -179,6 +191,80 @@ struct AdjSeedArgs {
   int n;
   int32_t traj_base;
 };
+// Cluster form of an adjoint window: its gates grouped into clusters on at most four
+// tile positions, each applied as one 16 x 16 matrix per trajectory.
+constexpr int kAdjClOps = 13;       // gates per cluster: their FP64 prefix products fit 64 KB of LDS
+constexpr int kAdjClMax = 6;        // clusters per window (per-thread sums of the backward pass in registers)
+struct AdjClOp {
+  int8_t kind, b0, b1, pad;         // one- or two-qubit gate, cluster bits of its local bits 0 and 1
+  int32_t gate;
+  int8_t idx[16];                   // local entry (a, b) is merged entry idx[a * d + b]
+  int32_t pad2[2];
+};
+static_assert(sizeof(AdjClOp) == 32, "AdjClOp is 32 bytes");
+struct AdjCl {
+  uint32_t pos;                     // byte i: tile position of cluster bit i
+  int32_t first, n, pad;            // ops [first, first + n)
+};
+struct AdjClWin {
+  int32_t cl_off, n_cl, np;
+  int32_t P[12];
+  uint32_t other;                   // bit mask of the qubits outside the window
+};
+// One schedule of a plan (host and device copies), made by the first call that needs
+// it and kept with the plan.
+struct AdjClSchedule {
+  bool ok = false;                  // every step is a plain gate and the circuit has at least 8 qubits
+  std::vector<AdjClWin> wins;
+  std::vector<AdjCl> cls;
+  std::vector<AdjClOp> ops;
+  AdjCl* d_cls = nullptr;
+  AdjClOp* d_ops = nullptr;
+};
+struct AdjClArgs {
+  int n, cl_off, n_cl, n_cl_total, wpj;
+  int P[12];
+  uint32_t other;
+  uint32_t pos[kAdjClMax];          // AdjCl::pos of the window's clusters
+  int64_t n_jobs;
+  const float2* U;                  // [n_jobs][n_cl_total][256] cluster matrices
+  const double2* U64;               // the same in 64 bits (value-only pass)
+  const float2* psi_in;             // forward: input states; backward: states after / before the window;
+                                    // null: |0 .. 0> of every trajectory
+  float2* psi_out;                  // forward: output states
+  float2* lam;                      // backward: adjoint states, in place
+  double* q;                        // backward: [n_jobs][wpj][n_cl][2][256] sums Q
+};
+// value: forward in 64 bits; forward; backward with unitary operators; backward with psi
+// recomputed from the window's starting state
+enum class AdjClPass { value, forward, backward, backward_recompute };
+struct AdjClBuildArgs {
+  GateCtx g;                        // kraus and site lists
+  const double2* mats;              // [G][16] bare gates, 64 bits
+  const double2* site_ops;          // [S][max_kraus][16] inserted operators, 64 bits
+  const int32_t* gate_param;        // [G] parameter index or -1
+  const int32_t* gate_axis;         // [G]
+  const double* theta;
+  int64_t n_jobs;
+  int32_t traj_base;
+  double2* A;                       // [n_jobs][n_ops][16] merged gates in op order, or null
+  const AdjCl* cls;
+  const AdjClOp* ops;
+  int n_cl, n_ops;
+  float2* U;                        // [n_jobs][n_cl][256], or
+  double2* U64;                     // the same in 64 bits
+};
+hipError_t launch_adj_cl_build(const AdjClBuildArgs& b, hipStream_t stream);
+// Workgroups per trajectory that fill the chip once (at most the window's tiles).
+int adj_cl_wpj(AdjClPass pass, int np, int n_cl, int64_t n_jobs, int n);
+hipError_t launch_adj_cl_pass(AdjClPass pass, const AdjClArgs& a, int np, hipStream_t stream);
+// Angle derivatives of a window's rotations from its sums: gop[n_jobs][n_ops_total].
+hipError_t launch_adj_cl_grad(const AdjClArgs& a, bool unitary, const AdjCl* cls, const AdjClOp* ops, int n_ops_total,
+                              const double2* A, const int32_t* gate_param, const int32_t* gate_axis,
+                              double* gop, hipStream_t stream);
+// grad[k] (+)= sum over jobs and the ops of parameter k (ops[off[k]] .. ops[off[k + 1] - 1]).
+hipError_t launch_adj_cl_params(const double* gop, int64_t n_jobs, int n_ops_total, const int32_t* off,
+                                const int32_t* ops, int n_params, bool add, double* grad, hipStream_t stream);
 size_t adj_window_lds_bytes(int mode, int np, int n_ops, int n_nslots);
 int adj_window_grid(int mode, const AdjArgs& a, size_t lds);
 hipError_t launch_adj_window(int mode, const AdjArgs& a, const AdjOp* d_ops, int grid, hipStream_t stream);
@@ -329,6 +415,13 @@ struct Plan {
   bool subtree_reuse = false;
   int sample_kernel = 0;               // 0: automatic lane-per-element sampling, 1: wavefront per element
 
+  // cluster schedule of the adjoint passes and the 64-bit gate operands it is built from
+  std::mutex adj_mu;
+  AdjClSchedule adj_cl;
+  bool adj_cl_made = false;
+  double2* d_mats64 = nullptr;
+  double2* d_site_ops64 = nullptr;
+
   // measurement
   int profile = 0;                                // 1: time the MFMA join; 2: also single HBM sweep steps
   double join_ms = 0, sweep_ms = 0, join_flops = 0, sweep_bytes = 0, fused_bytes = 0;
@@ -369,17 +462,14 @@ void build_adj_windows(const Plan& p, int wmax, int max_ops, std::vector<AdjWin>
 // tile positions (an op only moves past ops on other positions) and fills the
 // windows' group ranges; slots follow the new order.
 void build_adj_groups(std::vector<AdjWin>& wins, std::vector<AdjOp>& ops, std::vector<AdjGroup>& groups);
+// The same packing with each window's gates in clusters of at most kAdjClOps gates on at
+// most four positions, at most kAdjClMax clusters per window.  Leaves s.ok false when a
+// step is not a plain gate or the circuit has fewer than 8 qubits.
+void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& s);
+// Inserted operators of every site in its gate's space, 64 bits: [S][max_kraus][16].
+std::vector<double2> site_ops64(const Plan& p);
 
 // kernels.hip: launchers (all asynchronous on `stream`)
-struct GateCtx {
-  const DeviceGate* gates;
-  const int32_t* gate_site_list;
-  const float2* site_ops;
-  const uint8_t* kraus;     // [E][S]
-  int32_t S, max_kraus;
-  const float2* merged;     // [E][G][16] merged gates of every trajectory
-  int32_t G;
-};
 // UPV merge (error injection) of every (trajectory, gate): merged[t][g] =
 // (prod of the inserted operators of g's sites) . d_g, the shared default when
 // all of g's sites take Kraus index 0.

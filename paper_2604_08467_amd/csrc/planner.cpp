@@ -959,6 +959,76 @@ void build_adj_groups(std::vector<AdjWin>& wins, std::vector<AdjOp>& ops, std::v
   ops = out;
 }
 
+void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& S) {
+  S.ok = false;
+  S.wins.clear();
+  S.cls.clear();
+  S.ops.clear();
+  if (p.n < 8 || p.sv_steps.empty()) return;
+  for (const AbsorbStep& st : p.sv_steps)
+    if (!plain_step(st)) return;
+  const uint32_t all = p.n >= 32 ? 0xFFFFFFFFu : ((1u << p.n) - 1u);
+  std::vector<int> rest(p.sv_steps.size());
+  for (size_t i = 0; i < rest.size(); ++i) rest[i] = (int)i;
+  while (!rest.empty()) {
+    std::vector<int> taken, left_out, Pv, order;
+    std::vector<std::pair<int, int>> groups;
+    pack_window(p, rest, wmax, taken, left_out, Pv);
+    cluster_order(p, taken, order, groups);
+    AdjClWin w{};
+    w.cl_off = (int32_t)S.cls.size();
+    w.np = (int32_t)Pv.size();
+    uint32_t win = 0;
+    for (int k = 0; k < w.np; ++k) {
+      w.P[k] = Pv[(size_t)k];
+      win |= 1u << Pv[(size_t)k];
+    }
+    w.other = all & ~win;
+    size_t done = 0;                 // steps of `order` taken into clusters
+    for (const auto& gr : groups) {
+      for (int s0 = gr.first; s0 < gr.first + gr.second; s0 += kAdjClOps) {
+        if (w.n_cl >= kAdjClMax) break;
+        const int s1 = std::min(gr.first + gr.second, s0 + kAdjClOps);
+        std::set<int> Q;
+        for (int s = s0; s < s1; ++s) {
+          const AbsorbStep& st = p.sv_steps[(size_t)order[(size_t)s]];
+          for (int k = 0; k < st.nK; ++k) Q.insert(st.kpos[k]);
+        }
+        std::vector<int> loc, qs(Q.begin(), Q.end());
+        for (int q : qs) loc.push_back((int)(std::find(Pv.begin(), Pv.end(), q) - Pv.begin()));
+        for (int l = w.np - 1; (int)loc.size() < 4; --l)     // pad with other tile positions
+          if (std::find(loc.begin(), loc.end(), l) == loc.end()) loc.push_back(l);
+        AdjCl c{};
+        for (int i = 0; i < 4; ++i) c.pos |= (uint32_t)loc[(size_t)i] << (8 * i);
+        c.first = (int32_t)S.ops.size();
+        c.n = s1 - s0;
+        for (int s = s0; s < s1; ++s) {
+          const AbsorbStep& st = p.sv_steps[(size_t)order[(size_t)s]];
+          auto bit = [&](int q) { return (int8_t)(std::find(qs.begin(), qs.end(), q) - qs.begin()); };
+          AdjClOp op{};
+          op.kind = (int8_t)(st.nK == 1 ? kSvOpGate1 : kSvOpGate2);
+          op.b0 = bit(st.kpos[0]);
+          op.b1 = st.nK == 2 ? bit(st.kpos[1]) : (int8_t)0;
+          op.gate = st.gate;
+          const int d = 1 << st.nK;
+          for (int a = 0; a < d; ++a)
+            for (int b = 0; b < d; ++b) op.idx[a * d + b] = (int8_t)(st.nB[a] + st.kB[b]);
+          S.ops.push_back(op);
+        }
+        S.cls.push_back(c);
+        ++w.n_cl;
+        done = (size_t)s1;
+      }
+    }
+    // steps beyond the window's last cluster wait for the next window, in circuit order
+    left_out.insert(left_out.end(), order.begin() + (std::ptrdiff_t)done, order.end());
+    std::sort(left_out.begin(), left_out.end());
+    S.wins.push_back(w);
+    rest = left_out;
+  }
+  S.ok = true;
+}
+
 void build_sv_ops(Plan& p) {
   const uint32_t all = p.n >= 32 ? 0xFFFFFFFFu : ((1u << p.n) - 1u);
   for (int i = 0; i < 3; ++i) {
