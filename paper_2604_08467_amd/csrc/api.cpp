@@ -126,11 +126,14 @@ size_t join_traj_bytes(const ptsbe::BatchPlan& bp) {
   return ((size_t)8 << bp.right.labels.size()) + layout + part_scratch_per_job(bp.right);
 }
 
-// One LDS sweep launch (part_vm_kernel) over the first n_steps steps of a part;
-// under profiling, HIP events on the launch stream and the steps' algorithmic
+// A last step of an LDS sweep that raises the rank may write its output straight to HBM.
+bool direct_step(const ptsbe::AbsorbStep& st) { return st.nK <= 1 && st.nN > st.nK && st.nK + st.nN <= 4; }
+
+// One LDS sweep launch (part_vm_kernel) over the steps [first, first + n_steps) of a
+// part (d_steps: its first step on the device); under profiling, HIP events on the launch stream and the steps' algorithmic
 // flops (8 per complex multiply-add: 8 2^(rC + nK) per step and job).
-ptsbe_status_t timed_part_vm(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbStep* d_steps, int n_steps,
-                             int peak, const ptsbe::GateCtx& g, int64_t n_jobs, const int32_t* job_traj,
+ptsbe_status_t timed_part_vm(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbStep* d_steps, int first,
+                             int n_steps, int peak, const ptsbe::GateCtx& g, int64_t n_jobs, const int32_t* job_traj,
                              int32_t traj_base, const uint64_t* job_prefix, const ptsbe::InitArgs& init, float2* out,
                              int out_rank, hipStream_t s) {
   std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
@@ -145,23 +148,25 @@ ptsbe_status_t timed_part_vm(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::Ab
   // the ranks before it
   int lds_peak = 0, direct = 0;
   for (int i = 0; i < n_steps; ++i) {
-    const ptsbe::AbsorbStep& st = pp.steps[(size_t)i];
+    const ptsbe::AbsorbStep& st = pp.steps[(size_t)(first + i)];
     lds_peak = std::max(lds_peak, st.rA);
     if (i + 1 < n_steps) lds_peak = std::max(lds_peak, st.rC);
   }
   if (n_steps > 0) {
-    const ptsbe::AbsorbStep& last = pp.steps[(size_t)n_steps - 1];
-    if (last.rC > lds_peak && last.rC == out_rank && last.nK <= 1 && last.nN > last.nK && last.nK + last.nN <= 4)
-      direct = 1;
+    const ptsbe::AbsorbStep& last = pp.steps[(size_t)(first + n_steps) - 1];
+    if (last.rC > lds_peak && last.rC == out_rank && direct_step(last)) direct = 1;
   }
-  HIP_TRY(ptsbe::launch_part_vm(d_steps, n_steps, direct ? lds_peak : peak, g, n_jobs, job_traj, traj_base, job_prefix,
+  HIP_TRY(ptsbe::launch_part_vm(d_steps + first, n_steps, direct ? lds_peak : peak, g, n_jobs, job_traj, traj_base, job_prefix,
                                 p.NW, init, out, out_rank, direct, s));
   if (p.profile) {
     HIP_TRY(hipEventRecord(ev.second, s));
     p.vm_evs.push_back(ev);
     ++p.vm_launches;
     double f = 0.0;
-    for (int i = 0; i < n_steps; ++i) f += 8.0 * std::ldexp(1.0, pp.steps[(size_t)i].rC + pp.steps[(size_t)i].nK);
+    for (int i = 0; i < n_steps; ++i) {
+      const ptsbe::AbsorbStep& st = pp.steps[(size_t)(first + i)];
+      f += 8.0 * std::ldexp(1.0, st.rC + st.nK);
+    }
     p.vm_flops += f * (double)n_jobs;
   }
   return PTSBE_OK;
@@ -245,7 +250,7 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
     return PTSBE_OK;
   }
   if (part_uses_vm(pp))
-    return timed_part_vm(p, pp, d_steps, (int)pp.steps.size(), pp.peak, g, n_jobs, job_traj, traj_base, job_prefix,
+    return timed_part_vm(p, pp, d_steps, 0, (int)pp.steps.size(), pp.peak, g, n_jobs, job_traj, traj_base, job_prefix,
                          init, out, out_rank, s);
   const size_t mark = ar.used;
   float2* b0 = (float2*)ar.take((size_t)n_jobs * ((size_t)8 << pp.peak));
@@ -295,22 +300,32 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
     lv_pos = std::move(pos);
     return PTSBE_OK;
   };
-  // the leading segments whose tensors all fit 2^kVmMaxRank entries run as one
-  // LDS sweep (one launch) instead of one launch per step
+  // runs of segments whose tensors all fit 2^kVmMaxRank entries go as one LDS sweep (one
+  // launch) instead of one launch per step: the segments [si, end) for the run from si,
+  // with the largest rank held in LDS and the step that ends it.  The last step may raise
+  // the rank further when it can write to HBM.
   const size_t nseg = pp.segs.size();
-  size_t s0 = 0;
+  auto vm_run = [&](size_t si, int& end_step, int& peak) -> size_t {
+    int pk = 0;
+    for (; si < nseg && !pp.segs[si].fused; ++si) {
+      const ptsbe::AbsorbStep& st = pp.steps[(size_t)pp.segs[si].first];
+      if (st.rA > ptsbe::kVmMaxRank) break;
+      const bool over = st.rC > ptsbe::kVmMaxRank;
+      if (over && !direct_step(st)) break;
+      pk = std::max(pk, std::max(st.rA, std::min(st.rC, ptsbe::kVmMaxRank)));
+      end_step = pp.segs[si].first + 1;
+      if (over) { ++si; break; }
+    }
+    peak = pk;
+    return si;
+  };
   int h = 0, hpeak = 0;
-  while (s0 + 1 < nseg) {
-    const ptsbe::Segment& sg = pp.segs[s0];
-    int pk = hpeak;
-    for (int i = sg.first; i < sg.first + sg.count; ++i)
-      pk = std::max(pk, std::max(pp.steps[(size_t)i].rA, pp.steps[(size_t)i].rC));
-    if (pk > ptsbe::kVmMaxRank) break;
-    hpeak = pk;
-    h = sg.first + sg.count;
-    ++s0;
+  size_t s0 = vm_run(0, h, hpeak);
+  if (trie && s0 >= nseg) {          // with subtree reuse the last launch stands alone
+    s0 = nseg - 1;
+    h = pp.segs[s0].first;
   }
-  if (h < 2) s0 = 0;
+  if (h < 2) s0 = 0, h = 0;
   // the last rank-changing step writes the output; in-place runs after it work on
   // the output directly (no final copy; with subtree reuse the job set may still
   // grow, so the output is written by a final copy)
@@ -325,7 +340,7 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
     if (st != PTSBE_OK) return st;
   }
   if (h >= 2) {
-    const ptsbe_status_t st = timed_part_vm(p, pp, d_steps, h, hpeak, g, cur_n, cur_traj, traj_base, job_prefix,
+    const ptsbe_status_t st = timed_part_vm(p, pp, d_steps, 0, h, hpeak, g, cur_n, cur_traj, traj_base, job_prefix,
                                             init, A, pp.steps[(size_t)h - 1].rC, s);
     if (st != PTSBE_OK) return st;
   } else {
@@ -351,6 +366,25 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
       continue;
     }
     const size_t i = (size_t)sg.first;
+    if (!trie) {
+      int end_step = 0, peak = 0;
+      const size_t end = vm_run(si, end_step, peak);
+      if (end_step - (int)i >= 2) {
+        float2* C = (last_nf >= si && last_nf < end) ? out : (A == b0 ? b1 : b0);
+        ptsbe::InitArgs from;
+        from.Vprev = A;
+        from.stride = (int64_t)1 << cur_rank;
+        from.r0 = cur_rank;
+        const int rank = pp.steps[(size_t)end_step - 1].rC;
+        const ptsbe_status_t st = timed_part_vm(p, pp, d_steps, (int)i, end_step - (int)i, peak, g, cur_n, cur_traj,
+                                                traj_base, job_prefix, from, C, rank, s);
+        if (st != PTSBE_OK) return st;
+        A = C;
+        cur_rank = rank;
+        si = end - 1;
+        continue;
+      }
+    }
     float2* C = (si == last_nf) ? out : (A == b0 ? b1 : b0);
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
     if (p.profile >= 2) {

@@ -50,7 +50,13 @@ inline unsigned grid_blocks(int64_t blocks) {
 }
 constexpr int kMaxQubits = 1024;
 constexpr int kSvMaxQubits = 30;   // statevector method and adjoint pass
-constexpr int kVmMaxRank = 11;      // parts whose tensors fit 2^11 c64 run in LDS
+// Runs of steps whose tensors fit 2^12 c64 are swept in LDS by one launch (two 32 KB
+// buffers, two workgroups of 512 threads per CU).  With 2^11, and only a part's leading
+// steps, the per-trajectory parts of the 50-qubit chain, which move between ranks 10 and
+// 12, went step by step through HBM: 928 launches of 10 us per call at batches of 5 qubits,
+// now 104 of 17 us and 1 ms more in the sweeps (62.2 -> 55.4 ms); at batches of 10 qubits
+// 813 launches and 7.5 ms, now 29 and 1.3 ms, and 1.1 ms more in the sweeps (44.6 -> 39.3).
+constexpr int kVmMaxRank = 12;
 constexpr int kMaxSlices = 4;
 
 // ----------------------------------------------------------------------------
@@ -480,7 +486,7 @@ hipError_t launch_upv_merge(GateCtx g, int64_t E, float2* merged, hipStream_t st
 struct InitArgs {
   const float2* Vprev = nullptr;
   int64_t stride = 1;                 // entries per parent tensor
-  const int32_t* parent = nullptr;    // [job] parent index into Vprev
+  const int32_t* parent = nullptr;    // [job] parent index into Vprev (null: the job's own)
   int r0 = 0;                         // rank of the initial tensor
   int nsl = 0;
   int pos[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // sliced positions in the parent tensor (ascending)

@@ -194,7 +194,7 @@ __device__ inline uint32_t init_offset(const InitArgs& in, uint32_t m, const uin
 constexpr int kVmGateEntries = 512;
 constexpr int kVmMaxJobs = 64;        // jobs per workgroup (one wavefront assigns the trajectory slots)
 
-__global__ void __launch_bounds__(256) part_vm_kernel(const AbsorbStep* __restrict__ steps, int n_steps,
+__global__ void __launch_bounds__(512) part_vm_kernel(const AbsorbStep* __restrict__ steps, int n_steps,
                                                       int buf_elems, int J, GateCtx g, int64_t n_jobs,
                                                       const int32_t* __restrict__ job_traj, int32_t traj_base,
                                                       const uint64_t* __restrict__ job_prefix, int NW,
@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(256) part_vm_kernel(const AbsorbStep* __restri
       const uint32_t n0 = 1u << init.r0;
       const int tpj = nt / J, j = tid / tpj, jl = tid - j * tpj;
       if (j < nj) {
-        const float2* src = init.Vprev + (int64_t)init.parent[job0 + j] * init.stride;
+        const float2* src = init.Vprev + (init.parent ? (int64_t)init.parent[job0 + j] : job0 + j) * init.stride;
         const uint64_t* pj = pw + j * NW;
         float2* dst = bufA + (size_t)j * buf_elems;
         float2 v[8];
@@ -475,7 +475,7 @@ __global__ void init_gather_kernel(InitArgs init, int64_t n_jobs, const uint64_t
     const int64_t job = id / per;
     const uint32_t m = (uint32_t)(id % per);
     const uint64_t* pw = job_prefix + job * NW;
-    out[id] = init.Vprev[(int64_t)init.parent[job] * init.stride + init_offset(init, m, pw)];
+    out[id] = init.Vprev[(init.parent ? (int64_t)init.parent[job] : job) * init.stride + init_offset(init, m, pw)];
   }
 }
 
@@ -2018,10 +2018,10 @@ hipError_t launch_part_vm(const AbsorbStep* d_steps, int n_steps, int peak, Gate
   const int buf = 1 << (peak > 0 ? peak : 0);
   // small tensors: up to 64 jobs share a 256-thread workgroup (2048 entries of
   // tensors in the A and C buffers; peak is the largest rank held in LDS: with
-  // direct, the last step's larger output goes to HBM); one job per workgroup at
-  // 2^11 entries
+  // direct, the last step's larger output goes to HBM); one job per workgroup of 512
+  // threads from 2^11 entries on
   const int J = buf >= 2048 ? 1 : (2048 / buf > kVmMaxJobs ? kVmMaxJobs : 2048 / buf);
-  const int threads = J > 1 ? 256 : (buf / 2 < 64 ? 64 : (buf / 2 > 256 ? 256 : buf / 2));
+  const int threads = J > 1 ? 256 : 512;
   // jobs' tensors one entry apart beyond their size: the same index of
   // neighbouring jobs falls in different LDS banks
   const int stride = J > 1 ? buf + 1 : buf;
