@@ -821,6 +821,15 @@ ptsbe_status_t run_batch(Plan& p, int j, const uint8_t* d_kraus, const float2* m
         HIP_TRY(hipEventCreate(&ev.b));
         HIP_TRY(hipEventRecord(ev.a, s));
       }
+      // the trajectories of this chunk's elements, and the most rows (element, xb) of one of them
+      int64_t tA = t0, tB = t1 - 1;
+      while (tA + 1 < t1 && first[tA + 1] <= a0) ++tA;     // trajectory holding element a0
+      while (tB > tA && first[tB] >= a1) --tB;             // trajectory holding element a1-1
+      int64_t max_rows = 0;
+      for (int64_t t = tA; t <= tB; ++t) {
+        int64_t lo = std::max<int64_t>(first[t], a0), hi = std::min<int64_t>(first[t + 1], a1);
+        max_rows = std::max<int64_t>(max_rows, (hi - lo) << bp.xb.size());
+      }
       if (gemv) {
         if (gemv_lanes) HIP_TRY(ptsbe::launch_ketjoin_gemv_lanes(ja, glanes, s));
         else if (gemv_tiled) HIP_TRY(ptsbe::launch_ketjoin_gemv_tiled(ja, gtile, s));
@@ -832,14 +841,6 @@ ptsbe_status_t run_batch(Plan& p, int j, const uint8_t* d_kraus, const float2* m
         qa.th_plane = n_rt * ((int64_t)1 << ((int)bp.xT.size() + 2 * lkb));
         qa.th_scale = Th ? reinterpret_cast<const int32_t*>(reinterpret_cast<const uint16_t*>(Th) + 2 * qa.th_plane)
                          : nullptr;
-        int64_t tA = t0, tB = t1 - 1;
-        while (tA + 1 < t1 && first[tA + 1] <= a0) ++tA;     // trajectory holding element a0
-        while (tB > tA && first[tB] >= a1) --tB;             // trajectory holding element a1-1
-        int64_t max_rows = 0;
-        for (int64_t t = tA; t <= tB; ++t) {
-          int64_t lo = std::max<int64_t>(first[t], a0), hi = std::min<int64_t>(first[t + 1], a1);
-          max_rows = std::max<int64_t>(max_rows, (hi - lo) << bp.xb.size());
-        }
         qa.traj0 = (int32_t)tA;
         qa.first = d_first; qa.e_lo = a0; qa.e_hi = a1;
         qa.xb_bits = (int)bp.xb.size(); qa.lk_bits = (int)bp.lk.size(); qa.xT_bits = (int)bp.xT.size();
@@ -855,6 +856,8 @@ ptsbe_status_t run_batch(Plan& p, int j, const uint8_t* d_kraus, const float2* m
         } else {
           HIP_TRY(ptsbe::launch_ketjoin(qa, (int)(tB - tA + 1), (int)max_rows, s));
         }
+      } else if (ptsbe::join_rows_supported(ja, tB - tA + 1)) {
+        HIP_TRY(ptsbe::launch_join_rows(ja, d_first, a0, a1, (int32_t)tA, (int)(tB - tA + 1), max_rows, s));
       } else {
         HIP_TRY(ptsbe::launch_join(ja, s));
       }

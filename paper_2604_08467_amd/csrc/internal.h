@@ -534,6 +534,15 @@ struct JoinArgs {
   float2* amp;                           // [n_elems][2^b] (amplitude out) or null
 };
 hipError_t launch_join(const JoinArgs& a, hipStream_t stream);
+// Doubled join of 2^6 .. 2^8 crossing values, for the elements [e_lo, e_hi) of trajectories
+// traj0 .. traj0 + n_traj - 1 (first: [E + 1] first element of each trajectory; max_rows:
+// most rows (element, xb) of one of them).  From 2^6 because a wavefront's 64 lanes take
+// 64 values of k'; up to 2^8 because 16 rows of V then take 32 KB of LDS.
+inline bool join_rows_supported(const JoinArgs& a, int64_t n_traj) {
+  return a.doubled && a.pop && a.lk_bits >= 6 && a.lk_bits <= 8 && n_traj <= 65535;
+}
+hipError_t launch_join_rows(const JoinArgs& a, const int32_t* first, int64_t e_lo, int64_t e_hi, int32_t traj0,
+                            int n_traj, int64_t max_rows, hipStream_t stream);
 // Last-batch join as an HBM-bound GEMV on the right part's own layout (no
 // canonical copy): for elements of at most 4 rows and at least 256 values of x.
 inline bool ketjoin_gemv_supported(int xb_bits, int lk_bits, int xT_bits) {
