@@ -132,6 +132,11 @@ struct SvWin {
   int32_t op_off, n_ops, n_plain, cl_first, n_cl, np;
   int32_t P[12];
   uint32_t other;           // bit mask of the state's qubits outside the window
+  // From |0...0>, before this window only the qubits of earlier windows can be other than
+  // |0>: `live` are those outside the window (tiles with any other bit set are zero and
+  // stay zero), `fresh` the tile positions that no earlier window held (entries with any
+  // of these set are zero on entry; all of them in the first window).
+  uint32_t live, fresh;
 };
 
 struct DeviceGate;
@@ -402,6 +407,7 @@ struct Plan {
   std::vector<SvWin> sv_wins[3];
   std::vector<SvOp> sv_ops[3];
   SvOp* d_sv_ops[3] = {nullptr, nullptr, nullptr};
+  bool sv_covers[3] = {false, false, false};      // every qubit is in some window of the set
   // the same windows with every step a plain op (ragged sets), on the device
   std::vector<SvWin> sv_wins_plain[3];
   std::vector<SvOp> sv_ops_plain[3];
@@ -736,9 +742,12 @@ hipError_t launch_state_init(float2* psi, int64_t n_jobs, int n, hipStream_t str
 // Ucl[job][n_cl_total][256].  precision: PTSBE_C64 (FP32 MFMA for clusters) or
 // PTSBE_SPLIT_BF16 / _F16 (clusters with hi + lo 16-bit operands, three products,
 // FP32 accumulation).
+// grow: the states start as |0...0> and are written by the windows themselves as far as
+// they reach (SvWin::live, fresh); every window of the set has to run that way, and
+// together they have to cover the qubits.
 hipError_t launch_sv_window(const SvWin& w, const SvOp* d_ops, const float2* merged, int G, const float2* Ucl,
                             int n_cl_total, int64_t n_jobs, int32_t traj_base, float2* psi, int n, int precision,
-                            hipStream_t stream);
+                            bool grow, hipStream_t stream);
 // LDS bytes the window kernel needs for a window (0 if it cannot take it).
 size_t sv_window_lds_bytes(const SvWin& w);
 hipError_t launch_copy(const float2* src, float2* dst, int64_t n, hipStream_t stream);
@@ -814,6 +823,7 @@ struct RgPiece {                     // trajectories [t0, t0 + nj) of one job in
   int32_t job, n, f, n_win;
   int32_t t0, nj, traj_off;          // job trajectory range, first wave trajectory
   int32_t log_split0;                // slices per trajectory of the first-batch marginal
+  int32_t grow;                      // swin's windows write the states from |0...0> themselves
   int32_t start[kRgMaxBatches], b[kRgMaxBatches];
 };
 struct RgWave {                      // device arrays of one wave (all in the workspace)

@@ -1031,7 +1031,16 @@ void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& S) {
 
 void build_sv_ops(Plan& p) {
   const uint32_t all = p.n >= 32 ? 0xFFFFFFFFu : ((1u << p.n) - 1u);
+  // live and fresh of a window after the qubits `seen` were in earlier windows
+  auto reach = [](SvWin& w, uint32_t& seen) {
+    w.live = w.other & seen;
+    w.fresh = 0;
+    for (int k = 0; k < w.np; ++k)
+      if (!(seen >> w.P[k] & 1u)) w.fresh |= 1u << k;
+    for (int k = 0; k < w.np; ++k) seen |= 1u << w.P[k];
+  };
   for (int i = 0; i < 3; ++i) {
+    uint32_t seen = 0, seen_plain = 0;
     // plain form: every fused step of every window as its own op
     std::vector<SvWin>& pw = p.sv_wins_plain[i];
     std::vector<SvOp>& po = p.sv_ops_plain[i];
@@ -1048,6 +1057,7 @@ void build_sv_ops(Plan& p) {
         if (k < sg.np) win |= 1u << sg.P[k];
       }
       w.other = all & ~win;
+      reach(w, seen_plain);
       pok = pok && sg.P[0] == 0;
       for (int s = 0; s < sg.count && pok; ++s) {
         const FusedStep& f = p.fused[(size_t)(sg.fused_off + s)];
@@ -1089,6 +1099,7 @@ void build_sv_ops(Plan& p) {
         if (k < sg.np) win |= 1u << sg.P[k];
       }
       w.other = all & ~win;
+      reach(w, seen);
       ok = ok && sg.np >= 1 && sg.P[0] == 0;
       int cl_lo = -1, cl_hi = -1;
       for (int s = 0; s < sg.count && ok;) {
@@ -1130,6 +1141,10 @@ void build_sv_ops(Plan& p) {
       wins.clear();
       ops.clear();
     }
+    seen = 0;
+    for (const Segment& sg : p.sv_win[i])
+      for (int k = 0; k < sg.np; ++k) seen |= 1u << sg.P[k];
+    p.sv_covers[i] = seen == all;
   }
 }
 

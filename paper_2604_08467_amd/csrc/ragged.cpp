@@ -68,6 +68,14 @@ ptsbe_status_t check_jobs(const ptsbe_ragged_s& set, const ptsbe_ragged_job_t* j
   return PTSBE_OK;
 }
 
+// Window set w of the plan runs as compact plain ops: every window has them and a tile of
+// 10 .. 12 qubits.
+bool compact_set(const Plan& p, int w) {
+  bool ok = p.d_sv_ops_plain[w] && p.d_sv_wins_plain[w] && p.sv_wins_plain[w].size() == p.sv_win[w].size();
+  for (const auto& wd : p.sv_wins_plain[w]) ok = ok && wd.np >= 10 && wd.n_ops <= 224;
+  return ok;
+}
+
 int window_choice(const ptsbe_ragged_s& set, const Plan* p) {
   auto it = set.choice.find(p);
   return it == set.choice.end() ? 2 : it->second;
@@ -189,13 +197,13 @@ ptsbe_status_t ptsbe_ragged_autotune(ptsbe_ragged_t set, const ptsbe_ragged_job_
       for (int w = 0; w < 3; ++w) {
         for (int rep = 0; rep < 2; ++rep) {   // the first pass warms up
           HIP_TRY(hipEventRecord(ev[0], s));
-          HIP_TRY(ptsbe::launch_state_init(psi, nt, p.n, s));
           // the pass the set runs: compact plain ops for 10..12-qubit windows, else the generic one
-          const bool compact = p.d_sv_ops_plain[w] && p.sv_wins_plain[w].size() == p.sv_win[w].size();
+          const bool compact = compact_set(p, w), grow = compact && p.sv_covers[w];
+          if (!grow) HIP_TRY(ptsbe::launch_state_init(psi, nt, p.n, s));
           for (size_t k = 0; k < p.sv_win[w].size(); ++k) {
-            if (compact && p.sv_wins_plain[w][k].np >= 10 && p.sv_wins_plain[w][k].n_ops <= 224)
+            if (compact)
               HIP_TRY(ptsbe::launch_sv_window(p.sv_wins_plain[w][k], p.d_sv_ops_plain[w], merged, p.G, nullptr, 0,
-                                              nt, 0, psi, p.n, PTSBE_C64, s));
+                                              nt, 0, psi, p.n, PTSBE_C64, grow, s));
             else
               HIP_TRY(ptsbe::launch_fused(p.sv_win[w][k], p.d_fused, g, nt, nullptr, 0, nullptr, p.NW, psi, s));
           }
@@ -352,11 +360,10 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
       pc.psi = (float2*)wa.take((size_t)ps.nj * ((size_t)8 << p.n));
       pc.win = p.d_rg_win[wc];
       pc.fused = p.d_fused;
-      // compact plain ops when every window of the set has them and a 10..12-qubit tile
-      bool compact = p.d_sv_wins_plain[wc] && p.sv_wins_plain[wc].size() == p.sv_win[wc].size();
-      for (const auto& wd : p.sv_wins_plain[wc]) compact = compact && wd.np >= 10 && wd.n_ops <= 224;
+      const bool compact = compact_set(p, wc);
       pc.swin = compact ? p.d_sv_wins_plain[wc] : nullptr;
       pc.sops = compact ? p.d_sv_ops_plain[wc] : nullptr;
+      pc.grow = compact && p.sv_covers[wc];
       pc.shots = jb.d_shots;
       pc.norms = norms[ps.job];
       pc.row0 = row;
@@ -442,11 +449,12 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
       for (int k = 0; k < P; ++k) {
         if (pcs[k].n_win <= l) continue;
         const Plan& p = *reinterpret_cast<const Plan*>(jobs[pcs[k].job].plan);
-        const int np = p.sv_win[window_choice(*set, &p)][l].np;
-        if (pcs[k].swin) max_ops = std::max(max_ops, p.sv_wins_plain[window_choice(*set, &p)][l].n_ops);
+        const int wc = window_choice(*set, &p);
+        if (pcs[k].swin) max_ops = std::max(max_ops, p.sv_wins_plain[wc][l].n_ops);
         lp.push_back(k);
         ls.push_back(tasks);
-        tasks += (int64_t)pcs[k].nj << (pcs[k].n - np);
+        tasks += (int64_t)pcs[k].nj << (pcs[k].grow ? __builtin_popcount(p.sv_wins_plain[wc][l].live)
+                                                    : pcs[k].n - p.sv_win[wc][l].np);
       }
       RgLevel lv{};
       lv.piece = (const int32_t*)put(lp.data(), lp.size() * 4);

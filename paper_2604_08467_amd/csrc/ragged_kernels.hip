@@ -76,14 +76,14 @@ __global__ void rg_start_kernel(RgWave w) {
   *w.bad_flag = 0;
 }
 
-// |0...0> states, UPV-merged gates of every piece, shot rows and first-batch elements.
+// |0...0> states (where the windows do not write them themselves), UPV-merged gates of every piece, shot rows and first-batch elements.
 __global__ void __launch_bounds__(kRgThreads) rg_prepare_kernel(RgWave w) {
   const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int p = 0; p < w.n_pieces; ++p) {
     const RgPiece& pc = w.pieces[p];
     const int64_t sz = (int64_t)pc.nj << pc.n, mask = ((int64_t)1 << pc.n) - 1;
-    for (int64_t i = gid; i < sz; i += stride) pc.psi[i] = make_float2((i & mask) == 0 ? 1.f : 0.f, 0.f);
+    for (int64_t i = pc.grow ? sz : gid; i < sz; i += stride) pc.psi[i] = make_float2((i & mask) == 0 ? 1.f : 0.f, 0.f);
     float2* merged = const_cast<float2*>(pc.g.merged);
     for (int64_t id = gid; id < (int64_t)pc.nj * pc.g.G; id += stride) {
       float2 m[16];
@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(kRgThreads) rg_window_kernel(RgWave w, RgLevel
     const int e = find_le(lv.start, lv.n, task);
     const RgPiece& pc = w.pieces[lv.piece[e]];
     const RgWindow& wd = pc.win[level];
-    const int tb = pc.n - wd.np;
+    const int tb = pc.grow ? __popc(pc.swin[level].live) : pc.n - wd.np;
     const int64_t local = task - lv.start[e];
     const int64_t traj = local >> tb;
     const uint32_t t = (uint32_t)(local & (((int64_t)1 << tb) - 1));
@@ -145,10 +145,11 @@ __global__ void __launch_bounds__(kRgThreads) rg_window_kernel(RgWave w, RgLevel
         }
         __syncthreads();
       }
-      float2* A = pc.psi + (traj << pc.n) + deposit_other(t, sw.other);
-      if (sw.np == 12) plain_tile_pass<12>(ops, sw.n_ops, sw.P, A, A, tile, Gm);
-      else if (sw.np == 11) plain_tile_pass<11>(ops, sw.n_ops, sw.P, A, A, tile, Gm);
-      else plain_tile_pass<10>(ops, sw.n_ops, sw.P, A, A, tile, Gm);
+      float2* A = pc.psi + (traj << pc.n) + deposit_other(t, pc.grow ? sw.live : sw.other);
+      const uint32_t fresh = pc.grow ? sw.fresh : 0u;
+      if (sw.np == 12) plain_tile_pass<12>(ops, sw.n_ops, sw.P, A, A, tile, Gm, fresh);
+      else if (sw.np == 11) plain_tile_pass<11>(ops, sw.n_ops, sw.P, A, A, tile, Gm, fresh);
+      else plain_tile_pass<10>(ops, sw.n_ops, sw.P, A, A, tile, Gm, fresh);
     } else {
       const bool ready = same && wd.n_fs <= kGateChunk && last_pc && !last_pc->swin;
       window_tile_pass(pc.fused + wd.fused_off, wd.n_fs, wd.P, wd.np, pc.n, t, pc.psi + (traj << pc.n), pc.g,

@@ -75,26 +75,38 @@ ptsbe_status_t collect_window_events(Plan& p) {
 
 ptsbe_status_t sv_evolve(Plan& p, const GateCtx& g, int64_t t0, int64_t nj, float2* psi, float2* Ucl,
                          hipStream_t s) {
-  HIP_TRY(launch_state_init(psi, nj, p.n, s));
+  const bool compact = p.sv_wins[2].size() == p.sv_segs.size() && p.d_sv_ops[2];
+  auto fits = [&](size_t k) {
+    const size_t b = compact ? sv_window_lds_bytes(p.sv_wins[2][k]) : 0;
+    return b != 0 && b <= 64 * 1024;
+  };
+  // the windows write the states from |0...0> themselves if all of them take the window
+  // kernel and they reach every qubit
+  bool grow = p.sv_covers[2] && !p.sv_segs.empty();
+  for (size_t k = 0; k < p.sv_segs.size(); ++k) grow = grow && fits(k);
+  if (!grow) HIP_TRY(launch_state_init(psi, nj, p.n, s));
   const int n_cl = Ucl ? (int)p.sv_cl[2].size() : 0;
   if (n_cl > 0) HIP_TRY(launch_cluster_build(p.d_sv_cl[2], n_cl, p.d_fused, g, nj, nullptr, (int32_t)t0, Ucl, s));
-  const bool compact = p.sv_wins[2].size() == p.sv_segs.size() && p.d_sv_ops[2];
   for (size_t k = 0; k < p.sv_segs.size(); ++k) {
     const Segment& sg = p.sv_segs[k];
-    if (compact && sv_window_lds_bytes(p.sv_wins[2][k]) != 0 && sv_window_lds_bytes(p.sv_wins[2][k]) <= 64 * 1024) {
+    if (fits(k)) {
+      const SvWin& w = p.sv_wins[2][k];
       std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
       if (p.profile) {
         HIP_TRY(hipEventCreate(&ev.first));
         HIP_TRY(hipEventCreate(&ev.second));
         HIP_TRY(hipEventRecord(ev.first, s));
       }
-      HIP_TRY(launch_sv_window(p.sv_wins[2][k], p.d_sv_ops[2], g.merged, p.G, Ucl, n_cl, nj, (int32_t)t0, psi, p.n,
-                               p.precision, s));
+      HIP_TRY(launch_sv_window(w, p.d_sv_ops[2], g.merged, p.G, Ucl, n_cl, nj, (int32_t)t0, psi, p.n, p.precision, grow,
+                               s));
       if (p.profile) {
         HIP_TRY(hipEventRecord(ev.second, s));
         p.win_evs.push_back(ev);
         ++p.win_launches;
-        p.win_bytes += (double)nj * 16.0 * std::ldexp(1.0, p.n);   // every state read and written once
+        // every tile written once, and read once but for its fresh positions
+        const uint32_t live = grow ? w.live : w.other, fresh = grow ? w.fresh : 0u;
+        const double out = (double)nj * std::ldexp(8.0, w.np + __builtin_popcount(live));
+        p.win_bytes += out + ((fresh & 1u) ? 0.0 : std::ldexp(out, -__builtin_popcount(fresh)));
       }
       continue;
     }

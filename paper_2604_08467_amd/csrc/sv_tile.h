@@ -33,7 +33,8 @@ __device__ inline uint32_t ins0(uint32_t m, int p) {   // zero bit inserted at p
 
 struct SvwArgs {
   int n, np, n_ops, n_plain, n_cl, cl_first, n_cl_total, G;
-  uint32_t other;          // bit mask of the qubits outside the window
+  uint32_t live;           // bit mask of the qubits outside the window that tiles are made over
+  uint32_t fresh;          // tile positions whose qubits are still |0> on entry
   int P[kFuseMax];
   int64_t n_jobs;
   int32_t traj_base;
@@ -314,6 +315,23 @@ __device__ inline void load_pairs(const float2* __restrict__ A, const int* P, ui
   for (int i = 0; i < (1 << (NP - 9)); ++i) v[i] = *reinterpret_cast<const floatx4_t*>(A + (lo | pair_hi<NP>(P, i)));
 }
 
+// As load_pairs, for a tile whose positions in `fresh` are still |0>: entries with any of
+// them set are zero and not read.  Position 0 is fresh in the first window only, where
+// every position is and the tile is |0...0>.
+template <int NP>
+__device__ inline void load_fresh_pairs(const float2* __restrict__ A, const int* P, uint32_t lo, uint32_t fresh,
+                                        floatx4_t (&v)[1 << (NP - 9)]) {
+  const uint32_t e = 2u * threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < (1 << (NP - 9)); ++i) {
+    v[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    if (((e + 2u * kSvwThreads * i) & fresh) == 0) {
+      if (fresh & 1u) v[i][0] = 1.f;
+      else v[i] = *reinterpret_cast<const floatx4_t*>(A + (lo | pair_hi<NP>(P, i)));
+    }
+  }
+}
+
 // This thread's pair offset from its own bits (tile bits 1..8 = positions P[1..8]).
 __device__ inline uint32_t pair_lo(const int* P) {
   uint32_t lo = 0;
@@ -345,18 +363,19 @@ __device__ inline floatx4_t lds_get_pair(const floatx4_t* tile4, uint32_t pt2, i
 // One tile of a window of plain gates (no clusters): pairs loaded from Ain, the
 // ops applied in LDS (gate matrices staged in Gs), pairs stored to Aout (Ain and
 // Aout: the tile's first amplitude in the input and output states, which may be
-// the same).  Op records are 32 bytes with kind, p0 and p1 in the low three bytes
+// the same; fresh as in load_fresh_pairs).  Op records are 32 bytes with kind, p0 and p1 in the low three bytes
 // of the first dword and the staged matrix slot in the fourth (SvOp, AdjOp).
 // Ends with a barrier.
 template <int NP, typename Op>
 __device__ inline void plain_tile_pass(const Op* __restrict__ ops, int n_ops, const int* P, const float2* Ain,
-                                       float2* Aout, float2* tile, const float2* Gs) {
+                                       float2* Aout, float2* tile, const float2* Gs, uint32_t fresh = 0) {
   static_assert(sizeof(Op) == 32, "op records are eight dwords");
   constexpr int PPT = 1 << (NP - 9);
   floatx4_t* tile4 = reinterpret_cast<floatx4_t*>(tile);
   const uint32_t lo = pair_lo(P), pt2 = swz(2u * threadIdx.x);
   floatx4_t v[PPT];
-  load_pairs<NP>(Ain, P, lo, v);
+  if (fresh) load_fresh_pairs<NP>(Ain, P, lo, fresh, v);
+  else load_pairs<NP>(Ain, P, lo, v);
 #pragma unroll
   for (int i = 0; i < PPT; ++i) lds_put_pair(tile4, pt2, i, v[i]);
   __syncthreads();
