@@ -113,17 +113,24 @@ struct ClusterDesc {
 
 // Compact op of a statevector gate window, read by the window kernel through the
 // scalar cache: a plain one- or two-qubit gate applied in place on the LDS tile,
-// or a gate cluster (a 16 x 16 matrix on four tile positions, applied on MFMA).
-enum { kSvOpGate1 = 1, kSvOpGate2 = 2, kSvOpCluster = 3 };
+// or a gate cluster (a 16 x 16 matrix on four tile positions, applied on MFMA).  A run
+// of gates on at most np - 8 positions follows a group record: 256 threads take the
+// tile's 2^np amplitudes over those positions into registers, 2^(np - 8) each, apply the
+// group's gates there in order, and put them back.
+enum { kSvOpGate1 = 1, kSvOpGate2 = 2, kSvOpCluster = 3, kSvOpGroup = 4 };
 struct SvOp {
   int8_t kind;
-  int8_t p0, p1;            // gate: tile positions of local index bits 0 and 1
+  int8_t p0, p1;            // gate: tile positions of local index bits 0 and 1; group: p0 gates follow
   int8_t conj;              // gate: use the complex conjugate of the merged matrix
-  int8_t cpos[4];           // cluster: tile position of cluster-local bit i
+  int8_t cpos[4];           // cluster: tile position of cluster-local bit i; group: of register bit i;
+                            // gate: cpos[0] = register bit (one qubit) or bit pair (svg_pair)
   int32_t gate;             // gate: index into the trajectory's merged gates
-  int32_t slot;             // gate: staged matrix slot; cluster: index within the window
+  int32_t slot;             // gate: staged matrix slot; cluster: index within the window;
+                            // group: gate and slot hold the tile positions of thread bits 0 .. 7, a byte each
   int8_t idx[16];           // gate: local entry (n, k), n * d + k, is merged entry idx[n * d + k]
 };
+// Number of the register bit pair i < j < 4 of a two-qubit gate in a group.
+constexpr int svg_pair(int i, int j) { return i == 0 ? j - 1 : i + j; }   // 01 02 03 12 13 23
 static_assert(sizeof(SvOp) == 32, "SvOp is read as eight dwords");
 // One window of a statevector schedule in compact form: ops [op_off, op_off + n_ops)
 // on the tile positions P (|P| = np, P[0] == 0), n_plain staged gate matrices and

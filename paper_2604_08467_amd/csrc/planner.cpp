@@ -1029,6 +1029,88 @@ void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& S) {
   S.ok = true;
 }
 
+namespace {
+// The gates of a window's ops (in order, np tile positions) gathered into groups: a gate
+// joins the open group while its positions and the group's are at most np - 8 and some
+// order of them has every two-qubit gate's local bit 0 below its local bit 1 (the
+// kernels' register form; the chains and grids list their pairs that way throughout).
+// The order of the ops is kept, so that every amplitude sees the same products.
+void group_sv_ops(const std::vector<SvOp>& in, int np, std::vector<SvOp>& out) {
+  const int cap = np - 8;
+  auto order_of = [](std::vector<int> q, const std::vector<SvOp>& gs, std::vector<int>& found) {
+    std::sort(q.begin(), q.end());
+    do {
+      auto at = [&](int p) { return std::find(q.begin(), q.end(), p) - q.begin(); };
+      bool ok = true;
+      for (const SvOp& g : gs) ok = ok && (g.kind != kSvOpGate2 || at(g.p0) < at(g.p1));
+      if (ok) {
+        found = q;
+        return true;
+      }
+    } while (std::next_permutation(q.begin(), q.end()));
+    return false;
+  };
+  std::vector<SvOp> gates;
+  std::vector<int> order;            // positions of the open group, register bit order
+  auto close = [&]() {
+    if (gates.empty()) return;
+    auto in_order = [&](int p) { return std::find(order.begin(), order.end(), p) != order.end(); };
+    // unused register bits take the highest positions left: those of low index spread the
+    // lanes of a quarter wavefront over the LDS banks
+    for (int p = np - 1; (int)order.size() < cap; --p)
+      if (!in_order(p)) order.push_back(p);
+    // thread bits 0..3: positions of different swizzled slot bits (p mod 4, p < 8) where there are
+    std::vector<int> rest, lanes;
+    for (int p = 0; p < np; ++p)
+      if (!in_order(p)) rest.push_back(p);
+    for (int m = 0; m < 4; ++m)
+      for (size_t k = 0; k < rest.size(); ++k)
+        if (rest[k] < 8 && rest[k] % 4 == m) {
+          lanes.push_back(rest[k]);
+          rest.erase(rest.begin() + (std::ptrdiff_t)k);
+          break;
+        }
+    lanes.insert(lanes.end(), rest.begin(), rest.end());
+    SvOp h{};
+    h.kind = kSvOpGroup;
+    h.p0 = (int8_t)gates.size();
+    for (int i = 0; i < cap; ++i) h.cpos[i] = (int8_t)order[(size_t)i];
+    uint32_t t[2] = {0, 0};
+    for (int b = 0; b < 8; ++b) t[b >> 2] |= (uint32_t)lanes[(size_t)b] << (8 * (b & 3));
+    h.gate = (int32_t)t[0];
+    h.slot = (int32_t)t[1];
+    out.push_back(h);
+    auto at = [&](int p) { return (int)(std::find(order.begin(), order.end(), p) - order.begin()); };
+    for (SvOp& g : gates) {
+      g.cpos[0] = (int8_t)(g.kind == kSvOpGate1 ? at(g.p0) : svg_pair(at(g.p0), at(g.p1)));
+      out.push_back(g);
+    }
+    gates.clear();
+    order.clear();
+  };
+  for (const SvOp& op : in) {
+    if (op.kind == kSvOpCluster) {
+      close();
+      out.push_back(op);
+      continue;
+    }
+    for (int tries = 0; tries < 2; ++tries) {
+      std::vector<int> q = order, found;
+      for (int p : {(int)op.p0, op.kind == kSvOpGate2 ? (int)op.p1 : (int)op.p0})
+        if (std::find(q.begin(), q.end(), p) == q.end()) q.push_back(p);
+      gates.push_back(op);
+      if ((int)q.size() <= cap && (int)gates.size() <= 100 && order_of(q, gates, found)) {
+        order = found;
+        break;
+      }
+      gates.pop_back();
+      close();                       // the gate opens the next group
+    }
+  }
+  close();
+}
+}  // namespace
+
 void build_sv_ops(Plan& p) {
   const uint32_t all = p.n >= 32 ? 0xFFFFFFFFu : ((1u << p.n) - 1u);
   // live and fresh of a window after the qubits `seen` were in earlier windows
@@ -1059,6 +1141,7 @@ void build_sv_ops(Plan& p) {
       w.other = all & ~win;
       reach(w, seen_plain);
       pok = pok && sg.P[0] == 0;
+      std::vector<SvOp> wo;
       for (int s = 0; s < sg.count && pok; ++s) {
         const FusedStep& f = p.fused[(size_t)(sg.fused_off + s)];
         const bool plain = f.nH == 0 && f.nS == 0 && f.nK == f.nN && f.nK >= 1 && f.nK <= 2 &&
@@ -1074,9 +1157,10 @@ void build_sv_ops(Plan& p) {
         const int d = 1 << f.nK;
         for (int n = 0; n < d; ++n)
           for (int k = 0; k < d; ++k) op.idx[n * d + k] = (int8_t)(f.nB[n] + f.kB[k]);
-        po.push_back(op);
+        wo.push_back(op);
       }
       if (!pok) break;
+      if (sg.np >= 10) group_sv_ops(wo, sg.np, po);      // smaller tiles take the generic pass
       w.n_ops = (int32_t)po.size() - w.op_off;
       pw.push_back(w);
     }
@@ -1101,6 +1185,7 @@ void build_sv_ops(Plan& p) {
       w.other = all & ~win;
       reach(w, seen);
       ok = ok && sg.np >= 1 && sg.P[0] == 0;
+      std::vector<SvOp> wo;
       int cl_lo = -1, cl_hi = -1;
       for (int s = 0; s < sg.count && ok;) {
         const FusedStep& f = p.fused[(size_t)(sg.fused_off + s)];
@@ -1127,9 +1212,10 @@ void build_sv_ops(Plan& p) {
             for (int k = 0; k < d; ++k) op.idx[n * d + k] = (int8_t)(f.nB[n] + f.kB[k]);
           ++s;
         }
-        ops.push_back(op);
+        wo.push_back(op);
       }
       if (!ok) break;
+      if (sg.np >= 10) group_sv_ops(wo, sg.np, ops);
       w.n_ops = (int32_t)ops.size() - w.op_off;
       w.cl_first = cl_lo < 0 ? 0 : cl_lo;
       w.n_cl = cl_lo < 0 ? 0 : cl_hi - cl_lo + 1;

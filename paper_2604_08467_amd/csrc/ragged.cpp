@@ -70,9 +70,10 @@ ptsbe_status_t check_jobs(const ptsbe_ragged_s& set, const ptsbe_ragged_job_t* j
 
 // Window set w of the plan runs as compact plain ops: every window has them and a tile of
 // 10 .. 12 qubits.
+constexpr int kRgMaxGates = 224;      // staged gates of a window: with the tile and their forms 64 KB of LDS
 bool compact_set(const Plan& p, int w) {
   bool ok = p.d_sv_ops_plain[w] && p.d_sv_wins_plain[w] && p.sv_wins_plain[w].size() == p.sv_win[w].size();
-  for (const auto& wd : p.sv_wins_plain[w]) ok = ok && wd.np >= 10 && wd.n_ops <= 224;
+  for (const auto& wd : p.sv_wins_plain[w]) ok = ok && wd.np >= 10 && wd.n_plain <= kRgMaxGates;
   return ok;
 }
 
@@ -450,7 +451,7 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
         if (pcs[k].n_win <= l) continue;
         const Plan& p = *reinterpret_cast<const Plan*>(jobs[pcs[k].job].plan);
         const int wc = window_choice(*set, &p);
-        if (pcs[k].swin) max_ops = std::max(max_ops, p.sv_wins_plain[wc][l].n_ops);
+        if (pcs[k].swin) max_ops = std::max(max_ops, p.sv_wins_plain[wc][l].n_plain);
         lp.push_back(k);
         ls.push_back(tasks);
         tasks += (int64_t)pcs[k].nj << (pcs[k].grow ? __builtin_popcount(p.sv_wins_plain[wc][l].live)

@@ -111,10 +111,11 @@ __global__ void __launch_bounds__(kRgThreads) rg_prepare_kernel(RgWave w) {
 
 // Window level `level`: every 2^np tile of every trajectory of every piece that
 // has that many windows; tiles of heavier circuits come first in the queue.
-__global__ void __launch_bounds__(kRgThreads) rg_window_kernel(RgWave w, RgLevel lv, int level) {
+__global__ void __launch_bounds__(kRgThreads, 4) rg_window_kernel(RgWave w, RgLevel lv, int level) {
   extern __shared__ float2 lds[];
   float2* tile = lds;
-  float2* Gm = lds + (1 << kFuseMax);   // staged gates: generic chunks, or one 16-entry slot per op
+  float2* Gm = lds + (1 << kFuseMax);   // staged gates: generic chunks, or one 16-entry slot per gate
+  uint32_t* forms = reinterpret_cast<uint32_t*>(Gm + 16 * (lv.max_ops > kGateChunk ? lv.max_ops : kGateChunk));
   __shared__ uint64_t pw[1];
   if (threadIdx.x == 0) pw[0] = 0ull;
   // contiguous task ranges per workgroup: consecutive tiles of one trajectory
@@ -138,18 +139,13 @@ __global__ void __launch_bounds__(kRgThreads) rg_window_kernel(RgWave w, RgLevel
       const SvOp* ops = pc.sops + sw.op_off;
       if (!same) {
         __syncthreads();   // nobody reads the previous trajectory's gates any more
-        for (int i = threadIdx.x; i < 16 * sw.n_ops; i += kRgThreads) {
-          const SvOp& op = ops[i >> 4];
-          const int el = i & 15, d2 = op.kind == kSvOpGate1 ? 4 : 16;
-          Gm[i] = el < d2 ? pc.g.merged[(traj * pc.g.G + op.gate) * 16 + op.idx[el]] : make_float2(0.f, 0.f);
-        }
-        __syncthreads();
+        stage_gates(ops, sw.n_ops, pc.g.merged + traj * pc.g.G * 16, Gm, forms);
       }
       float2* A = pc.psi + (traj << pc.n) + deposit_other(t, pc.grow ? sw.live : sw.other);
       const uint32_t fresh = pc.grow ? sw.fresh : 0u;
-      if (sw.np == 12) plain_tile_pass<12>(ops, sw.n_ops, sw.P, A, A, tile, Gm, fresh);
-      else if (sw.np == 11) plain_tile_pass<11>(ops, sw.n_ops, sw.P, A, A, tile, Gm, fresh);
-      else plain_tile_pass<10>(ops, sw.n_ops, sw.P, A, A, tile, Gm, fresh);
+      if (sw.np == 12) plain_tile_pass<12>(ops, sw.n_ops, sw.P, A, fresh, tile, Gm, forms);
+      else if (sw.np == 11) plain_tile_pass<11>(ops, sw.n_ops, sw.P, A, fresh, tile, Gm, forms);
+      else plain_tile_pass<10>(ops, sw.n_ops, sw.P, A, fresh, tile, Gm, forms);
     } else {
       const bool ready = same && wd.n_fs <= kGateChunk && last_pc && !last_pc->swin;
       window_tile_pass(pc.fused + wd.fused_off, wd.n_fs, wd.P, wd.np, pc.n, t, pc.psi + (traj << pc.n), pc.g,
@@ -442,7 +438,8 @@ hipError_t launch_rg_prepare(const RgWave& w, int grid, hipStream_t s) {
 
 hipError_t launch_rg_window(const RgWave& w, const RgLevel& lv, int level, int n_cu, hipStream_t s) {
   if (lv.tasks <= 0) return hipSuccess;
-  const size_t shmem = (((size_t)1 << kFuseMax) + 16 * (size_t)std::max(kGateChunk, (int)lv.max_ops)) * sizeof(float2);
+  const size_t shmem = (((size_t)1 << kFuseMax) + 16 * (size_t)std::max(kGateChunk, (int)lv.max_ops)) * sizeof(float2) +
+                       (size_t)lv.max_ops * sizeof(uint32_t);
   // a persistent grid is only as large as what fits on the chip at once
   int per_cu = 0;
   hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rg_window_kernel, kRgThreads, shmem);

@@ -76,10 +76,7 @@ ptsbe_status_t collect_window_events(Plan& p) {
 ptsbe_status_t sv_evolve(Plan& p, const GateCtx& g, int64_t t0, int64_t nj, float2* psi, float2* Ucl,
                          hipStream_t s) {
   const bool compact = p.sv_wins[2].size() == p.sv_segs.size() && p.d_sv_ops[2];
-  auto fits = [&](size_t k) {
-    const size_t b = compact ? sv_window_lds_bytes(p.sv_wins[2][k]) : 0;
-    return b != 0 && b <= 64 * 1024;
-  };
+  auto fits = [&](size_t k) { return compact && sv_window_lds_bytes(p.sv_wins[2][k]) != 0; };
   // the windows write the states from |0...0> themselves if all of them take the window
   // kernel and they reach every qubit
   bool grow = p.sv_covers[2] && !p.sv_segs.empty();

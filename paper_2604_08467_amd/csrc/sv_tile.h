@@ -1,5 +1,5 @@
 // Device helpers of the statevector gate windows (included by the window kernel
-// and the ragged-set kernels; everything here is inline): the compact ops' gate
+// and the ragged-set kernels; everything here is inline): the compact ops' group
 // and cluster applications on an LDS tile of 2^NP amplitudes, and the 16-byte
 // amplitude-pair tile loads.  Qubit 0 is tile bit 0, so a pair of amplitudes is
 // one 16-byte run of the state.
@@ -206,93 +206,191 @@ __device__ inline void apply_cluster_f32(const ClusterCols& cc, const float2* __
 
 __device__ inline bool czero(float2 v) { return v.x == 0.f && v.y == 0.f; }
 
-// A one-qubit gate in place on tile position p (g: [n][k] row-major).
-template <int NP>
-__device__ inline void apply_gate1(const float2* __restrict__ G, int p, float2* tile) {
-  constexpr uint32_t nt = 1u << NP;
-  const float2 g00 = G[0], g01 = G[1], g10 = G[2], g11 = G[3];
-  // pair (lb, lb + 2^p), lb = ins0(tid + 256 i, p): swizzled as the thread's part
-  // XOR the uniform part of iteration i
-  const uint32_t pt = swz(ins0(threadIdx.x, p)), so = swz(1u << p);
-  if ((czero(g00) || czero(g01)) && (czero(g10) || czero(g11))) {
-    // monomial (diagonal or anti-diagonal): one product per amplitude
-    const bool swap0 = czero(g00), swap1 = czero(g11);
-    const float2 d0 = swap0 ? g01 : g00, d1 = swap1 ? g10 : g11;
-#pragma unroll 2
-    for (uint32_t i = 0; i < (nt >> 1) / kSvwThreads; ++i) {
-      const uint32_t l0 = pt ^ swz(ins0(kSvwThreads * i, p)), l1 = l0 ^ so;
-      const float2 a0 = tile[l0], a1 = tile[l1];
-      tile[l0] = cmul(d0, swap0 ? a1 : a0);
-      tile[l1] = cmul(d1, swap1 ? a0 : a1);
-    }
+// Forms of a staged gate, worked out once per staging: at most one nonzero a row
+// (diagonal gates with diagonal Kraus factors, CNOT, Pauli products) costs one product
+// per amplitude.  Bits 2n, 2n + 1: the column of row n's nonzero.
+constexpr uint32_t kFormDense = 0x100, kFormDiag = 0x200;
+
+__device__ inline uint32_t gate1_form(const float2* G) {
+  const bool z00 = czero(G[0]), z01 = czero(G[1]), z10 = czero(G[2]), z11 = czero(G[3]);
+  if (!((z00 || z01) && (z10 || z11))) return kFormDense;
+  return (!z00 && !z11) ? kFormDiag : (uint32_t)z00 | ((uint32_t)!z11 << 2);
+}
+__device__ inline uint32_t gate2_form(const float2* G) {
+  uint32_t form = 0;
+  bool mono = true, diag = true;
+  for (int n = 0; n < 4; ++n) {
+    int col = -1;
+    for (int k = 0; k < 4; ++k)
+      if (!czero(G[4 * n + k])) {
+        mono = mono && col < 0;
+        col = k;
+      }
+    diag = diag && (col < 0 || col == n);
+    form |= (uint32_t)(col < 0 ? 3 : col) << (2 * n);
+  }
+  return mono ? (diag ? kFormDiag : form) : kFormDense;
+}
+
+// A value that all lanes hold, in scalar registers (a gate entry there leaves the vector
+// registers to the amplitudes).
+__device__ inline float2 uniform2(float2 v) {
+  return make_float2(__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v.x))),
+                     __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v.y))));
+}
+
+// g a with its roundings spelled out, so that they do not hang on how a kernel is compiled.
+__device__ inline float2 gmul(float2 g, float2 a) {
+  return make_float2(fmaf(g.x, a.x, -(g.y * a.y)), fmaf(g.y, a.x, g.x * a.y));
+}
+
+// A one-qubit gate on register bit B of x (g: [n][k] row-major in LDS).
+template <int LB, int B>
+__device__ __forceinline__ void reg_gate1(float2 (&x)[1 << LB], const float2* G, uint32_t form) {
+  const float2 g00 = uniform2(G[0]), g01 = uniform2(G[1]), g10 = uniform2(G[2]), g11 = uniform2(G[3]);
+  if (form == kFormDense) {
+#pragma unroll
+    for (int l = 0; l < (1 << LB); ++l)
+      if (!(l >> B & 1)) {
+        const float2 a0 = x[l], a1 = x[l | 1 << B];
+        x[l] = cfma(g01, a1, gmul(g00, a0));
+        x[l | 1 << B] = cfma(g11, a1, gmul(g10, a0));
+      }
+  } else if (form == kFormDiag) {
+#pragma unroll
+    for (int l = 0; l < (1 << LB); ++l) x[l] = gmul(l >> B & 1 ? g11 : g00, x[l]);
   } else {
-#pragma unroll 2
-    for (uint32_t i = 0; i < (nt >> 1) / kSvwThreads; ++i) {
-      const uint32_t l0 = pt ^ swz(ins0(kSvwThreads * i, p)), l1 = l0 ^ so;
-      const float2 a0 = tile[l0], a1 = tile[l1];
-      tile[l0] = cfma(g01, a1, cmul(g00, a0));
-      tile[l1] = cfma(g11, a1, cmul(g10, a0));
+    const bool c0 = form & 1u, c1 = form & 4u;       // rows 0 and 1 take amplitude 1
+    const float2 d0 = c0 ? g01 : g00, d1 = c1 ? g11 : g10;
+#pragma unroll
+    for (int l = 0; l < (1 << LB); ++l)
+      if (!(l >> B & 1)) {
+        const float2 a0 = x[l], a1 = x[l | 1 << B];
+        x[l] = gmul(d0, c0 ? a1 : a0);
+        x[l | 1 << B] = gmul(d1, c1 ? a1 : a0);
+      }
+  }
+}
+
+// A two-qubit gate on register bits I (local bit 0) < J (local bit 1) of x.
+template <int LB, int I, int J>
+__device__ __forceinline__ void reg_gate2(float2 (&x)[1 << LB], const float2* G, uint32_t form) {
+  constexpr int o[4] = {0, 1 << I, 1 << J, 1 << I | 1 << J};
+  if (form == kFormDense) {
+    float2 g[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) g[i] = uniform2(G[i]);
+#pragma unroll
+    for (int l = 0; l < (1 << LB); ++l)
+      if (!(l & o[3])) {
+        const float2 a0 = x[l], a1 = x[l | o[1]], a2 = x[l | o[2]], a3 = x[l | o[3]];
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+          x[l | o[n]] = cfma(g[4 * n + 3], a3, cfma(g[4 * n + 2], a2, cfma(g[4 * n + 1], a1, gmul(g[4 * n], a0))));
+        __builtin_amdgcn_sched_barrier(0);   // one quad at a time: eight chains, few registers
+      }
+  } else if (form == kFormDiag) {
+    float2 g[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) g[n] = uniform2(G[5 * n]);
+#pragma unroll
+    for (int l = 0; l < (1 << LB); ++l)
+      if (!(l & o[3]))
+#pragma unroll
+        for (int n = 0; n < 4; ++n) x[l | o[n]] = gmul(g[n], x[l | o[n]]);
+  } else {
+    float2 g[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) g[n] = uniform2(G[4 * n + (form >> (2 * n) & 3u)]);
+#pragma unroll
+    for (int l = 0; l < (1 << LB); ++l)
+      if (!(l & o[3])) {
+        const float2 a0 = x[l], a1 = x[l | o[1]], a2 = x[l | o[2]], a3 = x[l | o[3]];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+          const uint32_t c = form >> (2 * n) & 3u;
+          x[l | o[n]] = gmul(g[n], c == 0 ? a0 : c == 1 ? a1 : c == 2 ? a2 : a3);
+        }
+      }
+  }
+}
+
+// The n gates after a group record (h: its first four dwords) on the tile: 2^(NP - 8)
+// amplitudes a thread in registers.  One LDS pass and one barrier for all of them: a pass
+// per gate cost 0.5 ms on a 12.9 GB set of states (25 qubits x 48), three times its own
+// arithmetic, and a window of 14 gates 12.1 ms where it takes 8.3 now (5.3 ms to read and
+// write the states).  group_sv_ops has which gates share a group.
+template <int NP>
+__device__ __forceinline__ void apply_group(const uint4 h, const uint4* __restrict__ ops, int n, float2* tile,
+                                   const float2* Gs, const uint32_t* forms) {
+  constexpr int LB = NP - 8;
+  const uint32_t tid = threadIdx.x;
+  uint32_t pt = 0;                 // this thread's part of the address, then the register bits'
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const uint32_t p = ((b < 4 ? h.z : h.w) >> (8 * (b & 3))) & 0xffu;
+    pt ^= (tid >> b & 1u) ? swz(1u << p) : 0u;
+  }
+  uint32_t so[LB];
+#pragma unroll
+  for (int i = 0; i < LB; ++i) so[i] = swz(1u << (h.y >> (8 * i) & 0xffu));
+  float2 x[1 << LB];
+#pragma unroll
+  for (int l = 0; l < (1 << LB); ++l) {
+    uint32_t at = pt;
+#pragma unroll
+    for (int i = 0; i < LB; ++i)
+      if (l >> i & 1) at ^= so[i];
+    x[l] = tile[at];
+  }
+  for (int s = 0; s < n; ++s) {
+    const uint4 w = ops[2 * s];
+    const int slot = (int)w.w;
+    const float2* G = Gs + 16 * slot;
+    const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)forms[slot]);
+    const uint32_t code = (w.x & 0xffu) == (uint32_t)kSvOpGate1 ? (w.y & 0xffu) : 4u + (w.y & 0xffu);
+    switch (code) {
+      case 0: reg_gate1<LB, 0>(x, G, form); break;
+      case 1: reg_gate1<LB, 1>(x, G, form); break;
+      case 2: if constexpr (LB > 2) reg_gate1<LB, 2>(x, G, form); break;
+      case 3: if constexpr (LB > 3) reg_gate1<LB, 3>(x, G, form); break;
+      case 4 + svg_pair(0, 1): reg_gate2<LB, 0, 1>(x, G, form); break;
+      case 4 + svg_pair(0, 2): if constexpr (LB > 2) reg_gate2<LB, 0, 2>(x, G, form); break;
+      case 4 + svg_pair(0, 3): if constexpr (LB > 3) reg_gate2<LB, 0, 3>(x, G, form); break;
+      case 4 + svg_pair(1, 2): if constexpr (LB > 2) reg_gate2<LB, 1, 2>(x, G, form); break;
+      case 4 + svg_pair(1, 3): if constexpr (LB > 3) reg_gate2<LB, 1, 3>(x, G, form); break;
+      default: if constexpr (LB > 3) reg_gate2<LB, 2, 3>(x, G, form); break;
     }
+  }
+  asm volatile("" : "+v"(pt));     // the addresses are worked out again, not kept in registers
+#pragma unroll
+  for (int l = 0; l < (1 << LB); ++l) {
+    uint32_t at = pt;
+#pragma unroll
+    for (int i = 0; i < LB; ++i)
+      if (l >> i & 1) at ^= so[i];
+    tile[at] = x[l];
   }
   __syncthreads();
 }
 
-// A two-qubit gate in place on tile positions p0 (local bit 0) and p1 (local bit 1).
-template <int NP>
-__device__ inline void apply_gate2(const float2* __restrict__ Gm, int p0, int p1, float2* tile) {
-  constexpr uint32_t nt = 1u << NP;
-  float2 g[4][4];
-#pragma unroll
-  for (int n = 0; n < 4; ++n)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) g[n][k] = Gm[n * 4 + k];
-  const int pa = p0 < p1 ? p0 : p1, pb = p0 < p1 ? p1 : p0;   // zero bits inserted low one first
-  // quad lb + {0, 2^p0, 2^p1, both}, lb = ins0(ins0(tid + 256 i, pa), pb), swizzled
-  const uint32_t pt = swz(ins0(ins0(threadIdx.x, pa), pb));
-  const uint32_t s1 = swz(1u << p0), s2 = swz(1u << p1), s3 = s1 ^ s2;
-  int col[4];
-  bool mono = true;
-#pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    col[n] = -1;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (!czero(g[n][k])) {
-        mono = mono && col[n] < 0;
-        col[n] = k;
-      }
+// The window's gates (records [0, n_ops), groups and clusters among them) into Gs, 16
+// entries a slot, and their forms; ends with a barrier.
+__device__ __forceinline__ void stage_gates(const SvOp* __restrict__ ops, int n_ops, const float2* __restrict__ merged,
+                                   float2* Gs, uint32_t* forms) {
+  for (int i = threadIdx.x; i < 16 * n_ops; i += kSvwThreads) {
+    const SvOp& op = ops[i >> 4];
+    const int el = i & 15, d2 = op.kind == kSvOpGate1 ? 4 : 16;
+    if ((op.kind != kSvOpGate1 && op.kind != kSvOpGate2) || el >= d2) continue;
+    float2 g = merged[(int64_t)op.gate * 16 + op.idx[el]];
+    if (op.conj) g.y = -g.y;
+    Gs[16 * op.slot + el] = g;
   }
-  if (mono) {
-    // at most one nonzero per row (diagonal gates with diagonal Kraus factors,
-    // CNOT, Pauli products): one product per amplitude
-    float2 gd[4];
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-      const int c = col[n];
-      gd[n] = c == 0 ? g[n][0] : c == 1 ? g[n][1] : c == 2 ? g[n][2] : c == 3 ? g[n][3] : make_float2(0.f, 0.f);
-    }
-#pragma unroll 2
-    for (uint32_t i = 0; i < (nt >> 2) / kSvwThreads; ++i) {
-      const uint32_t lb = pt ^ swz(ins0(ins0(kSvwThreads * i, pa), pb));
-      const uint32_t off[4] = {lb, lb ^ s1, lb ^ s2, lb ^ s3};
-      const float2 a0 = tile[off[0]], a1 = tile[off[1]], a2 = tile[off[2]], a3 = tile[off[3]];
-#pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        const int c = col[n];
-        const float2 x = c == 0 ? a0 : c == 1 ? a1 : c == 2 ? a2 : a3;
-        tile[off[n]] = cmul(gd[n], x);
-      }
-    }
-  } else {
-#pragma unroll 2
-    for (uint32_t i = 0; i < (nt >> 2) / kSvwThreads; ++i) {
-      const uint32_t lb = pt ^ swz(ins0(ins0(kSvwThreads * i, pa), pb));
-      const uint32_t off[4] = {lb, lb ^ s1, lb ^ s2, lb ^ s3};
-      const float2 a0 = tile[off[0]], a1 = tile[off[1]], a2 = tile[off[2]], a3 = tile[off[3]];
-#pragma unroll
-      for (int n = 0; n < 4; ++n)
-        tile[off[n]] = cfma(g[n][3], a3, cfma(g[n][2], a2, cfma(g[n][1], a1, cmul(g[n][0], a0))));
-    }
+  __syncthreads();
+  for (int i = threadIdx.x; i < n_ops; i += kSvwThreads) {
+    const SvOp& op = ops[i];
+    if (op.kind == kSvOpGate1) forms[op.slot] = gate1_form(Gs + 16 * op.slot);
+    if (op.kind == kSvOpGate2) forms[op.slot] = gate2_form(Gs + 16 * op.slot);
   }
   __syncthreads();
 }
@@ -307,12 +405,19 @@ __device__ inline uint32_t pair_hi(const int* P, int i) {
   return off;
 }
 
+// Pair at lane offset lo of the uniform address A: 8 lo fits 32 bits (n <= 30, and lo's
+// highest bit P[8] has a window qubit above it), so that the pair's address is a scalar
+// base and one 32-bit register for all pairs of the thread.
+__device__ inline floatx4_t* pair_at(const float2* A, uint32_t lo) {
+  return reinterpret_cast<floatx4_t*>(reinterpret_cast<char*>(const_cast<float2*>(A)) + (size_t)(lo * 8u));
+}
+
 // The thread's pairs of one tile (A: the tile's first amplitude) into v.
 template <int NP>
 __device__ inline void load_pairs(const float2* __restrict__ A, const int* P, uint32_t lo,
                                   floatx4_t (&v)[1 << (NP - 9)]) {
 #pragma unroll
-  for (int i = 0; i < (1 << (NP - 9)); ++i) v[i] = *reinterpret_cast<const floatx4_t*>(A + (lo | pair_hi<NP>(P, i)));
+  for (int i = 0; i < (1 << (NP - 9)); ++i) v[i] = *pair_at(A + pair_hi<NP>(P, i), lo);
 }
 
 // As load_pairs, for a tile whose positions in `fresh` are still |0>: entries with any of
@@ -327,7 +432,7 @@ __device__ inline void load_fresh_pairs(const float2* __restrict__ A, const int*
     v[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
     if (((e + 2u * kSvwThreads * i) & fresh) == 0) {
       if (fresh & 1u) v[i][0] = 1.f;
-      else v[i] = *reinterpret_cast<const floatx4_t*>(A + (lo | pair_hi<NP>(P, i)));
+      else v[i] = *pair_at(A + pair_hi<NP>(P, i), lo);
     }
   }
 }
@@ -360,34 +465,31 @@ __device__ inline floatx4_t lds_get_pair(const floatx4_t* tile4, uint32_t pt2, i
   return (e & 1u) ? floatx4_t{v[2], v[3], v[0], v[1]} : v;
 }
 
-// One tile of a window of plain gates (no clusters): pairs loaded from Ain, the
-// ops applied in LDS (gate matrices staged in Gs), pairs stored to Aout (Ain and
-// Aout: the tile's first amplitude in the input and output states, which may be
-// the same; fresh as in load_fresh_pairs).  Op records are 32 bytes with kind, p0 and p1 in the low three bytes
-// of the first dword and the staged matrix slot in the fourth (SvOp, AdjOp).
-// Ends with a barrier.
-template <int NP, typename Op>
-__device__ inline void plain_tile_pass(const Op* __restrict__ ops, int n_ops, const int* P, const float2* Ain,
-                                       float2* Aout, float2* tile, const float2* Gs, uint32_t fresh = 0) {
-  static_assert(sizeof(Op) == 32, "op records are eight dwords");
+// One tile of a window of plain gates (no clusters): pairs loaded from A (the tile's
+// first amplitude; fresh as in load_fresh_pairs), the groups of gates applied, pairs
+// stored back.  Ends with a barrier.
+template <int NP>
+__device__ inline void plain_tile_pass(const SvOp* __restrict__ ops, int n_ops, const int* P, float2* A,
+                                       uint32_t fresh, float2* tile, const float2* Gs, const uint32_t* forms) {
   constexpr int PPT = 1 << (NP - 9);
   floatx4_t* tile4 = reinterpret_cast<floatx4_t*>(tile);
   const uint32_t lo = pair_lo(P), pt2 = swz(2u * threadIdx.x);
   floatx4_t v[PPT];
-  if (fresh) load_fresh_pairs<NP>(Ain, P, lo, fresh, v);
-  else load_pairs<NP>(Ain, P, lo, v);
+  if (fresh) load_fresh_pairs<NP>(A, P, lo, fresh, v);
+  else load_pairs<NP>(A, P, lo, v);
 #pragma unroll
   for (int i = 0; i < PPT; ++i) lds_put_pair(tile4, pt2, i, v[i]);
   __syncthreads();
-  for (int s = 0; s < n_ops; ++s) {
-    const uint4 w = reinterpret_cast<const uint4*>(ops)[2 * s];
-    const int kind = (int)(w.x & 0xffu), slot = (int)w.w;
-    if (kind == kSvOpGate1) apply_gate1<NP>(Gs + 16 * slot, (int)((w.x >> 8) & 0xffu), tile);
-    else apply_gate2<NP>(Gs + 16 * slot, (int)((w.x >> 8) & 0xffu), (int)((w.x >> 16) & 0xffu), tile);
+  const uint4* rec = reinterpret_cast<const uint4*>(ops);
+  for (int s = 0; s < n_ops;) {
+    const uint4 h = rec[2 * s];
+    const int n = (int)(h.x >> 8 & 0xffu);
+    apply_group<NP>(h, rec + 2 * (s + 1), n, tile, Gs, forms);
+    s += 1 + n;
   }
 #pragma unroll
   for (int i = 0; i < PPT; ++i)
-    *reinterpret_cast<floatx4_t*>(Aout + (lo | pair_hi<NP>(P, i))) = lds_get_pair(tile4, pt2, i);
+    *pair_at(A + pair_hi<NP>(P, i), lo) = lds_get_pair(tile4, pt2, i);
   __syncthreads();
 }
 

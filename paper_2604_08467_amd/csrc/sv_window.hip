@@ -15,8 +15,8 @@
 // The ops of a window are read through the scalar cache (uniform loads), the gate
 // matrices of a trajectory and its gate-cluster matrices are staged in LDS when
 // a workgroup reaches a new trajectory, and tiles move as 16-byte pairs of
-// amplitudes (qubit 0 is tile bit 0).  With PIPE the next tile's loads are issued
-// before the current tile's ops, so that they are in flight during its LDS work.
+// amplitudes (qubit 0 is tile bit 0).  The next tile's loads are issued before
+// the current tile's ops, so that they are in flight during its LDS work.
 //
 // A gate cluster (a 16 x 16 complex matrix on four tile positions, the product
 // of several gates built once per trajectory) is a real 32 x 32 by 32 x 2^(np-4)
@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_util.h"
 #include "internal.h"
@@ -34,8 +35,8 @@
 namespace ptsbe {
 namespace {
 
-template <int PREC, int NP, bool PIPE>
-__global__ void __launch_bounds__(kSvwThreads) sv_window_kernel(SvwArgs a, const SvOp* __restrict__ ops,
+template <int PREC, int NP, bool FRESH>
+__global__ void __launch_bounds__(kSvwThreads, 4) sv_window_kernel(SvwArgs a, const SvOp* __restrict__ ops,
                                                                const float2* __restrict__ merged,
                                                                const float2* __restrict__ Ucl,
                                                                float2* __restrict__ psi) {
@@ -46,6 +47,7 @@ __global__ void __launch_bounds__(kSvwThreads) sv_window_kernel(SvwArgs a, const
   const int n = a.n;
   float2* Gs = tile + (1 << NP);                   // [n_plain][16]
   float2* Us = Gs + 16 * a.n_plain;                // [n_cl][256]
+  uint32_t* forms = reinterpret_cast<uint32_t*>(Us + 256 * a.n_cl);   // [n_plain]
   const int tid = threadIdx.x;
   const int tb = __popc(a.live);
   const int64_t total = a.n_jobs << tb;
@@ -60,7 +62,7 @@ __global__ void __launch_bounds__(kSvwThreads) sv_window_kernel(SvwArgs a, const
   floatx4_t v[PPT];
   auto load = [&](int64_t bid) {
     const float2* A = psi + ((bid >> tb) << n) + tile_base(bid);
-    if (a.fresh) load_fresh_pairs<NP>(A, a.P, lo, a.fresh, v);
+    if (FRESH) load_fresh_pairs<NP>(A, a.P, lo, a.fresh, v);
     else load_pairs<NP>(A, a.P, lo, v);
   };
   load(b0);
@@ -70,35 +72,25 @@ __global__ void __launch_bounds__(kSvwThreads) sv_window_kernel(SvwArgs a, const
     if (job != last_job) {
       // stage the trajectory's gate matrices and cluster matrices (the previous
       // tile's last barrier has passed: nobody reads Gs / Us any more)
-      const int traj = a.traj_base + (int)job;
-      for (int s = 0; s < a.n_ops; ++s) {
-        const int kind = ops[s].kind;
-        if (kind == kSvOpCluster) continue;
-        const int d2 = kind == kSvOpGate1 ? 4 : 16;
-        if (tid < d2) {
-          float2 g = merged[((int64_t)traj * a.G + ops[s].gate) * 16 + ops[s].idx[tid]];
-          if (ops[s].conj) g.y = -g.y;
-          Gs[16 * ops[s].slot + tid] = g;
-        }
-      }
       for (int i = tid; i < 256 * a.n_cl; i += kSvwThreads)
         Us[i] = Ucl[((int64_t)job * a.n_cl_total + a.cl_first) * 256 + i];
+      stage_gates(ops, a.n_ops, merged + (a.traj_base + job) * a.G * 16, Gs, forms);
       last_job = job;
     }
 #pragma unroll
     for (int i = 0; i < PPT; ++i) lds_put_pair(tile4, pt2, i, v[i]);
     __syncthreads();   // the tile (and any staging) is complete before the first op
-    if (PIPE && bid + 1 < b1) load(bid + 1);
-    for (int s = 0; s < a.n_ops; ++s) {
-      // the op's first four dwords as one uniform (scalar-cache) load: kind, p0, p1,
-      // conj | cluster positions | gate | slot
+    if (!FRESH && bid + 1 < b1) load(bid + 1);   // in flight during the ops
+    for (int s = 0; s < a.n_ops;) {
+      // the record's first four dwords as one uniform (scalar-cache) load
       const uint4 w = reinterpret_cast<const uint4*>(ops)[2 * s];
-      const int kind = (int)(w.x & 0xffu), slot = (int)w.w;
-      if (kind == kSvOpGate1) {
-        apply_gate1<NP>(Gs + 16 * slot, (int)((w.x >> 8) & 0xffu), tile);
-      } else if (kind == kSvOpGate2) {
-        apply_gate2<NP>(Gs + 16 * slot, (int)((w.x >> 8) & 0xffu), (int)((w.x >> 16) & 0xffu), tile);
+      if ((w.x & 0xffu) == (uint32_t)kSvOpGroup) {
+        const int ng = (int)(w.x >> 8 & 0xffu);
+        apply_group<NP>(w, reinterpret_cast<const uint4*>(ops) + 2 * (s + 1), ng, tile, Gs, forms);
+        s += 1 + ng;
       } else {
+        const int slot = (int)w.w;
+        ++s;
         const ClusterCols cc(w.y);
         if (PREC == PTSBE_C64)
           apply_cluster_f32(cc, Us + 256 * slot, NP, tile);
@@ -110,10 +102,10 @@ __global__ void __launch_bounds__(kSvwThreads) sv_window_kernel(SvwArgs a, const
       const uint32_t base = tile_base(bid);
       float2* A = psi + (job << n) + base;
 #pragma unroll
-      for (int i = 0; i < PPT; ++i) *reinterpret_cast<floatx4_t*>(A + (lo | pair_hi<NP>(a.P, i))) = lds_get_pair(tile4, pt2, i);
+      for (int i = 0; i < PPT; ++i) *pair_at(A + pair_hi<NP>(a.P, i), lo) = lds_get_pair(tile4, pt2, i);
     }
     __syncthreads();   // every thread has read its part of the tile before it is refilled
-    if (!PIPE && bid + 1 < b1) load(bid + 1);
+    if (FRESH && bid + 1 < b1) load(bid + 1);
   }
 }
 
@@ -121,8 +113,9 @@ __global__ void __launch_bounds__(kSvwThreads) sv_window_kernel(SvwArgs a, const
 
 size_t sv_window_lds_bytes(const SvWin& w) {
   if (w.np < 10 || w.np > kFuseMax || w.P[0] != 0) return 0;
-  return ((size_t)1 << w.np) * sizeof(float2) + (size_t)w.n_plain * 16 * sizeof(float2) +
-         (size_t)w.n_cl * 256 * sizeof(float2);
+  const size_t b = ((size_t)1 << w.np) * sizeof(float2) + (size_t)w.n_plain * 16 * sizeof(float2) +
+                   (size_t)w.n_cl * 256 * sizeof(float2);
+  return b > 64 * 1024 ? 0 : b + (size_t)w.n_plain * sizeof(uint32_t);
 }
 
 hipError_t launch_sv_window(const SvWin& w, const SvOp* d_ops, const float2* merged, int G, const float2* Ucl,
@@ -130,7 +123,7 @@ hipError_t launch_sv_window(const SvWin& w, const SvOp* d_ops, const float2* mer
                             bool grow, hipStream_t stream) {
   if (n_jobs <= 0 || (w.n_ops == 0 && !grow)) return hipSuccess;
   const size_t lds = sv_window_lds_bytes(w);
-  if (lds == 0 || lds > 64 * 1024) return hipErrorInvalidValue;
+  if (lds == 0) return hipErrorInvalidValue;
   SvwArgs a{};
   a.n = n;
   a.np = w.np;
@@ -162,14 +155,18 @@ hipError_t launch_sv_window(const SvWin& w, const SvOp* d_ops, const float2* mer
     return hipGetLastError();
   };
   auto by_np = [&](auto k10, auto k11, auto k12) { return w.np == 10 ? go(k10) : w.np == 11 ? go(k11) : go(k12); };
-  if (precision == PTSBE_SPLIT_BF16)
-    return by_np(sv_window_kernel<PTSBE_SPLIT_BF16, 10, true>, sv_window_kernel<PTSBE_SPLIT_BF16, 11, true>,
-                 sv_window_kernel<PTSBE_SPLIT_BF16, 12, true>);
-  if (precision == PTSBE_SPLIT_F16)
-    return by_np(sv_window_kernel<PTSBE_SPLIT_F16, 10, true>, sv_window_kernel<PTSBE_SPLIT_F16, 11, true>,
-                 sv_window_kernel<PTSBE_SPLIT_F16, 12, true>);
-  return by_np(sv_window_kernel<PTSBE_C64, 10, true>, sv_window_kernel<PTSBE_C64, 11, true>,
-               sv_window_kernel<PTSBE_C64, 12, true>);
+  auto by_prec = [&](auto fresh) -> hipError_t {
+    constexpr bool F = decltype(fresh)::value;
+    if (precision == PTSBE_SPLIT_BF16)
+      return by_np(sv_window_kernel<PTSBE_SPLIT_BF16, 10, F>, sv_window_kernel<PTSBE_SPLIT_BF16, 11, F>,
+                   sv_window_kernel<PTSBE_SPLIT_BF16, 12, F>);
+    if (precision == PTSBE_SPLIT_F16)
+      return by_np(sv_window_kernel<PTSBE_SPLIT_F16, 10, F>, sv_window_kernel<PTSBE_SPLIT_F16, 11, F>,
+                   sv_window_kernel<PTSBE_SPLIT_F16, 12, F>);
+    return by_np(sv_window_kernel<PTSBE_C64, 10, F>, sv_window_kernel<PTSBE_C64, 11, F>,
+                 sv_window_kernel<PTSBE_C64, 12, F>);
+  };
+  return a.fresh ? by_prec(std::true_type{}) : by_prec(std::false_type{});
 }
 
 }  // namespace ptsbe
