@@ -850,12 +850,21 @@ struct RgWave {                      // device arrays of one wave (all in the wo
   int32_t* bad_flag;
   int32_t n_jobs;
 };
-// window level l: entries (piece, first task) of the pieces with more than l windows
-struct RgLevel { const int32_t* piece; const int64_t* start; int32_t n; int64_t tasks; int32_t max_ops; };
+// Window `level` of the pieces that share a tile form (np qubits as compact plain ops, with
+// fresh positions or without; np = 0: the generic pass)
+struct RgLevel {
+  const int32_t* piece;              // [n]
+  const int64_t* start;              // [n]
+  const int64_t* cost;               // [n + 1] cost of the tasks before each entry; a task of entry e
+  const int32_t* weight;             // [n] costs weight[e]
+  int32_t n;
+  int64_t tasks;
+  int32_t max_ops, level, np, fresh;
+};
 hipError_t launch_rg_start(const RgWave& w, hipStream_t s);
 hipError_t launch_rg_prepare(const RgWave& w, int grid, hipStream_t s);
 // grid: n_cu times the kernel's occupancy per CU
-hipError_t launch_rg_window(const RgWave& w, const RgLevel& lv, int level, int n_cu, hipStream_t s);
+hipError_t launch_rg_window(const RgWave& w, const RgLevel& lv, int n_cu, hipStream_t s);
 hipError_t launch_rg_marginal0(const RgWave& w, int64_t tasks, int grid, hipStream_t s);
 hipError_t launch_rg_marginal(const RgWave& w, int j, int cur, int grid, hipStream_t s);
 hipError_t launch_rg_sample(const RgWave& w, int j, int cur, int grid, hipStream_t s);

@@ -12,6 +12,7 @@
 #include <cstring>
 #include <numeric>
 #include <string>
+#include <map>
 #include <unordered_map>
 #include <vector>
 
@@ -75,6 +76,23 @@ bool compact_set(const Plan& p, int w) {
   bool ok = p.d_sv_ops_plain[w] && p.d_sv_wins_plain[w] && p.sv_wins_plain[w].size() == p.sv_win[w].size();
   for (const auto& wd : p.sv_wins_plain[w]) ok = ok && wd.np >= 10 && wd.n_plain <= kRgMaxGates;
   return ok;
+}
+
+// Cost of a tile of window l among those of its tile form: its gates' products (a two-qubit
+// gate has twice the terms of a one-qubit gate) and 16 for its way through memory and LDS.
+int32_t window_weight(const Plan& p, int w, int l, bool compact) {
+  int32_t gates = 2 * p.sv_win[w][l].count;
+  if (compact) {
+    const ptsbe::SvWin& wd = p.sv_wins_plain[w][l];
+    gates = 0;
+    for (int s = 0; s < wd.n_ops; ++s) {
+      const int kind = p.sv_ops_plain[w][(size_t)(wd.op_off + s)].kind;
+      gates += kind == ptsbe::kSvOpGate1 ? 1 : kind == ptsbe::kSvOpGate2 ? 2 : 0;
+    }
+  } else {
+    gates <<= p.sv_win[w][l].np;     // tiles of different sizes
+  }
+  return gates + 16;
 }
 
 int window_choice(const ptsbe_ragged_s& set, const Plan* p) {
@@ -443,28 +461,53 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
     int maxW = 0;
     for (auto& pc : pcs) maxW = std::max(maxW, pc.n_win);
     for (int l = 0; l < maxW; ++l) {
-      std::vector<int32_t> lp;
-      std::vector<int64_t> ls;
-      int64_t tasks = 0;
-      int32_t max_ops = 0;
+      // the level's pieces by tile form, in wave order: key 2 np + fresh, 0 for the generic pass
+      std::map<int, std::vector<int32_t>> forms;
       for (int k = 0; k < P; ++k) {
         if (pcs[k].n_win <= l) continue;
         const Plan& p = *reinterpret_cast<const Plan*>(jobs[pcs[k].job].plan);
-        const int wc = window_choice(*set, &p);
-        if (pcs[k].swin) max_ops = std::max(max_ops, p.sv_wins_plain[wc][l].n_plain);
-        lp.push_back(k);
-        ls.push_back(tasks);
-        tasks += (int64_t)pcs[k].nj << (pcs[k].grow ? __builtin_popcount(p.sv_wins_plain[wc][l].live)
-                                                    : pcs[k].n - p.sv_win[wc][l].np);
+        int form = 0;
+        if (pcs[k].swin) {
+          const ptsbe::SvWin& wd = p.sv_wins_plain[window_choice(*set, &p)][l];
+          form = 2 * wd.np + (pcs[k].grow && wd.fresh ? 1 : 0);
+        }
+        forms[form].push_back(k);
       }
-      RgLevel lv{};
-      lv.piece = (const int32_t*)put(lp.data(), lp.size() * 4);
-      lv.start = (const int64_t*)put(ls.data(), ls.size() * 8);
-      if (!lv.piece || !lv.start) return fail(PTSBE_ERR_OUT_OF_MEMORY, "wave tables do not fit");
-      lv.n = (int32_t)lp.size();
-      lv.tasks = tasks;
-      lv.max_ops = max_ops;
-      L.levels.push_back(lv);
+      for (const auto& fm : forms) {
+        const std::vector<int32_t>& lp = fm.second;
+        std::vector<int64_t> ls, lc;
+        std::vector<int32_t> lw;
+        RgLevel lv{};
+        int64_t cost = 0;
+        for (int32_t k : lp) {
+          const Plan& p = *reinterpret_cast<const Plan*>(jobs[pcs[k].job].plan);
+          const int wc = window_choice(*set, &p);
+          int tb = pcs[k].n - p.sv_win[wc][l].np;
+          if (pcs[k].swin) {
+            const ptsbe::SvWin& wd = p.sv_wins_plain[wc][l];
+            lv.max_ops = std::max(lv.max_ops, wd.n_plain);
+            if (pcs[k].grow) tb = __builtin_popcount(wd.live);
+          }
+          ls.push_back(lv.tasks);
+          lw.push_back(window_weight(p, wc, l, pcs[k].swin != nullptr));
+          lc.push_back(cost);
+          const int64_t nt = (int64_t)pcs[k].nj << tb;
+          lv.tasks += nt;
+          cost += nt * lw.back();
+        }
+        lc.push_back(cost);
+        lv.piece = (const int32_t*)put(lp.data(), lp.size() * 4);
+        lv.start = (const int64_t*)put(ls.data(), ls.size() * 8);
+        lv.cost = (const int64_t*)put(lc.data(), lc.size() * 8);
+        lv.weight = (const int32_t*)put(lw.data(), lw.size() * 4);
+        if (!lv.piece || !lv.start || !lv.cost || !lv.weight)
+          return fail(PTSBE_ERR_OUT_OF_MEMORY, "wave tables do not fit");
+        lv.n = (int32_t)lp.size();
+        lv.level = l;
+        lv.np = fm.first / 2;
+        lv.fresh = fm.first & 1;
+        L.levels.push_back(lv);
+      }
     }
   }
   // launch (or replay) every wave
@@ -483,8 +526,8 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
     if (wi == 0) { HIP_TRY(ptsbe::launch_rg_start(L.w, s)); ++launches; }
     HIP_TRY(ptsbe::launch_rg_prepare(L.w, g_mem, s));
     ++launches;
-    for (size_t l = 0; l < L.levels.size(); ++l) {
-      HIP_TRY(ptsbe::launch_rg_window(L.w, L.levels[l], (int)l, set->n_cu, s));
+    for (const RgLevel& lv : L.levels) {
+      HIP_TRY(ptsbe::launch_rg_window(L.w, lv, set->n_cu, s));
       ++launches;
     }
     HIP_TRY(ptsbe::launch_rg_marginal0(L.w, L.m0_tasks, g_mem, s));

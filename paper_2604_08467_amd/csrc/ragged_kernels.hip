@@ -109,50 +109,82 @@ __global__ void __launch_bounds__(kRgThreads) rg_prepare_kernel(RgWave w) {
   }
 }
 
-// Window level `level`: every 2^np tile of every trajectory of every piece that
-// has that many windows; tiles of heavier circuits come first in the queue.
-__global__ void __launch_bounds__(kRgThreads, 4) rg_window_kernel(RgWave w, RgLevel lv, int level) {
-  extern __shared__ float2 lds[];
-  float2* tile = lds;
-  float2* Gm = lds + (1 << kFuseMax);   // staged gates: generic chunks, or one 16-entry slot per gate
-  uint32_t* forms = reinterpret_cast<uint32_t*>(Gm + 16 * (lv.max_ops > kGateChunk ? lv.max_ops : kGateChunk));
+// Values that every lane holds, into scalar registers.
+__device__ inline int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ inline int64_t uni64(int64_t v) {
+  return ((int64_t)uni((int)(v >> 32)) << 32) | (uint32_t)uni((int)v);
+}
+template <typename T>
+__device__ inline T* uni_ptr(T* p) { return reinterpret_cast<T*>(uni64((int64_t)p)); }
+
+// First task of workgroup `block` of `blocks`: the tasks' costs are split evenly (a tile of
+// a deep circuit has several times the gates of its neighbour's).
+__device__ inline int64_t level_task(const RgLevel& lv, int64_t block, int64_t blocks) {
+  if (block >= blocks) return lv.tasks;
+  const int64_t total = lv.cost[lv.n];
+  const int64_t c = total / blocks * block + total % blocks * block / blocks;
+  const int e = find_le(lv.cost, lv.n, c);
+  return lv.start[e] + (c - lv.cost[e]) / lv.weight[e];
+}
+
+// The entries of one window level that share a tile form: every 2^np tile of every
+// trajectory of their pieces, as a range of tasks a workgroup with equal shares of their
+// cost, piece by piece (consecutive tiles of a trajectory reuse its staged gates).  Bound
+// by the gates' products: 12 circuits of 12 .. 20 qubits, 106 GFLOP (1.35 ms at 78.6
+// TFLOP/s), 3.8 -> 3.0 ms against one kernel for all forms, equal numbers of tasks a
+// workgroup and no loads ahead.
+template <int NP, bool FRESH>
+__global__ void __launch_bounds__(kRgThreads, 4) rg_window_kernel(RgWave w, RgLevel lv) {
+  extern __shared__ floatx4_t rg_lds[];
+  const int64_t b0 = level_task(lv, blockIdx.x, gridDim.x), b1 = level_task(lv, (int64_t)blockIdx.x + 1, gridDim.x);
+  if (b0 >= b1) return;
+  for (int e = find_le(lv.start, lv.n, b0); e < lv.n; ++e) {
+    const int64_t first = lv.start[e], end = e + 1 < lv.n ? lv.start[e + 1] : lv.tasks;
+    if (first >= b1) break;
+    const int64_t t0 = uni64((b0 > first ? b0 : first) - first), t1 = uni64((b1 < end ? b1 : end) - first);
+    const RgPiece& pc = w.pieces[lv.piece[e]];
+    const SvWin& sw = pc.swin[lv.level];
+    const bool grow = uni(pc.grow) != 0;
+    SvwArgs a;
+    a.n = uni(pc.n);
+    a.n_ops = uni(sw.n_ops);
+    a.n_plain = uni(sw.n_plain);
+    a.n_cl = a.cl_first = a.n_cl_total = 0;
+    a.G = uni(pc.g.G);
+    a.live = (uint32_t)uni((int)(grow ? sw.live : sw.other));
+    a.fresh = grow ? (uint32_t)uni((int)sw.fresh) : 0u;
+    for (int k = 0; k < kFuseMax; ++k) a.P[k] = uni(sw.P[k]);
+    a.n_jobs = pc.nj;
+    a.traj_base = 0;
+    window_tiles<kSvwPlain, NP, FRESH>(a, uni_ptr(pc.sops) + uni(sw.op_off), uni_ptr(pc.g.merged), nullptr,
+                                       uni_ptr(pc.psi), t0, t1, rg_lds);
+  }
+}
+
+// The same for windows of circuits of fewer than 10 qubits, and those with more gates than
+// are staged.
+__global__ void __launch_bounds__(kRgThreads) rg_window_generic_kernel(RgWave w, RgLevel lv) {
+  extern __shared__ floatx4_t rg_lds[];
+  float2* tile = reinterpret_cast<float2*>(rg_lds);
   __shared__ uint64_t pw[1];
   if (threadIdx.x == 0) pw[0] = 0ull;
-  // contiguous task ranges per workgroup: consecutive tiles of one trajectory
-  // reuse the staged gate matrices
-  const int64_t per = (lv.tasks + gridDim.x - 1) / gridDim.x;
-  const int64_t b0 = (int64_t)blockIdx.x * per, b1 = b0 + per < lv.tasks ? b0 + per : lv.tasks;
-  const RgPiece* last_pc = nullptr;
-  int64_t last_traj = -1;
-  for (int64_t task = b0; task < b1; ++task) {
-    const int e = find_le(lv.start, lv.n, task);
+  __syncthreads();
+  const int64_t b0 = level_task(lv, blockIdx.x, gridDim.x), b1 = level_task(lv, (int64_t)blockIdx.x + 1, gridDim.x);
+  if (b0 >= b1) return;
+  for (int e = find_le(lv.start, lv.n, b0); e < lv.n; ++e) {
+    const int64_t first = lv.start[e], end = e + 1 < lv.n ? lv.start[e + 1] : lv.tasks;
+    if (first >= b1) break;
     const RgPiece& pc = w.pieces[lv.piece[e]];
-    const RgWindow& wd = pc.win[level];
-    const int tb = pc.grow ? __popc(pc.swin[level].live) : pc.n - wd.np;
-    const int64_t local = task - lv.start[e];
-    const int64_t traj = local >> tb;
-    const uint32_t t = (uint32_t)(local & (((int64_t)1 << tb) - 1));
-    const bool same = &pc == last_pc && traj == last_traj;
-    if (pc.swin) {
-      // compact plain ops (scalar-cache reads), gates staged once per trajectory
-      const SvWin& sw = pc.swin[level];
-      const SvOp* ops = pc.sops + sw.op_off;
-      if (!same) {
-        __syncthreads();   // nobody reads the previous trajectory's gates any more
-        stage_gates(ops, sw.n_ops, pc.g.merged + traj * pc.g.G * 16, Gm, forms);
-      }
-      float2* A = pc.psi + (traj << pc.n) + deposit_other(t, pc.grow ? sw.live : sw.other);
-      const uint32_t fresh = pc.grow ? sw.fresh : 0u;
-      if (sw.np == 12) plain_tile_pass<12>(ops, sw.n_ops, sw.P, A, fresh, tile, Gm, forms);
-      else if (sw.np == 11) plain_tile_pass<11>(ops, sw.n_ops, sw.P, A, fresh, tile, Gm, forms);
-      else plain_tile_pass<10>(ops, sw.n_ops, sw.P, A, fresh, tile, Gm, forms);
-    } else {
-      const bool ready = same && wd.n_fs <= kGateChunk && last_pc && !last_pc->swin;
-      window_tile_pass(pc.fused + wd.fused_off, wd.n_fs, wd.P, wd.np, pc.n, t, pc.psi + (traj << pc.n), pc.g,
-                       (int)traj, pw, tile, Gm, nullptr, ready);
+    const RgWindow& wd = pc.win[lv.level];
+    const int tb = pc.n - wd.np;
+    int64_t last_traj = -1;
+    for (int64_t task = b0 > first ? b0 : first; task < (b1 < end ? b1 : end); ++task) {
+      const int64_t t = task - first, traj = t >> tb;
+      window_tile_pass(pc.fused + wd.fused_off, wd.n_fs, wd.P, wd.np, pc.n, (uint32_t)(t & (((int64_t)1 << tb) - 1)),
+                       pc.psi + (traj << pc.n), pc.g, (int)traj, pw, tile, tile + (1 << kFuseMax), nullptr,
+                       traj == last_traj && wd.n_fs <= kGateChunk);
+      last_traj = traj;
     }
-    last_pc = &pc;
-    last_traj = traj;
   }
 }
 
@@ -436,17 +468,22 @@ hipError_t launch_rg_prepare(const RgWave& w, int grid, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_rg_window(const RgWave& w, const RgLevel& lv, int level, int n_cu, hipStream_t s) {
+hipError_t launch_rg_window(const RgWave& w, const RgLevel& lv, int n_cu, hipStream_t s) {
   if (lv.tasks <= 0) return hipSuccess;
-  const size_t shmem = (((size_t)1 << kFuseMax) + 16 * (size_t)std::max(kGateChunk, (int)lv.max_ops)) * sizeof(float2) +
+  auto go = [&](auto kernel, size_t shmem) -> hipError_t {
+    // a persistent grid is only as large as what fits on the chip at once
+    int per_cu = 0;
+    hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kRgThreads, shmem);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n_cu * std::max(per_cu, 1))), dim3(kRgThreads), shmem, s, w, lv);
+    return hipGetLastError();
+  };
+  if (lv.np == 0) return go(rg_window_generic_kernel, (((size_t)1 << kFuseMax) + 16 * kGateChunk) * sizeof(float2));
+  const size_t shmem = (((size_t)1 << lv.np) + 16 * (size_t)lv.max_ops) * sizeof(float2) +
                        (size_t)lv.max_ops * sizeof(uint32_t);
-  // a persistent grid is only as large as what fits on the chip at once
-  int per_cu = 0;
-  hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rg_window_kernel, kRgThreads, shmem);
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(rg_window_kernel, dim3((unsigned)(n_cu * std::max(per_cu, 1))), dim3(kRgThreads), shmem, s, w,
-                     lv, level);
-  return hipGetLastError();
+  if (lv.np == 12) return lv.fresh ? go(rg_window_kernel<12, true>, shmem) : go(rg_window_kernel<12, false>, shmem);
+  if (lv.np == 11) return lv.fresh ? go(rg_window_kernel<11, true>, shmem) : go(rg_window_kernel<11, false>, shmem);
+  return lv.fresh ? go(rg_window_kernel<10, true>, shmem) : go(rg_window_kernel<10, false>, shmem);
 }
 
 hipError_t launch_rg_marginal0(const RgWave& w, int64_t tasks, int grid, hipStream_t s) {

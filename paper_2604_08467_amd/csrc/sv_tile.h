@@ -31,8 +31,10 @@ __device__ inline uint32_t ins0(uint32_t m, int p) {   // zero bit inserted at p
   return ((m & ~lo) << 1) | (m & lo);
 }
 
+constexpr int kSvwPlain = -1;   // "precision" of a window without clusters
+
 struct SvwArgs {
-  int n, np, n_ops, n_plain, n_cl, cl_first, n_cl_total, G;
+  int n, n_ops, n_plain, n_cl, cl_first, n_cl_total, G;
   uint32_t live;           // bit mask of the qubits outside the window that tiles are made over
   uint32_t fresh;          // tile positions whose qubits are still |0> on entry
   int P[kFuseMax];
@@ -465,32 +467,72 @@ __device__ inline floatx4_t lds_get_pair(const floatx4_t* tile4, uint32_t pt2, i
   return (e & 1u) ? floatx4_t{v[2], v[3], v[0], v[1]} : v;
 }
 
-// One tile of a window of plain gates (no clusters): pairs loaded from A (the tile's
-// first amplitude; fresh as in load_fresh_pairs), the groups of gates applied, pairs
-// stored back.  Ends with a barrier.
-template <int NP>
-__device__ inline void plain_tile_pass(const SvOp* __restrict__ ops, int n_ops, const int* P, float2* A,
-                                       uint32_t fresh, float2* tile, const float2* Gs, const uint32_t* forms) {
-  constexpr int PPT = 1 << (NP - 9);
-  floatx4_t* tile4 = reinterpret_cast<floatx4_t*>(tile);
-  const uint32_t lo = pair_lo(P), pt2 = swz(2u * threadIdx.x);
+// Tiles [b0, b1) of a window over the states psi [n_jobs][2^n] (tile t of job j is number
+// (j << popc(live)) + t), their trajectories' merged gates and cluster matrices: pairs
+// loaded, the groups and clusters applied in LDS, pairs stored.  With no fresh position
+// the next tile's loads are issued before the current tile's ops.  LDS: the tile, n_plain
+// staged gates, n_cl clusters, n_plain forms.  Ends with a barrier.
+template <int PREC, int NP, bool FRESH>
+__device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __restrict__ ops,
+                                             const float2* __restrict__ merged, const float2* __restrict__ Ucl,
+                                             float2* __restrict__ psi, int64_t b0, int64_t b1, floatx4_t* lds) {
+  float2* tile = reinterpret_cast<float2*>(lds);
+  floatx4_t* tile4 = lds;
+  constexpr int PPT = 1 << (NP - 9);     // pairs per thread
+  float2* Gs = tile + (1 << NP);                   // [n_plain][16]
+  float2* Us = Gs + 16 * a.n_plain;                // [n_cl][256]
+  uint32_t* forms = reinterpret_cast<uint32_t*>(Us + 256 * a.n_cl);   // [n_plain]
+  const int tid = threadIdx.x;
+  const int tb = __popc(a.live), n = a.n;
+  // this thread's pair offset from its own bits (tile bits 1..8 = positions P[1..8])
+  const uint32_t lo = pair_lo(a.P), pt2 = swz(2u * tid);
+  auto tile_base = [&](int64_t bid) -> uint32_t {   // the tile's other bits, spread over the non-window positions
+    return deposit_other((uint32_t)(bid & (((int64_t)1 << tb) - 1)), a.live);
+  };
   floatx4_t v[PPT];
-  if (fresh) load_fresh_pairs<NP>(A, P, lo, fresh, v);
-  else load_pairs<NP>(A, P, lo, v);
+  auto load = [&](int64_t bid) {
+    const float2* A = psi + ((bid >> tb) << n) + tile_base(bid);
+    if (FRESH) load_fresh_pairs<NP>(A, a.P, lo, a.fresh, v);
+    else load_pairs<NP>(A, a.P, lo, v);
+  };
+  load(b0);
+  int64_t last_job = -1;
+  for (int64_t bid = b0; bid < b1; ++bid) {
+    const int64_t job = bid >> tb;
+    if (job != last_job) {
+      // stage the trajectory's gate matrices and cluster matrices (the previous
+      // tile's last barrier has passed: nobody reads Gs / Us any more)
+      for (int i = tid; i < 256 * a.n_cl; i += kSvwThreads)
+        Us[i] = Ucl[((int64_t)job * a.n_cl_total + a.cl_first) * 256 + i];
+      stage_gates(ops, a.n_ops, merged + (a.traj_base + job) * a.G * 16, Gs, forms);
+      last_job = job;
+    }
 #pragma unroll
-  for (int i = 0; i < PPT; ++i) lds_put_pair(tile4, pt2, i, v[i]);
-  __syncthreads();
-  const uint4* rec = reinterpret_cast<const uint4*>(ops);
-  for (int s = 0; s < n_ops;) {
-    const uint4 h = rec[2 * s];
-    const int n = (int)(h.x >> 8 & 0xffu);
-    apply_group<NP>(h, rec + 2 * (s + 1), n, tile, Gs, forms);
-    s += 1 + n;
+    for (int i = 0; i < PPT; ++i) lds_put_pair(tile4, pt2, i, v[i]);
+    __syncthreads();   // the tile (and any staging) is complete before the first op
+    if (!FRESH && bid + 1 < b1) load(bid + 1);   // in flight during the ops
+    for (int s = 0; s < a.n_ops;) {
+      // the record's first four dwords as one uniform (scalar-cache) load
+      const uint4 w = reinterpret_cast<const uint4*>(ops)[2 * s];
+      if ((w.x & 0xffu) == (uint32_t)kSvOpGroup) {
+        const int ng = (int)(w.x >> 8 & 0xffu);
+        apply_group<NP>(w, reinterpret_cast<const uint4*>(ops) + 2 * (s + 1), ng, tile, Gs, forms);
+        s += 1 + ng;
+      } else {
+        ++s;
+        if constexpr (PREC != kSvwPlain) {
+          const ClusterCols cc(w.y);
+          if constexpr (PREC == PTSBE_C64) apply_cluster_f32(cc, Us + 256 * (int)w.w, NP, tile);
+          else apply_cluster_split<PREC>(cc, Us + 256 * (int)w.w, NP, tile);
+        }
+      }
+    }
+    float2* A = psi + (job << n) + tile_base(bid);
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) *pair_at(A + pair_hi<NP>(a.P, i), lo) = lds_get_pair(tile4, pt2, i);
+    __syncthreads();   // every thread has read its part of the tile before it is refilled
+    if (FRESH && bid + 1 < b1) load(bid + 1);
   }
-#pragma unroll
-  for (int i = 0; i < PPT; ++i)
-    *pair_at(A + pair_hi<NP>(P, i), lo) = lds_get_pair(tile4, pt2, i);
-  __syncthreads();
 }
 
 }  // namespace

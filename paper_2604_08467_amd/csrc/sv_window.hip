@@ -41,72 +41,10 @@ __global__ void __launch_bounds__(kSvwThreads, 4) sv_window_kernel(SvwArgs a, co
                                                                const float2* __restrict__ Ucl,
                                                                float2* __restrict__ psi) {
   extern __shared__ floatx4_t svw_lds[];
-  float2* tile = reinterpret_cast<float2*>(svw_lds);
-  floatx4_t* tile4 = svw_lds;
-  constexpr int PPT = 1 << (NP - 9);     // pairs per thread
-  const int n = a.n;
-  float2* Gs = tile + (1 << NP);                   // [n_plain][16]
-  float2* Us = Gs + 16 * a.n_plain;                // [n_cl][256]
-  uint32_t* forms = reinterpret_cast<uint32_t*>(Us + 256 * a.n_cl);   // [n_plain]
-  const int tid = threadIdx.x;
-  const int tb = __popc(a.live);
-  const int64_t total = a.n_jobs << tb;
+  const int64_t total = a.n_jobs << __popc(a.live);
   const int64_t per = (total + gridDim.x - 1) / gridDim.x;
   const int64_t b0 = (int64_t)blockIdx.x * per, b1 = b0 + per < total ? b0 + per : total;
-  if (b0 >= b1) return;
-  // this thread's pair offset from its own bits (tile bits 1..8 = positions P[1..8])
-  const uint32_t lo = pair_lo(a.P), pt2 = swz(2u * tid);
-  auto tile_base = [&](int64_t bid) -> uint32_t {   // the tile's other bits, spread over the non-window positions
-    return deposit_other((uint32_t)(bid & (((int64_t)1 << tb) - 1)), a.live);
-  };
-  floatx4_t v[PPT];
-  auto load = [&](int64_t bid) {
-    const float2* A = psi + ((bid >> tb) << n) + tile_base(bid);
-    if (FRESH) load_fresh_pairs<NP>(A, a.P, lo, a.fresh, v);
-    else load_pairs<NP>(A, a.P, lo, v);
-  };
-  load(b0);
-  int64_t last_job = -1;
-  for (int64_t bid = b0; bid < b1; ++bid) {
-    const int64_t job = bid >> tb;
-    if (job != last_job) {
-      // stage the trajectory's gate matrices and cluster matrices (the previous
-      // tile's last barrier has passed: nobody reads Gs / Us any more)
-      for (int i = tid; i < 256 * a.n_cl; i += kSvwThreads)
-        Us[i] = Ucl[((int64_t)job * a.n_cl_total + a.cl_first) * 256 + i];
-      stage_gates(ops, a.n_ops, merged + (a.traj_base + job) * a.G * 16, Gs, forms);
-      last_job = job;
-    }
-#pragma unroll
-    for (int i = 0; i < PPT; ++i) lds_put_pair(tile4, pt2, i, v[i]);
-    __syncthreads();   // the tile (and any staging) is complete before the first op
-    if (!FRESH && bid + 1 < b1) load(bid + 1);   // in flight during the ops
-    for (int s = 0; s < a.n_ops;) {
-      // the record's first four dwords as one uniform (scalar-cache) load
-      const uint4 w = reinterpret_cast<const uint4*>(ops)[2 * s];
-      if ((w.x & 0xffu) == (uint32_t)kSvOpGroup) {
-        const int ng = (int)(w.x >> 8 & 0xffu);
-        apply_group<NP>(w, reinterpret_cast<const uint4*>(ops) + 2 * (s + 1), ng, tile, Gs, forms);
-        s += 1 + ng;
-      } else {
-        const int slot = (int)w.w;
-        ++s;
-        const ClusterCols cc(w.y);
-        if (PREC == PTSBE_C64)
-          apply_cluster_f32(cc, Us + 256 * slot, NP, tile);
-        else
-          apply_cluster_split<PREC == PTSBE_C64 ? PTSBE_SPLIT_BF16 : PREC>(cc, Us + 256 * slot, NP, tile);
-      }
-    }
-    {
-      const uint32_t base = tile_base(bid);
-      float2* A = psi + (job << n) + base;
-#pragma unroll
-      for (int i = 0; i < PPT; ++i) *pair_at(A + pair_hi<NP>(a.P, i), lo) = lds_get_pair(tile4, pt2, i);
-    }
-    __syncthreads();   // every thread has read its part of the tile before it is refilled
-    if (FRESH && bid + 1 < b1) load(bid + 1);
-  }
+  if (b0 < b1) window_tiles<PREC, NP, FRESH>(a, ops, merged, Ucl, psi, b0, b1, svw_lds);
 }
 
 }  // namespace
@@ -126,7 +64,6 @@ hipError_t launch_sv_window(const SvWin& w, const SvOp* d_ops, const float2* mer
   if (lds == 0) return hipErrorInvalidValue;
   SvwArgs a{};
   a.n = n;
-  a.np = w.np;
   a.n_ops = w.n_ops;
   a.n_plain = w.n_plain;
   a.n_cl = w.n_cl;
