@@ -830,6 +830,7 @@ struct RgPiece {                     // trajectories [t0, t0 + nj) of one job in
   int32_t job, n, f, n_win;
   int32_t t0, nj, traj_off;          // job trajectory range, first wave trajectory
   int32_t log_split0;                // slices per trajectory of the first-batch marginal
+  int64_t merge_off;                 // (trajectory, gate) pairs of the pieces before
   int32_t grow;                      // swin's windows write the states from |0...0> themselves
   int32_t start[kRgMaxBatches], b[kRgMaxBatches];
 };
@@ -845,6 +846,8 @@ struct RgWave {                      // device arrays of one wave (all in the wo
   int32_t* counts;                   // [kRgMaxBatches + 1] elements per batch level (device)
   int64_t cap;                       // element capacity
   float* pop; double* part;
+  const int64_t* merge_start;        // [n_pieces] RgPiece::merge_off
+  int64_t n_merge;                   // (trajectory, gate) pairs of the wave
   const int64_t* m0_start;           // [n_pieces + 1] first-batch marginal tasks per piece
   uint64_t* done;                    // [n_jobs + 1] completion stamps or null
   int32_t* bad_flag;

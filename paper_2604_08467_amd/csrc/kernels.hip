@@ -27,17 +27,13 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 
 
-__global__ void upv_merge_kernel(GateCtx g, int64_t E, float2* __restrict__ merged) {
-  for (int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; id < E * g.G; id += (int64_t)gridDim.x * blockDim.x) {
-    const int traj = (int)(id / g.G), gate = (int)(id % g.G);
-    float2 m[16];
-    merge_gate(g, gate, traj, m);
-    float4* o = reinterpret_cast<float4*>(merged + id * 16);
-    for (int i = 0; i < 8; ++i) o[i] = make_float4(m[2 * i].x, m[2 * i].y, m[2 * i + 1].x, m[2 * i + 1].y);
+__global__ void __launch_bounds__(256) upv_merge_kernel(GateCtx g, int64_t E, float2* __restrict__ merged) {
+  const int64_t total = E * g.G * 16;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t id = i >> 4;
+    merged[i] = merge_gate(g, (int)(id % g.G), (int)(id / g.G), (int)(i & 15));
   }
 }
-
-
 
 __device__ inline int slice_base(const AbsorbStep& st, const uint64_t* prefix) {
   int sb = 0;
@@ -2122,7 +2118,7 @@ hipError_t launch_part_vm(const AbsorbStep* d_steps, int n_steps, int peak, Gate
 hipError_t launch_upv_merge(GateCtx g, int64_t E, float2* merged, hipStream_t stream) {
   const int64_t n = E * g.G;
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(upv_merge_kernel, dim3(grid_blocks((n + 127) / 128)), dim3(128), 0, stream, g, E, merged);
+  hipLaunchKernelGGL(upv_merge_kernel, dim3(grid_blocks((n * 16 + 255) / 256)), dim3(256), 0, stream, g, E, merged);
   return hipGetLastError();
 }
 

@@ -355,7 +355,7 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
     const int ls_target = 4;
     std::vector<RgPiece> pcs(P);
     std::vector<int32_t> traj_piece((size_t)wp.T);
-    std::vector<int64_t> traj_row0((size_t)wp.T + 1), m0_start((size_t)P + 1);
+    std::vector<int64_t> traj_row0((size_t)wp.T + 1), m0_start((size_t)P + 1), merge_start((size_t)P);
     Arena wa;
     wa.base = arena;
     wa.cap = arena_bytes - 4096;
@@ -408,6 +408,8 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
         row += jb.shots_per_traj[ps.t0 + i];
       }
       m0_start[k] = mt;
+      merge_start[k] = pc.merge_off = w.n_merge;
+      w.n_merge += ps.nj * p.G;
       mt += ps.nj << pc.log_split0;
       part_rows += ps.nj << pc.log_split0;
       toff += ps.nj;
@@ -447,7 +449,8 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
     w.traj_piece = (const int32_t*)put(traj_piece.data(), traj_piece.size() * 4);
     w.traj_row0 = (const int64_t*)put(traj_row0.data(), traj_row0.size() * 8);
     w.m0_start = (const int64_t*)put(m0_start.data(), m0_start.size() * 8);
-    if (!w.pieces || !w.traj_piece || !w.traj_row0 || !w.m0_start)
+    w.merge_start = (const int64_t*)put(merge_start.data(), merge_start.size() * 8);
+    if (!w.pieces || !w.traj_piece || !w.traj_row0 || !w.m0_start || !w.merge_start)
       return fail(PTSBE_ERR_OUT_OF_MEMORY, "wave tables do not fit");
     w.n_pieces = P;
     w.T = (int32_t)wp.T;
@@ -514,7 +517,7 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
   const bool replay = use_graph && set->key == key && set->execs.size() == waves.size();
   if (use_graph && !replay) set->drop_graphs();
   int64_t launches = 0;
-  const int g_mem = set->n_cu * 8, g_samp = set->n_cu * 2;
+  const int g_mem = set->n_cu * 8, g_samp = set->n_cu * 8;
   for (size_t wi = 0; wi < waves.size(); ++wi) {
     const WaveLaunch& L = wl[wi];
     if (replay) {

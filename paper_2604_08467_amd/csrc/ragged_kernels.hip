@@ -84,12 +84,12 @@ __global__ void __launch_bounds__(kRgThreads) rg_prepare_kernel(RgWave w) {
     const RgPiece& pc = w.pieces[p];
     const int64_t sz = (int64_t)pc.nj << pc.n, mask = ((int64_t)1 << pc.n) - 1;
     for (int64_t i = pc.grow ? sz : gid; i < sz; i += stride) pc.psi[i] = make_float2((i & mask) == 0 ? 1.f : 0.f, 0.f);
-    float2* merged = const_cast<float2*>(pc.g.merged);
-    for (int64_t id = gid; id < (int64_t)pc.nj * pc.g.G; id += stride) {
-      float2 m[16];
-      merge_gate(pc.g, (int)(id % pc.g.G), (int)(id / pc.g.G), m);
-      for (int i = 0; i < 16; ++i) merged[id * 16 + i] = m[i];
-    }
+  }
+  for (int64_t i = gid; i < 16 * w.n_merge; i += stride) {
+    const RgPiece& pc = w.pieces[find_le(w.merge_start, w.n_pieces, i >> 4)];
+    const int64_t at = (i >> 4) - pc.merge_off;
+    const_cast<float2*>(pc.g.merged)[at * 16 + (i & 15)] =
+        merge_gate(pc.g, (int)(at % pc.g.G), (int)(at / pc.g.G), (int)(i & 15));
   }
   for (int64_t r = gid; r < w.R; r += stride) {
     w.ids[0][r] = (int32_t)r;
