@@ -129,9 +129,15 @@ size_t join_traj_bytes(const ptsbe::BatchPlan& bp) {
 // A last step of an LDS sweep that raises the rank may write its output straight to HBM.
 bool direct_step(const ptsbe::AbsorbStep& st) { return st.nK <= 1 && st.nN > st.nK && st.nK + st.nN <= 4; }
 
-// One LDS sweep launch (part_vm_kernel) over the steps [first, first + n_steps) of a
-// part (d_steps: its first step on the device); under profiling, HIP events on the launch stream and the steps' algorithmic
-// flops (8 per complex multiply-add: 8 2^(rC + nK) per step and job).
+// Sweeps with a job a lane pay from this many jobs on: 15 steps take them 30 us and 0.2 us
+// a thousand jobs, part_vm_kernel 30 us and 0.55 us; below, their wavefronts leave SIMDs
+// without work.  Their step tables are in LDS.
+constexpr int64_t kLaneSweepJobs = 32768;
+constexpr int kLaneSweepSteps = 512;
+
+// One sweep launch (part_vm_kernel or part_lanes_kernel) over the steps [first, first +
+// n_steps) of a part (d_steps: its first step on the device); under profiling, HIP events
+// on the launch stream and the steps' algorithmic flops (8 per complex multiply-add: 8 2^(rC + nK) per step and job).
 ptsbe_status_t timed_part_vm(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbStep* d_steps, int first,
                              int n_steps, int peak, const ptsbe::GateCtx& g, int64_t n_jobs, const int32_t* job_traj,
                              int32_t traj_base, const uint64_t* job_prefix, const ptsbe::InitArgs& init, float2* out,
@@ -156,8 +162,15 @@ ptsbe_status_t timed_part_vm(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::Ab
     const ptsbe::AbsorbStep& last = pp.steps[(size_t)(first + n_steps) - 1];
     if (last.rC > lds_peak && last.rC == out_rank && direct_step(last)) direct = 1;
   }
-  HIP_TRY(ptsbe::launch_part_vm(d_steps + first, n_steps, direct ? lds_peak : peak, g, n_jobs, job_traj, traj_base, job_prefix,
-                                p.NW, init, out, out_rank, direct, s));
+  bool raise = false;
+  const int lanes = init.Vprev && job_prefix && n_jobs >= kLaneSweepJobs && n_steps <= kLaneSweepSteps
+                        ? ptsbe::lane_sweep_rank(pp.steps.data() + first, n_steps, init.r0, &raise) : 0;
+  if (lanes != 0)
+    HIP_TRY(ptsbe::launch_part_lanes(d_steps + first, n_steps, lanes, raise, g, n_jobs, job_traj, traj_base, job_prefix,
+                                     p.NW, init, out, s));
+  else
+    HIP_TRY(ptsbe::launch_part_vm(d_steps + first, n_steps, direct ? lds_peak : peak, g, n_jobs, job_traj, traj_base,
+                                  job_prefix, p.NW, init, out, out_rank, direct, s));
   if (p.profile) {
     HIP_TRY(hipEventRecord(ev.second, s));
     p.vm_evs.push_back(ev);

@@ -505,6 +505,14 @@ struct InitArgs {
   int pos[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // sliced positions in the parent tensor (ascending)
   int q[8] = {0, 0, 0, 0, 0, 0, 0, 0};     // qubit whose prefix bit fixes each
 };
+// Sweeps with a job a lane (part_lanes.hip): n steps on a tensor of rank r0 = 4 or 5 taken
+// from init, all in place on one leg (sliced or not) or on two, the last one possibly
+// splitting its leg into itself and a new top position (*raise).  lane_sweep_rank: r0 for
+// such steps, else 0.
+int lane_sweep_rank(const AbsorbStep* st, int n, int r0, bool* raise);
+hipError_t launch_part_lanes(const AbsorbStep* d_steps, int n_steps, int rank, bool raise, GateCtx g, int64_t n_jobs,
+                             const int32_t* job_traj, int32_t traj_base, const uint64_t* job_prefix, int NW,
+                             const InitArgs& init, float2* out, hipStream_t stream);
 // Run all steps of one part in LDS, up to 64 jobs per workgroup.
 // jobs: traj of job = job_traj ? job_traj[job] : job0 + job; prefix words of job.
 // peak: largest rank held in LDS; direct = 1: the last step (contracted legs <= 1,
