@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_util.h"
 #include "internal.h"
@@ -1058,19 +1059,38 @@ __global__ void __launch_bounds__(256) theta_T_kernel(const float2* __restrict__
   }
 }
 
-// One workgroup = 4 wavefronts = 64 rows of one trajectory (16 per wave) x a tile
-// of XT = 16 NC values of x.  The inner dimension runs in chunks of 32 slots:
-// Theta[x][chunk] is staged in LDS in MFMA fragment order (double-buffered, the
-// next chunk in flight during the MFMAs), and each lane builds its A operand
-// M_f(row) on the fly from the row's V entries (for K = 32 the chunk fixes a and
-// the lane's b runs over 8 values it keeps in registers).  Output: v_mfma
-// accumulators hold pi[row][x] directly.
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {       // f(0), .., f(N - 1) as constants
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// One workgroup = 4 wavefronts = 64 rows of one trajectory (16 per wave) x a tile of XT =
+// 16 NC values of x.  The inner dimension runs in chunks of 32 slots: Theta[x][chunk] is
+// staged in LDS in MFMA fragment order (double-buffered, the next chunks in flight during
+// the MFMAs), and each lane builds its A operand M_f(row) on the fly from the row's V
+// entries (a chunk fixes a, or two of them, and the lane's b runs over K / 4 values it keeps
+// in registers).  Output: v_mfma accumulators hold pi[row][x] directly.
+//
+// On this chip the FP32 MFMAs (32 cycles per 16 x 16 x 4) and the vector instructions (4
+// cycles) of a SIMD do not overlap, so that what bounds the kernel is 32 cycles an MFMA and
+// 4 an instruction, and with few x (NC = 1, 2) there is little to hide behind an MFMA: the
+// chunks are unrolled (which slots are real and which imaginary parts is then static, two
+// instructions a k-step), addresses are scalar bases with 32-bit lane offsets fixed before
+// the loop, and waves without rows take no MFMAs.  50-qubit chain, 4096 x 1000 shots in
+// batches of 5, all joins of a pass: 11.0 -> 9.4 ms (NC = 1), 8.9 -> 7.5 (NC = 2); 384 x
+// 1000 in batches of 10: 19.1 -> 16.8 (NC = 8).
 template <int K, int NC>
-__global__ void __launch_bounds__(256) qform_mfma_kernel(QformArgs a) {
+__global__ void __launch_bounds__(256, NC == 8 ? 3 : 4) qform_mfma_kernel(QformArgs a) {
   constexpr int ROWS = 64, KK = K * K, KC = 32, NS = KC / 4, XT = 16 * NC, NCH = KK / KC, KB = K / 4;
-  constexpr int F4C = KC * XT / 4;              // float4 of Theta per chunk
-  constexpr int PL = (F4C + 255) / 256;          // float4 per thread per chunk
-  static_assert(PL <= 4, "four float4 per thread at most");
+  constexpr int LW = NC == 1 ? 2 : 4;            // floats of Theta per load
+  constexpr int PL = KC * XT / LW / 256;         // loads per thread per chunk
+  constexpr int PF = PL == 1 ? 4 : 2;            // chunks of Theta in flight
+  constexpr int VI = ROWS * K / 256;             // V entries per thread
+  typedef float TL __attribute__((ext_vector_type(LW)));
+  static_assert(PL >= 1 && PL <= 4 && NCH >= PF, "one to four loads per thread");
   __shared__ float Thl[2][KC * XT];
   __shared__ float2 Vs[ROWS][K + 1];
   // Workgroups go round-robin to the 8 XCDs in linear launch order; renumber them
@@ -1097,133 +1117,143 @@ __global__ void __launch_bounds__(256) qform_mfma_kernel(QformArgs a) {
   const int x0 = (int)bz * XT;
   if (x0 >= nx) return;
   const int xv = nx - x0 < XT ? nx - x0 : XT;         // valid x of this tile
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lo_b = xb_bits < 12 ? xb_bits : 12, lo_k = a.lk_bits < 12 ? a.lk_bits : 12;
-  // stage the 64 rows of V (zero beyond the trajectory's rows)
-  for (int i = tid; i < ROWS * K; i += 256) {
-    const int rr = i / K, k = i % K;
-    const int64_t row = row0 + rr;
-    float2 v = make_float2(0.f, 0.f);
-    if (row < rows_t) {
-      const int64_t e = e_begin + (row >> xb_bits);
-      const uint32_t xb = (uint32_t)(row & ((1 << xb_bits) - 1));
-      v = a.V[(e - a.v_base) * a.v_stride + tab(a.tab, a.jd.vr_lo, a.jd.vr_hi, lo_b, xb) +
-              tab(a.tab, a.jd.vc_lo, a.jd.vc_hi, lo_k, (uint32_t)k)];
-    }
-    Vs[rr][k] = v;
-  }
-  // Theta chunk loader: float4 number idx holds slots 4s..4s+3 of the chunk at
-  // x = x0 + idx % XT (s = idx / XT); in LDS slot 4s + q of x = x0 + 16c + j sits
-  // at ((s * 64 + 16 q + j) * NC + c), the B operand of lane 16 q + j at k-step s.
+  const int nrow = rows_t - row0 < ROWS ? (int)(rows_t - row0) : ROWS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), q = lane >> 4;
+  // Theta chunk loader: load number idx holds slots LW u .. of the chunk at x = x0 + idx %
+  // XT (u = idx / XT); in LDS slot 4s + q of x = x0 + 16c + j sits at ((s * 64 + 16 q + j) *
+  // NC + c), the B operand of lane 16 q + j at k-step s.  (x beyond the last one repeat it:
+  // their columns are not stored.)
   const int32_t ts = a.tslot ? a.tslot[t - a.traj_base] : t - a.traj_base;
-  const float* Tt = a.Th + ((int64_t)ts * nx + x0) * KK;
-  int xlq[PL], sq[PL];
-  bool hq[PL], vq[PL];
+  const char* Tt = reinterpret_cast<const char*>(a.Th + ((int64_t)ts * nx + x0) * KK);
+  uint32_t from[PL];                                  // byte offset of the thread's load in chunk 0
+  int to[PL];                                         // and of its first slot in LDS
 #pragma unroll
   for (int i = 0; i < PL; ++i) {
-    const int idx = tid + 256 * i;
-    hq[i] = idx < F4C;
-    xlq[i] = idx % XT;
-    sq[i] = (idx / XT) % NS;
-    vq[i] = hq[i] && xlq[i] < xv;
+    const int idx = tid + 256 * i, xl = idx % XT, slot = LW * (idx / XT);
+    from[i] = (uint32_t)(xl < xv ? xl : xv - 1) * (KK * 4u) + 4u * (uint32_t)slot;
+    to[i] = (slot / 4 * 64 + slot % 4 * 16 + (xl & 15)) * NC + (xl >> 4);
   }
-  auto ld = [&](int ch, int xl, int s, bool ok) -> float4 {
-    return ok ? *reinterpret_cast<const float4*>(Tt + (int64_t)xl * KK + ch * KC + 4 * s)
-              : make_float4(0.f, 0.f, 0.f, 0.f);
-  };
-  auto st = [&](float* d, int xl, int s, float4 v) {
-    float* p = d + (s * 64 + (xl & 15)) * NC + (xl >> 4);
-    p[0] = v.x; p[16 * NC] = v.y; p[32 * NC] = v.z; p[48 * NC] = v.w;
-  };
-  float4 rq[PL];
+  TL rq[PF][PL];                                      // ring slot ch % PF
+  auto load = [&](auto CH) {
+    constexpr int ch = decltype(CH)::value;
 #pragma unroll
-  for (int i = 0; i < PL; ++i) rq[i] = ld(0, xlq[i], sq[i], vq[i]);
+    for (int i = 0; i < PL; ++i) rq[ch % PF][i] = *reinterpret_cast<const TL*>(Tt + ch * (KC * 4) + (size_t)from[i]);
+  };
+  auto store = [&](auto CH) {
+    constexpr int ch = decltype(CH)::value;
 #pragma unroll
-  for (int i = 0; i < PL; ++i)
-    if (hq[i]) st(Thl[0], xlq[i], sq[i], rq[i]);
+    for (int i = 0; i < PL; ++i)
+#pragma unroll
+      for (int u = 0; u < LW; ++u) Thl[ch & 1][to[i] + 16 * NC * u] = rq[ch % PF][i][u];
+  };
+  static_for<PF>(load);
+  // The rows of V (zero beyond the trajectory's), thread's column k = tid % K, and the
+  // output's offsets.  Elements of this tile start at e_begin + row0 / 2^xb (64 rows are
+  // whole elements, or one element's); offsets from there fit 32 bits.  Tables of up to 12
+  // bits have one upper entry.
+  const int64_t e0 = e_begin - a.v_base + (row0 >> xb_bits);
+  const uint32_t xb0 = (uint32_t)row0 & ((1u << xb_bits) - 1u), xbm = (1u << xb_bits) - 1u;
+  const int64_t* tab_vr = a.tab + a.jd.vr_lo;
+  const int64_t* tab_ob = a.tab + a.jd.ob_lo;
+  const bool hi_b = xb_bits > 12;
+  auto xb_at = [&](const int64_t* lo, int64_t hi, int rr) -> int64_t {
+    const uint32_t xb = (xb0 + (uint32_t)rr) & xbm;
+    return lo[hi_b ? xb & 4095u : xb] + a.tab[hi + (hi_b ? (int64_t)(xb >> 12) : 0)];
+  };
+  const int vsh = __ffsll((long long)a.v_stride) - 1;     // V's rows are 2^rank entries
+  {
+    const int k = tid % K, r0 = tid / K;
+    const float2* Vt = a.V + (e0 << vsh) + a.tab[a.jd.vc_hi];
+    const int64_t vc = a.tab[a.jd.vc_lo + k];
+    float2 v[VI];
+    if (nrow == ROWS && xb_bits <= (K == 32 ? 3 : 4)) {
+      // a thread's rows are 256 / K apart: whole elements, the same xb
+      const uint32_t off = (uint32_t)((r0 >> xb_bits) << vsh) + (uint32_t)(vc + xb_at(tab_vr, a.jd.vr_hi, r0));
+      const uint32_t step = (uint32_t)((256 / K) >> xb_bits) << vsh;
+#pragma unroll
+      for (int it = 0; it < VI; ++it) v[it] = (Vt + it * step)[off];
+    } else {
+      int64_t at[VI];
+#pragma unroll
+      for (int it = 0; it < VI; ++it) {
+        const int rr = r0 + it * (256 / K) < nrow ? r0 + it * (256 / K) : nrow - 1;
+        at[it] = ((int64_t)((xb0 + (uint32_t)rr) >> xb_bits) << vsh) + vc + xb_at(tab_vr, a.jd.vr_hi, rr);
+      }
+#pragma unroll
+      for (int it = 0; it < VI; ++it) v[it] = Vt[at[it]];
+#pragma unroll
+      for (int it = 0; it < VI; ++it)
+        if (r0 + it * (256 / K) >= nrow) v[it] = make_float2(0.f, 0.f);
+    }
+#pragma unroll
+    for (int it = 0; it < VI; ++it) Vs[r0 + it * (256 / K)][k] = v[it];
+  }
+  store(std::integral_constant<int, 0>{});
   __syncthreads();
   // per lane: row rl, slot offset q; vb[i] = v[rl][4 i + q]
-  const int rl = wave * 16 + (lane & 15), q = lane >> 4;
+  const int rl = wave * 16 + (lane & 15);
   float2 vb[KB];
 #pragma unroll
   for (int i = 0; i < KB; ++i) vb[i] = Vs[rl][4 * i + q];
-  const int nout = 1 << a.b;
-  int64_t obase[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t row = row0 + wave * 16 + 4 * q + i;
-    obase[i] = -1;
-    if (row < rows_t) {
-      const int64_t e = e_begin + (row >> xb_bits);
-      const uint32_t xb = (uint32_t)(row & ((1 << xb_bits) - 1));
-      obase[i] = (e - a.v_base) * nout + tab(a.tab, a.jd.ob_lo, a.jd.ob_hi, lo_b, xb);
-    }
-  }
   floatx4 acc[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int ch = 0; ch < NCH; ++ch) {
-    const int buf = ch & 1;
-    const bool more = ch + 1 < NCH;
-    const int cn = more ? ch + 1 : ch;            // the last chunk reloads itself (not stored)
-#pragma unroll
-    for (int i = 0; i < PL; ++i) rq[i] = ld(cn, xlq[i], sq[i], vq[i]);
+  const bool rows = wave * 16 < nrow;                 // this wave has rows
+  static_for<NCH>([&](auto CH) {
+    constexpr int ch = decltype(CH)::value;
+    if constexpr (ch + PF < NCH) load(std::integral_constant<int, ch + PF>{});
     __builtin_amdgcn_sched_barrier(0);          // keep the loads ahead of the MFMAs
-    const float* B = Thl[buf];
+    if (rows) {
+      const float* B = Thl[ch & 1];
+      float2 va;
+      // slot (a, b = 4 ib + q): Re(v_a conj v_b) for a <= b, else Im(v_b conj v_a)
+      static_for<NS>([&](auto S) {
+        constexpr int s = decltype(S)::value, ib = s % KB, av = 4 * (ch * NS + s) / K;
+        if constexpr (ib == 0) va = Vs[rl][av];
+        const float2 w = vb[ib];
+        const float R = fmaf(va.x, w.x, va.y * w.y), I = fmaf(w.y, va.x, -(w.x * va.y));
+        const float m = av <= 4 * ib ? R : av > 4 * ib + 3 ? I : (av <= 4 * ib + q ? R : I);
+        float bv[NC];
+        if constexpr (NC == 8) {
+          const float4 b0 = *reinterpret_cast<const float4*>(B + (s * 64 + lane) * 8);
+          const float4 b1 = *reinterpret_cast<const float4*>(B + (s * 64 + lane) * 8 + 4);
+          bv[0] = b0.x; bv[1] = b0.y; bv[2] = b0.z; bv[3] = b0.w;
+          bv[4] = b1.x; bv[5] = b1.y; bv[6] = b1.z; bv[7] = b1.w;
+        } else if constexpr (NC == 4) {
+          const float4 b0 = *reinterpret_cast<const float4*>(B + (s * 64 + lane) * 4);
+          bv[0] = b0.x; bv[1] = b0.y; bv[2] = b0.z; bv[3] = b0.w;
+        } else if constexpr (NC == 2) {
+          const float2 b0 = *reinterpret_cast<const float2*>(B + (s * 64 + lane) * 2);
+          bv[0] = b0.x; bv[1] = b0.y;
+        } else {
+          bv[0] = B[s * 64 + lane];
+        }
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int kstep = ch * NS + s;
-      const int av = (4 * kstep) / K;               // the slot's a: uniform
-      const int ib = s % KB;                         // kstep % KB: static
-      const int b = 4 * ib + q;
-      const float2 va = Vs[rl][av];
-      const float2 w = vb[ib];
-      const float R = va.x * w.x + va.y * w.y;       // Re(v_a conj v_b)
-      const float I = w.y * va.x - w.x * va.y;       // Im(v_b conj v_a)
-      const float m = av <= b ? R : I;
-      if constexpr (NC == 8) {
-        const float4 bq = *reinterpret_cast<const float4*>(B + (s * 64 + lane) * 8);
-        const float4 bp = *reinterpret_cast<const float4*>(B + (s * 64 + lane) * 8 + 4);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.x, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.y, acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.z, acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.w, acc[3], 0, 0, 0);
-        acc[4] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bp.x, acc[4], 0, 0, 0);
-        acc[5] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bp.y, acc[5], 0, 0, 0);
-        acc[6] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bp.z, acc[6], 0, 0, 0);
-        acc[7] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bp.w, acc[7], 0, 0, 0);
-      } else if constexpr (NC == 4) {
-        const float4 bq = *reinterpret_cast<const float4*>(B + (s * 64 + lane) * 4);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.x, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.y, acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.z, acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.w, acc[3], 0, 0, 0);
-      } else if constexpr (NC == 2) {
-        const float2 bq = *reinterpret_cast<const float2*>(B + (s * 64 + lane) * 2);
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.x, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bq.y, acc[1], 0, 0, 0);
-      } else {
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, B[s * 64 + lane], acc[0], 0, 0, 0);
-      }
+        for (int c = 0; c < NC; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, bv[c], acc[c], 0, 0, 0);
+      });
     }
-    if (more) {
-#pragma unroll
-      for (int i = 0; i < PL; ++i)
-        if (hq[i]) st(Thl[buf ^ 1], xlq[i], sq[i], rq[i]);
+    if constexpr (ch + 1 < NCH) {
+      store(std::integral_constant<int, ch + 1>{});
+      __syncthreads();
     }
-    __syncthreads();
-  }
+  });
+  if (!rows) return;
   // acc[c][i] = pi[row wave*16 + 4 q + i][x0 + 16 c + lane % 16]
-  const int lo_x = a.xT_bits < 12 ? a.xT_bits : 12;
+  float* pop = a.pop + (e0 << a.b) + a.tab[a.jd.ox_hi + (x0 >> 12)];
+  const int64_t* tab_ox = a.tab + a.jd.ox_lo + (x0 & 4095);
+  uint32_t ox[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     const int xl = 16 * c + (lane & 15);
-    if (xl < xv) {
-      const int64_t ox = tab(a.tab, a.jd.ox_lo, a.jd.ox_hi, lo_x, (uint32_t)(x0 + xl));
+    ox[c] = (uint32_t)tab_ox[xl < xv ? xl : 0];
+  }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (obase[i] >= 0) a.pop[obase[i] + ox] = acc[c][i];
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int rr = wave * 16 + 4 * q + i, rc = rr < nrow ? rr : nrow - 1;
+    const uint32_t ob = (((xb0 + (uint32_t)rc) >> xb_bits) << a.b) + (uint32_t)xb_at(tab_ob, a.jd.ob_hi, rc);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (rr < nrow && 16 * c + (lane & 15) < xv) pop[(size_t)(ob + ox[c])] = acc[c][i];
   }
 }
 
