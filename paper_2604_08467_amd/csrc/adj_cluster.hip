@@ -30,6 +30,34 @@
 namespace ptsbe {
 namespace {
 
+// Column addressing of a cluster on tile positions cp[0..3]: cluster-local state
+// v sits at offset soff(v); the other tile bits (the column) are deposited around
+// the four positions (cs: cp ascending).
+struct ClusterCols {
+  int cp[4], cs[4];
+  __device__ explicit ClusterCols(uint32_t pos) {    // byte i: position of cluster-local bit i
+#pragma unroll
+    for (int i = 0; i < 4; ++i) cp[i] = cs[i] = (int)((pos >> (8 * i)) & 0xffu);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (cs[k] > cs[k + 1]) { const int t = cs[k]; cs[k] = cs[k + 1]; cs[k + 1] = t; }
+  }
+  __device__ uint32_t soff(int v) const {
+    return ((uint32_t)(v & 1) << cp[0]) | ((uint32_t)((v >> 1) & 1) << cp[1]) |
+           ((uint32_t)((v >> 2) & 1) << cp[2]) | ((uint32_t)((v >> 3) & 1) << cp[3]);
+  }
+  __device__ uint32_t colbase(uint32_t col) const {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t lo = col & ((1u << cs[i]) - 1u);
+      col = ((col >> cs[i]) << (cs[i] + 1)) | lo;
+    }
+    return col;
+  }
+};
+
 __device__ inline double2 zfma(double2 a, double2 b, double2 c) {
   return make_double2(fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y)));
 }

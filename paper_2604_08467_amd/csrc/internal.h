@@ -127,7 +127,8 @@ struct SvOp {
   int32_t gate;             // gate: index into the trajectory's merged gates
   int32_t slot;             // gate: staged matrix slot; cluster: index within the window;
                             // group: gate and slot hold the tile positions of thread bits 0 .. 7, a byte each
-  int8_t idx[16];           // gate: local entry (n, k), n * d + k, is merged entry idx[n * d + k]
+  int8_t idx[16];           // gate: local entry (n, k), n * d + k, is merged entry idx[n * d + k];
+                            // cluster: idx[0 .. np - 5] the tile positions of its column's bits
 };
 // Number of the register bit pair i < j < 4 of a two-qubit gate in a group.
 constexpr int svg_pair(int i, int j) { return i == 0 ? j - 1 : i + j; }   // 01 02 03 12 13 23

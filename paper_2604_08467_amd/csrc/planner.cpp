@@ -1030,6 +1030,24 @@ void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& S) {
 }
 
 namespace {
+// The tile positions not in `used`, those first that lanes 0..15 of a quarter wavefront can
+// step along without LDS bank conflicts: four of different swizzled slot bits (p mod 4 for
+// p < 8) where there are.
+std::vector<int> spread_positions(const std::vector<int>& used, int np) {
+  std::vector<int> rest, out;
+  for (int p = 0; p < np; ++p)
+    if (std::find(used.begin(), used.end(), p) == used.end()) rest.push_back(p);
+  for (int m = 0; m < 4; ++m)
+    for (size_t k = 0; k < rest.size(); ++k)
+      if (rest[k] < 8 && rest[k] % 4 == m) {
+        out.push_back(rest[k]);
+        rest.erase(rest.begin() + (std::ptrdiff_t)k);
+        break;
+      }
+  out.insert(out.end(), rest.begin(), rest.end());
+  return out;
+}
+
 // The gates of a window's ops (in order, np tile positions) gathered into groups: a gate
 // joins the open group while its positions and the group's are at most np - 8 and some
 // order of them has every two-qubit gate's local bit 0 below its local bit 1 (the
@@ -1059,18 +1077,7 @@ void group_sv_ops(const std::vector<SvOp>& in, int np, std::vector<SvOp>& out) {
     // lanes of a quarter wavefront over the LDS banks
     for (int p = np - 1; (int)order.size() < cap; --p)
       if (!in_order(p)) order.push_back(p);
-    // thread bits 0..3: positions of different swizzled slot bits (p mod 4, p < 8) where there are
-    std::vector<int> rest, lanes;
-    for (int p = 0; p < np; ++p)
-      if (!in_order(p)) rest.push_back(p);
-    for (int m = 0; m < 4; ++m)
-      for (size_t k = 0; k < rest.size(); ++k)
-        if (rest[k] < 8 && rest[k] % 4 == m) {
-          lanes.push_back(rest[k]);
-          rest.erase(rest.begin() + (std::ptrdiff_t)k);
-          break;
-        }
-    lanes.insert(lanes.end(), rest.begin(), rest.end());
+    const std::vector<int> lanes = spread_positions(order, np);
     SvOp h{};
     h.kind = kSvOpGroup;
     h.p0 = (int8_t)gates.size();
@@ -1091,7 +1098,10 @@ void group_sv_ops(const std::vector<SvOp>& in, int np, std::vector<SvOp>& out) {
   for (const SvOp& op : in) {
     if (op.kind == kSvOpCluster) {
       close();
-      out.push_back(op);
+      SvOp c = op;
+      const std::vector<int> cols = spread_positions({c.cpos[0], c.cpos[1], c.cpos[2], c.cpos[3]}, np);
+      for (size_t k = 0; k < cols.size(); ++k) c.idx[k] = (int8_t)cols[k];
+      out.push_back(c);
       continue;
     }
     for (int tries = 0; tries < 2; ++tries) {

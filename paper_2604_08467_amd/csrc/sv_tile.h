@@ -26,12 +26,13 @@ constexpr int kSvwThreads = 256;
 // swz is linear, swz(a ^ b) = swz(a) ^ swz(b), so each thread swizzles its own
 // part of an index once per op and XORs uniform parts in.
 __host__ __device__ inline uint32_t swz(uint32_t l) { return l ^ ((l >> 4) & 15u); }
+
+constexpr int kSvwPlain = -1;   // "precision" of a window without clusters
+
 __device__ inline uint32_t ins0(uint32_t m, int p) {   // zero bit inserted at position p
   const uint32_t lo = (1u << p) - 1u;
   return ((m & ~lo) << 1) | (m & lo);
 }
-
-constexpr int kSvwPlain = -1;   // "precision" of a window without clusters
 
 struct SvwArgs {
   int n, n_ops, n_plain, n_cl, cl_first, n_cl_total, G;
@@ -56,31 +57,50 @@ template <> struct SvwSplit<PTSBE_SPLIT_F16> {
   static __device__ floatx4_t mfma(V a, V b, floatx4_t c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 };
 
-// Column addressing of a cluster on tile positions cp[0..3]: cluster-local state
-// v sits at offset soff(v); the other tile bits (the column) are deposited around
-// the four positions (cs: cp ascending).
-struct ClusterCols {
-  int cp[4], cs[4];
-  __device__ explicit ClusterCols(uint32_t pos) {    // byte i: position of cluster-local bit i
+// Byte address of an LDS tile entry as a lane's part XOR uniform parts (the swizzle is
+// linear): positions' bits are deposited with one select and one XOR each.
+__device__ inline uint32_t pos_bytes(uint32_t bytes, int i) {   // byte i of `bytes`: a tile position
+  return 8u * swz(1u << (bytes >> (8 * i) & 0xffu));
+}
+__device__ inline float2& tile_at(float2* tile, uint32_t addr) {
+  return *reinterpret_cast<float2*>(reinterpret_cast<char*>(tile) + addr);
+}
+
+// Addresses of a cluster's entries: lane 16 q + j of wave w, column tile ct takes column
+// 64 ct' + 16 w + j (in the order of its column positions: the first four spread over the
+// LDS banks), states 4 s + q where it reads (FP32) and 4 q + i where it writes.
+template <int NP>
+struct ClusterAt {
+  uint32_t r, w;            // lane parts: column j and state bits 0, 1 = q (read), 2, 3 = q (written)
+  uint32_t s1[4], s4[4];    // states i and 4 i
+  uint32_t c[NP - 8];       // column tile bits
+  __device__ ClusterAt(uint32_t cpos, uint2 cols) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    uint32_t j = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) cp[i] = cs[i] = (int)((pos >> (8 * i)) & 0xffu);
+    for (int b = 0; b < 4; ++b) j ^= (lane >> b & 1u) ? pos_bytes(cols.x, b) : 0u;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int b = 0; b < 2; ++b) j ^= (wave >> b & 1u) ? pos_bytes(cols.y, b) : 0u;
+    uint32_t p[4];
 #pragma unroll
-      for (int k = 0; k < 3; ++k)
-        if (cs[k] > cs[k + 1]) { const int t = cs[k]; cs[k] = cs[k + 1]; cs[k + 1] = t; }
-  }
-  __device__ uint32_t soff(int v) const {
-    return ((uint32_t)(v & 1) << cp[0]) | ((uint32_t)((v >> 1) & 1) << cp[1]) |
-           ((uint32_t)((v >> 2) & 1) << cp[2]) | ((uint32_t)((v >> 3) & 1) << cp[3]);
-  }
-  __device__ uint32_t colbase(uint32_t col) const {
+    for (int i = 0; i < 4; ++i) p[i] = pos_bytes(cpos, i);
+    r = j ^ ((lane & 16u) ? p[0] : 0u) ^ ((lane & 32u) ? p[1] : 0u);
+    w = j ^ ((lane & 16u) ? p[2] : 0u) ^ ((lane & 32u) ? p[3] : 0u);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t lo = col & ((1u << cs[i]) - 1u);
-      col = ((col >> cs[i]) << (cs[i] + 1)) | lo;
+      s1[i] = (i & 1 ? p[0] : 0u) ^ (i & 2 ? p[1] : 0u);
+      s4[i] = (i & 1 ? p[2] : 0u) ^ (i & 2 ? p[3] : 0u);
     }
-    return col;
+#pragma unroll
+    for (int b = 0; b < NP - 10; ++b) c[b] = pos_bytes(cols.y, 2 + b);
+  }
+  __device__ uint32_t tile(int ct) const {       // uniform
+    uint32_t a = 0;
+#pragma unroll
+    for (int b = 0; b < NP - 10; ++b)
+      if (ct >> b & 1) a ^= c[b];
+    return a;
   }
 };
 
@@ -90,8 +110,9 @@ struct ClusterCols {
 // One 16x16x32 MFMA covers the whole inner dimension: per 16 columns, 2 row tiles
 // (real and imaginary outputs) x 3 products.  Each wavefront reads and then
 // overwrites only its own columns.  Needs blockDim.x == 256 and np >= 10.
-template <int PREC>
-__device__ inline void apply_cluster_split(const ClusterCols& cc, const float2* __restrict__ U, int np, float2* tile) {
+template <int PREC, int NP>
+__device__ __forceinline__ void apply_cluster_split(const ClusterAt<NP>& at, const float2* __restrict__ U,
+                                                    float2* tile) {
   typedef typename SvwSplit<PREC>::E E;
   typedef typename SvwSplit<PREC>::V V;
   const int tid = threadIdx.x;
@@ -114,19 +135,13 @@ __device__ inline void apply_cluster_split(const ClusterCols& cc, const float2* 
         al[rt][i] = (E)(a[rt][i] - (float)h);
       }
   }
-  const int ncol = 1 << (np - 4), per_wave = ncol >> 2, nct = per_wave >> 4;
-  // swizzled parts of the addresses: this lane's column and states, then the
-  // wavefront's column tile
-  const uint32_t pj = swz(cc.colbase((uint32_t)j));
-  uint32_t ps[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) ps[i] = pj ^ swz(cc.soff(4 * q + i));
-  for (int ct = 0; ct < nct; ++ct) {
-    const uint32_t pc = swz(cc.colbase((uint32_t)(wave * per_wave + 16 * ct)));
+  for (int ct = 0; ct < (1 << (NP - 10)); ++ct) {
+    const uint32_t pc = at.tile(ct);
     float x[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float2 v = tile[pc ^ ps[i]];
+      const float2 v = tile_at(tile, at.w ^ (pc ^ at.s1[i]));
       x[2 * i] = v.x;
       x[2 * i + 1] = v.y;
     }
@@ -163,16 +178,17 @@ __device__ inline void apply_cluster_split(const ClusterCols& cc, const float2* 
     }
     // D[4 q + i][j]: output state 4 q + i of column j
 #pragma unroll
-    for (int i = 0; i < 4; ++i) tile[pc ^ ps[i]] = make_float2(acc[0][i] * unscale, acc[1][i] * unscale);
+    for (int i = 0; i < 4; ++i)
+      tile_at(tile, at.w ^ (pc ^ at.s1[i])) = make_float2(acc[0][i] * unscale, acc[1][i] * unscale);
   }
   __syncthreads();
 }
 
 // FP32 cluster on v_mfma_f32_16x16x4f32 (inner index k < 16 real, >= 16 imaginary
 // parts; lane 16 q + j takes states 4 s + q of column j), U in LDS.
-__device__ inline void apply_cluster_f32(const ClusterCols& cc, const float2* __restrict__ U, int np, float2* tile) {
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, q = lane >> 4, j = lane & 15;
+template <int NP>
+__device__ __forceinline__ void apply_cluster_f32(const ClusterAt<NP>& at, const float2* __restrict__ U, float2* tile) {
+  const int lane = threadIdx.x & 63, q = lane >> 4, j = lane & 15;
   float af[2][8];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
@@ -180,19 +196,12 @@ __device__ inline void apply_cluster_f32(const ClusterCols& cc, const float2* __
     af[0][s] = u.x;  af[0][s + 4] = -u.y;
     af[1][s] = u.y;  af[1][s + 4] = u.x;
   }
-  const int ncol = 1 << (np - 4), per_wave = ncol >> 2, nct = per_wave >> 4;
-  const uint32_t pj = swz(cc.colbase((uint32_t)j));
-  uint32_t pr[4], pw[4];     // states 4 s + q (read) and 4 q + i (written)
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    pr[s] = pj ^ swz(cc.soff(4 * s + q));
-    pw[s] = pj ^ swz(cc.soff(4 * q + s));
-  }
-  for (int ct = 0; ct < nct; ++ct) {
-    const uint32_t pc = swz(cc.colbase((uint32_t)(wave * per_wave + 16 * ct)));
+  for (int ct = 0; ct < (1 << (NP - 10)); ++ct) {
+    const uint32_t pc = at.tile(ct);
     float2 x[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) x[s] = tile[pc ^ pr[s]];
+    for (int s = 0; s < 4; ++s) x[s] = tile_at(tile, at.r ^ (pc ^ at.s4[s]));
     floatx4_t acc0 = floatx4_t{0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
@@ -201,7 +210,7 @@ __device__ inline void apply_cluster_f32(const ClusterCols& cc, const float2* __
       acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(af[1][s], b, acc1, 0, 0, 0);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) tile[pc ^ pw[i]] = make_float2(acc0[i], acc1[i]);
+    for (int i = 0; i < 4; ++i) tile_at(tile, at.w ^ (pc ^ at.s1[i])) = make_float2(acc0[i], acc1[i]);
   }
   __syncthreads();
 }
@@ -210,12 +219,20 @@ __device__ inline bool czero(float2 v) { return v.x == 0.f && v.y == 0.f; }
 
 // Forms of a staged gate, worked out once per staging: at most one nonzero a row
 // (diagonal gates with diagonal Kraus factors, CNOT, Pauli products) costs one product
-// per amplitude.  Bits 2n, 2n + 1: the column of row n's nonzero.
+// per amplitude.  Bits 2n, 2n + 1: the column of row n's nonzero.  A dense one-qubit gate
+// whose diagonal or off-diagonal entries are all real or all imaginary (rotations about an
+// axis, Hadamard, with Pauli noise and damping) takes half the terms for those: bits 0, 1
+// for the diagonal and 2, 3 for the others, kEntry*.
 constexpr uint32_t kFormDense = 0x100, kFormDiag = 0x200;
+constexpr int kEntryComplex = 0, kEntryReal = 1, kEntryImag = 2;
 
+__device__ inline uint32_t entry_kind(float2 a, float2 b) {
+  return a.y == 0.f && b.y == 0.f ? kEntryReal : a.x == 0.f && b.x == 0.f ? kEntryImag : kEntryComplex;
+}
 __device__ inline uint32_t gate1_form(const float2* G) {
   const bool z00 = czero(G[0]), z01 = czero(G[1]), z10 = czero(G[2]), z11 = czero(G[3]);
-  if (!((z00 || z01) && (z10 || z11))) return kFormDense;
+  if (!((z00 || z01) && (z10 || z11)))
+    return kFormDense | entry_kind(G[0], G[3]) | entry_kind(G[1], G[2]) << 2;
   return (!z00 && !z11) ? kFormDiag : (uint32_t)z00 | ((uint32_t)!z11 << 2);
 }
 __device__ inline uint32_t gate2_form(const float2* G) {
@@ -246,18 +263,46 @@ __device__ inline float2 gmul(float2 g, float2 a) {
   return make_float2(fmaf(g.x, a.x, -(g.y * a.y)), fmaf(g.y, a.x, g.x * a.y));
 }
 
+// gmul and cfma for an entry of known kind: the zero part's terms left out.
+template <int KIND>
+__device__ __forceinline__ float2 kmul(float2 g, float2 a) {
+  if constexpr (KIND == kEntryReal) return make_float2(g.x * a.x, g.x * a.y);
+  else if constexpr (KIND == kEntryImag) return make_float2(-(g.y * a.y), g.y * a.x);
+  else return gmul(g, a);
+}
+template <int KIND>
+__device__ __forceinline__ float2 kfma(float2 g, float2 a, float2 c) {
+  if constexpr (KIND == kEntryReal) return make_float2(fmaf(g.x, a.x, c.x), fmaf(g.x, a.y, c.y));
+  else if constexpr (KIND == kEntryImag) return make_float2(fmaf(-g.y, a.y, c.x), fmaf(g.y, a.x, c.y));
+  else return cfma(g, a, c);
+}
+
+// A dense one-qubit gate on register bit B of x: D and O the kinds of its diagonal and
+// off-diagonal entries.
+template <int LB, int B, int D, int O>
+__device__ __forceinline__ void reg_dense1(float2 (&x)[1 << LB], float2 g00, float2 g01, float2 g10, float2 g11) {
+#pragma unroll
+  for (int l = 0; l < (1 << LB); ++l)
+    if (!(l >> B & 1)) {
+      const float2 a0 = x[l], a1 = x[l | 1 << B];
+      x[l] = kfma<O>(g01, a1, kmul<D>(g00, a0));
+      x[l | 1 << B] = kfma<D>(g11, a1, kmul<O>(g10, a0));
+    }
+}
+
 // A one-qubit gate on register bit B of x (g: [n][k] row-major in LDS).
 template <int LB, int B>
 __device__ __forceinline__ void reg_gate1(float2 (&x)[1 << LB], const float2* G, uint32_t form) {
   const float2 g00 = uniform2(G[0]), g01 = uniform2(G[1]), g10 = uniform2(G[2]), g11 = uniform2(G[3]);
-  if (form == kFormDense) {
-#pragma unroll
-    for (int l = 0; l < (1 << LB); ++l)
-      if (!(l >> B & 1)) {
-        const float2 a0 = x[l], a1 = x[l | 1 << B];
-        x[l] = cfma(g01, a1, gmul(g00, a0));
-        x[l | 1 << B] = cfma(g11, a1, gmul(g10, a0));
-      }
+  if (form & kFormDense) {
+    switch (form & 15u) {
+      case kEntryReal | kEntryReal << 2: reg_dense1<LB, B, kEntryReal, kEntryReal>(x, g00, g01, g10, g11); break;
+      case kEntryReal | kEntryImag << 2: reg_dense1<LB, B, kEntryReal, kEntryImag>(x, g00, g01, g10, g11); break;
+      case kEntryImag | kEntryReal << 2: reg_dense1<LB, B, kEntryImag, kEntryReal>(x, g00, g01, g10, g11); break;
+      case kEntryReal: reg_dense1<LB, B, kEntryReal, kEntryComplex>(x, g00, g01, g10, g11); break;
+      case kEntryReal << 2: reg_dense1<LB, B, kEntryComplex, kEntryReal>(x, g00, g01, g10, g11); break;
+      default: reg_dense1<LB, B, kEntryComplex, kEntryComplex>(x, g00, g01, g10, g11); break;
+    }
   } else if (form == kFormDiag) {
 #pragma unroll
     for (int l = 0; l < (1 << LB); ++l) x[l] = gmul(l >> B & 1 ? g11 : g00, x[l]);
@@ -329,13 +374,10 @@ __device__ __forceinline__ void apply_group(const uint4 h, const uint4* __restri
   const uint32_t tid = threadIdx.x;
   uint32_t pt = 0;                 // this thread's part of the address, then the register bits'
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const uint32_t p = ((b < 4 ? h.z : h.w) >> (8 * (b & 3))) & 0xffu;
-    pt ^= (tid >> b & 1u) ? swz(1u << p) : 0u;
-  }
-  uint32_t so[LB];
+  for (int b = 0; b < 8; ++b) pt ^= (tid >> b & 1u) ? pos_bytes(b < 4 ? h.z : h.w, b & 3) : 0u;
+  uint32_t so[LB];                 // uniform
 #pragma unroll
-  for (int i = 0; i < LB; ++i) so[i] = swz(1u << (h.y >> (8 * i) & 0xffu));
+  for (int i = 0; i < LB; ++i) so[i] = pos_bytes(h.y, i);
   float2 x[1 << LB];
 #pragma unroll
   for (int l = 0; l < (1 << LB); ++l) {
@@ -343,7 +385,7 @@ __device__ __forceinline__ void apply_group(const uint4 h, const uint4* __restri
 #pragma unroll
     for (int i = 0; i < LB; ++i)
       if (l >> i & 1) at ^= so[i];
-    x[l] = tile[at];
+    x[l] = tile_at(tile, at);
   }
   for (int s = 0; s < n; ++s) {
     const uint4 w = ops[2 * s];
@@ -371,7 +413,7 @@ __device__ __forceinline__ void apply_group(const uint4 h, const uint4* __restri
 #pragma unroll
     for (int i = 0; i < LB; ++i)
       if (l >> i & 1) at ^= so[i];
-    tile[at] = x[l];
+    tile_at(tile, at) = x[l];
   }
   __syncthreads();
 }
@@ -428,7 +470,8 @@ __device__ inline void load_pairs(const float2* __restrict__ A, const int* P, ui
 template <int NP>
 __device__ inline void load_fresh_pairs(const float2* __restrict__ A, const int* P, uint32_t lo, uint32_t fresh,
                                         floatx4_t (&v)[1 << (NP - 9)]) {
-  const uint32_t e = 2u * threadIdx.x;
+  uint32_t e = 2u * threadIdx.x;
+  asm volatile("" : "+v"(e));        // the conditions are worked out here, not kept over the tiles
 #pragma unroll
   for (int i = 0; i < (1 << (NP - 9)); ++i) {
     v[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -469,8 +512,9 @@ __device__ inline floatx4_t lds_get_pair(const floatx4_t* tile4, uint32_t pt2, i
 
 // Tiles [b0, b1) of a window over the states psi [n_jobs][2^n] (tile t of job j is number
 // (j << popc(live)) + t), their trajectories' merged gates and cluster matrices: pairs
-// loaded, the groups and clusters applied in LDS, pairs stored.  With no fresh position
-// the next tile's loads are issued before the current tile's ops.  LDS: the tile, n_plain
+// loaded, the groups and clusters applied in LDS, pairs stored.  Where every entry is read
+// and clusters are applied the next tile's loads are issued before the current tile's ops;
+// windows of plain gates are bound by their products and short of registers.  LDS: the tile, n_plain
 // staged gates, n_cl clusters, n_plain forms.  Ends with a barrier.
 template <int PREC, int NP, bool FRESH>
 __device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __restrict__ ops,
@@ -479,6 +523,7 @@ __device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __res
   float2* tile = reinterpret_cast<float2*>(lds);
   floatx4_t* tile4 = lds;
   constexpr int PPT = 1 << (NP - 9);     // pairs per thread
+  constexpr bool AHEAD = !FRESH && PREC != kSvwPlain;
   float2* Gs = tile + (1 << NP);                   // [n_plain][16]
   float2* Us = Gs + 16 * a.n_plain;                // [n_cl][256]
   uint32_t* forms = reinterpret_cast<uint32_t*>(Us + 256 * a.n_cl);   // [n_plain]
@@ -495,22 +540,22 @@ __device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __res
     if (FRESH) load_fresh_pairs<NP>(A, a.P, lo, a.fresh, v);
     else load_pairs<NP>(A, a.P, lo, v);
   };
-  load(b0);
-  int64_t last_job = -1;
-  for (int64_t bid = b0; bid < b1; ++bid) {
-    const int64_t job = bid >> tb;
-    if (job != last_job) {
-      // stage the trajectory's gate matrices and cluster matrices (the previous
-      // tile's last barrier has passed: nobody reads Gs / Us any more)
-      for (int i = tid; i < 256 * a.n_cl; i += kSvwThreads)
-        Us[i] = Ucl[((int64_t)job * a.n_cl_total + a.cl_first) * 256 + i];
-      stage_gates(ops, a.n_ops, merged + (a.traj_base + job) * a.G * 16, Gs, forms);
-      last_job = job;
-    }
+  auto put = [&]() {
 #pragma unroll
     for (int i = 0; i < PPT; ++i) lds_put_pair(tile4, pt2, i, v[i]);
+  };
+  auto stage = [&](int64_t job) {
+    for (int i = tid; i < 256 * a.n_cl; i += kSvwThreads)
+      Us[i] = Ucl[((int64_t)job * a.n_cl_total + a.cl_first) * 256 + i];
+    stage_gates(ops, a.n_ops, merged + (a.traj_base + job) * a.G * 16, Gs, forms);
+  };
+  load(b0);
+  stage(b0 >> tb);
+  put();
+  for (int64_t bid = b0; bid < b1; ++bid) {
     __syncthreads();   // the tile (and any staging) is complete before the first op
-    if (!FRESH && bid + 1 < b1) load(bid + 1);   // in flight during the ops
+    const bool more = bid + 1 < b1;
+    if (AHEAD && more) load(bid + 1);   // in flight during the ops
     for (int s = 0; s < a.n_ops;) {
       // the record's first four dwords as one uniform (scalar-cache) load
       const uint4 w = reinterpret_cast<const uint4*>(ops)[2 * s];
@@ -521,18 +566,34 @@ __device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __res
       } else {
         ++s;
         if constexpr (PREC != kSvwPlain) {
-          const ClusterCols cc(w.y);
-          if constexpr (PREC == PTSBE_C64) apply_cluster_f32(cc, Us + 256 * (int)w.w, NP, tile);
-          else apply_cluster_split<PREC>(cc, Us + 256 * (int)w.w, NP, tile);
+          const uint4 w2 = reinterpret_cast<const uint4*>(ops)[2 * s - 1];
+          const ClusterAt<NP> at(w.y, make_uint2(w2.x, w2.y));
+          if constexpr (PREC == PTSBE_C64) apply_cluster_f32<NP>(at, Us + 256 * (int)w.w, tile);
+          else apply_cluster_split<PREC, NP>(at, Us + 256 * (int)w.w, tile);
         }
       }
     }
-    float2* A = psi + (job << n) + tile_base(bid);
+    floatx4_t o[PPT];
 #pragma unroll
-    for (int i = 0; i < PPT; ++i) *pair_at(A + pair_hi<NP>(a.P, i), lo) = lds_get_pair(tile4, pt2, i);
-    __syncthreads();   // every thread has read its part of the tile before it is refilled
-    if (FRESH && bid + 1 < b1) load(bid + 1);
+    for (int i = 0; i < PPT; ++i) o[i] = lds_get_pair(tile4, pt2, i);
+    float2* A = psi + ((bid >> tb) << n) + tile_base(bid);
+    auto keep = [&]() {
+#pragma unroll
+      for (int i = 0; i < PPT; ++i) *pair_at(A + pair_hi<NP>(a.P, i), lo) = o[i];
+    };
+    if (!AHEAD) keep();
+    __syncthreads();   // every thread has read its part of the tile
+    if (more) {
+      if (!AHEAD) load(bid + 1);
+      put();
+    }
+    // with loads ahead the next tile takes this one's place before this one is stored: memory
+    // operations finish in order, so a wait for the loads after the stores would wait for
+    // them too
+    if (AHEAD) keep();
+    if (more && (bid + 1) >> tb != bid >> tb) stage((bid + 1) >> tb);   // the next trajectory's gates
   }
+  __syncthreads();
 }
 
 }  // namespace
