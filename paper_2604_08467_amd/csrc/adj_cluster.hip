@@ -188,14 +188,27 @@ template <int NP> __device__ inline bool has_pair() { return NP > 8 || threadIdx
 // cluster's states or its columns, spread over the slots.  Linear, as swz.
 __device__ inline uint32_t cl_swz(uint32_t l) { return l ^ ((l >> 4) & 15u) ^ ((l >> 8) & 15u); }
 
-// The pairs of the tile at `base` of a state (null: the state |0 .. 0>, nothing is read).
+// The pairs of the tile at `base` of a state (null: the state |0 .. 0>, nothing is read);
+// entries with a tile position of `fresh` set are zero and not read.
 template <int NP>
-__device__ inline void cl_load(const float2* state, uint32_t base, const int* P, uint32_t lo,
+__device__ inline void cl_load(const float2* state, uint32_t base, const int* P, uint32_t lo, uint32_t fresh,
                                floatx4_t (&v)[kPairs<NP>]) {
   if (!state) {
 #pragma unroll
     for (int i = 0; i < kPairs<NP>; ++i)
       v[i] = floatx4_t{(base | lo | pair_hi<NP>(P, i)) == 0u ? 1.f : 0.f, 0.f, 0.f, 0.f};
+    return;
+  }
+  if (fresh) {
+    uint32_t e = 2u * threadIdx.x;
+    asm volatile("" : "+v"(e));        // the conditions are worked out here, not kept over the tiles
+    if (has_pair<NP>())
+#pragma unroll
+      for (int i = 0; i < kPairs<NP>; ++i) {
+        v[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        if (((e + 512u * i) & fresh) == 0)
+          v[i] = *reinterpret_cast<const floatx4_t*>(state + (base | lo | pair_hi<NP>(P, i)));
+      }
     return;
   }
   if (has_pair<NP>())
@@ -431,9 +444,9 @@ __device__ inline void cl_back(const ClTables<NP, float2>& tb, int c, float2* ps
 }
 
 // The tiles [b0, b1) of this workgroup within its trajectory.
-__device__ inline void cl_range(const AdjClArgs& a, int np, int64_t& job, uint32_t& b0, uint32_t& b1) {
+__device__ inline void cl_range(const AdjClArgs& a, int64_t& job, uint32_t& b0, uint32_t& b1) {
   job = blockIdx.x / a.wpj;
-  const uint32_t part = blockIdx.x % a.wpj, tiles = 1u << (a.n - np);
+  const uint32_t part = blockIdx.x % a.wpj, tiles = 1u << __popc(a.live);
   b0 = (uint32_t)((uint64_t)tiles * part / a.wpj);
   b1 = (uint32_t)((uint64_t)tiles * (part + 1) / a.wpj);
 }
@@ -452,19 +465,19 @@ __global__ void __launch_bounds__(256) adj_cl_fwd_kernel(AdjClArgs a, const type
   const uint32_t lo = pair_lo(a.P), pt2 = cl_swz(2u * threadIdx.x);
   int64_t job;
   uint32_t b0, b1;
-  cl_range(a, NP, job, b0, b1);
+  cl_range(a, job, b0, b1);
   const float2* in = a.psi_in ? a.psi_in + (job << a.n) : nullptr;
   float2* out = a.psi_out + (job << a.n);
-  uint32_t base = deposit_other(b0, a.other);
+  uint32_t base = deposit_other(b0, a.live);
   floatx4_t v[kPairs<NP>];
-  cl_load<NP>(in, base, a.P, lo, v);
+  cl_load<NP>(in, base, a.P, lo, a.fresh, v);
   cl_stage(Uall + (job * a.n_cl_total + a.cl_off) * 256, a.n_cl, false, tb.U);
   cl_addresses<T>(a.pos, a.n_cl, 1 << (NP - 8), tb.tab, tb.col);
   for (uint32_t t = b0; t < b1; ++t) {
-    const uint32_t next = ((base | ~a.other) + 1u) & a.other;   // the next tile's other bits
+    const uint32_t next = ((base | ~a.live) + 1u) & a.live;   // the next tile's other bits
     cl_put<NP>(tile, pt2, v);
     __syncthreads();
-    if (t + 1 < b1) cl_load<NP>(in, next, a.P, lo, v);
+    if (t + 1 < b1) cl_load<NP>(in, next, a.P, lo, a.fresh, v);
     for (int c = 0; c < a.n_cl; ++c) {
       cl_apply<NP, T>(tb, c, tb.U, tile);
       __syncthreads();
@@ -493,13 +506,13 @@ __global__ void __launch_bounds__(256, 3) adj_cl_bwd_kernel(AdjClArgs a, const f
   const uint32_t lo = pair_lo(a.P), pt2 = cl_swz(2u * tid);
   int64_t job;
   uint32_t b0, b1;
-  cl_range(a, NP, job, b0, b1);
+  cl_range(a, job, b0, b1);
   const float2* in = a.psi_in ? a.psi_in + (job << a.n) : nullptr;
   float2* lg = a.lam + (job << a.n);
-  uint32_t base = deposit_other(b0, a.other);
+  uint32_t base = deposit_other(b0, a.live);
   floatx4_t v[kPairs<NP>], w[kPairs<NP>];
-  cl_load<NP>(in, base, a.P, lo, v);
-  cl_load<NP>(lg, base, a.P, lo, w);
+  cl_load<NP>(in, base, a.P, lo, a.fresh, v);
+  cl_load<NP>(lg, base, a.P, lo, 0u, w);
   {
     const float2* U = Uall + (job * a.n_cl_total + a.cl_off) * 256;
     cl_stage(U, a.n_cl, true, tb.U);
@@ -513,10 +526,10 @@ __global__ void __launch_bounds__(256, 3) adj_cl_bwd_kernel(AdjClArgs a, const f
     cl_put<NP>(psi, pt2, v);
     cl_put<NP>(lam, pt2, w);
     __syncthreads();
-    const uint32_t next = ((base | ~a.other) + 1u) & a.other;   // the next tile's other bits
+    const uint32_t next = ((base | ~a.live) + 1u) & a.live;   // the next tile's other bits
     if (t + 1 < b1) {
-      cl_load<NP>(in, next, a.P, lo, v);
-      cl_load<NP>(lg, next, a.P, lo, w);
+      cl_load<NP>(in, next, a.P, lo, a.fresh, v);
+      cl_load<NP>(lg, next, a.P, lo, 0u, w);
     }
     for (int c = a.n_cl - 1; c >= 0; --c) {
       floatx4_t qr = floatx4_t{0.f, 0.f, 0.f, 0.f}, qi = qr;
@@ -726,8 +739,8 @@ hipError_t launch_adj_cl_build(const AdjClBuildArgs& b, hipStream_t stream) {
   return hipGetLastError();
 }
 
-int adj_cl_wpj(AdjClPass pass, int np, int n_cl, int64_t n_jobs, int n) {
-  if (np == n) return 1;               // one tile per trajectory
+int adj_cl_wpj(AdjClPass pass, int np, int n_cl, int64_t n_jobs, int tile_bits) {
+  if (tile_bits == 0) return 1;        // one tile per trajectory
   int per_cu = 0, dev = 0, cus = 0;
   const hipError_t e = by_pass(pass, np, [&](auto k) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, cl_lds_bytes(pass, np, n_cl));
@@ -736,7 +749,7 @@ int adj_cl_wpj(AdjClPass pass, int np, int n_cl, int64_t n_jobs, int n) {
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
   const int64_t resident = (int64_t)std::max(per_cu, 1) * std::max(cus, 1);
-  return (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)1 << (n - np), resident / std::max<int64_t>(n_jobs, 1)));
+  return (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)1 << tile_bits, resident / std::max<int64_t>(n_jobs, 1)));
 }
 
 hipError_t launch_adj_cl_pass(AdjClPass pass, const AdjClArgs& a, int np, hipStream_t stream) {

@@ -290,7 +290,7 @@ ptsbe_status_t run_clusters(Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedul
       a.n_cl = wd.n_cl;
       a.n_cl_total = n_cl;
       for (int k = 0; k < 12; ++k) a.P[k] = wd.P[k];
-      a.other = wd.other;
+      a.live = wd.live;
       a.n_jobs = nj;
       for (int c = 0; c < wd.n_cl; ++c) a.pos[c] = sched.cls[(size_t)(wd.cl_off + c)].pos;
       a.U = (const float2*)U;
@@ -302,9 +302,11 @@ ptsbe_status_t run_clusters(Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedul
       ptsbe::AdjClArgs a = args_for(wd);
       a.psi_in = state(w);
       a.psi_out = state(w + 1);
+      a.fresh = wd.fresh;
       const ptsbe::AdjClPass pass = grad ? ptsbe::AdjClPass::forward : ptsbe::AdjClPass::value;
-      a.wpj = ptsbe::adj_cl_wpj(pass, wd.np, wd.n_cl, nj, n);
-      const ptsbe_status_t st = timed((double)nj * 16.0 * std::ldexp(1.0, n),
+      const int tb = __builtin_popcount(wd.live);
+      a.wpj = ptsbe::adj_cl_wpj(pass, wd.np, wd.n_cl, nj, tb);
+      const ptsbe_status_t st = timed((double)nj * 16.0 * std::ldexp(1.0, wd.np + tb),
                                       [&] { return ptsbe::launch_adj_cl_pass(pass, a, wd.np, s); });
       if (st != PTSBE_OK) return st;
     }
@@ -324,11 +326,13 @@ ptsbe_status_t run_clusters(Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedul
         const ptsbe::AdjClWin& wd = sched.wins[(size_t)w];
         ptsbe::AdjClArgs a = args_for(wd);
         a.psi_in = recompute ? ck[(size_t)w] : ck[(size_t)w + 1];
+        a.fresh = recompute ? wd.fresh : 0u;
         a.lam = lam;
         a.q = q;
+        const int tb = __builtin_popcount(wd.live);
         const ptsbe::AdjClPass pass = recompute ? ptsbe::AdjClPass::backward_recompute : ptsbe::AdjClPass::backward;
-        a.wpj = (int)std::min<int64_t>(ptsbe::adj_cl_wpj(pass, wd.np, wd.n_cl, nj, n), std::max<int64_t>(1, q_slots));
-        const ptsbe_status_t st = timed((double)nj * 24.0 * std::ldexp(1.0, n),
+        a.wpj = (int)std::min<int64_t>(ptsbe::adj_cl_wpj(pass, wd.np, wd.n_cl, nj, tb), std::max<int64_t>(1, q_slots));
+        const ptsbe_status_t st = timed((double)nj * 24.0 * std::ldexp(1.0, wd.np + tb),
                                         [&] { return ptsbe::launch_adj_cl_pass(pass, a, wd.np, s); });
         if (st != PTSBE_OK) return st;
         HIP_TRY(ptsbe::launch_adj_cl_grad(a, !recompute, sched.d_cls, sched.d_ops, n_ops, A, d_gp, d_ga, gop, s));

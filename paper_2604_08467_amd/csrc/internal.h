@@ -228,7 +228,10 @@ struct AdjCl {
 struct AdjClWin {
   int32_t cl_off, n_cl, np;
   int32_t P[12];
-  uint32_t other;                   // bit mask of the qubits outside the window
+  // Before this window only the qubits of earlier windows can be other than |0>: tiles are
+  // made over those outside it (`live`), and entries with a tile position of `fresh` set
+  // are zero on entry (as SvWin's).  The backward pass needs lambda no further than that.
+  uint32_t live, fresh;
 };
 // One schedule of a plan (host and device copies), made by the first call that needs
 // it and kept with the plan.
@@ -243,7 +246,7 @@ struct AdjClSchedule {
 struct AdjClArgs {
   int n, cl_off, n_cl, n_cl_total, wpj;
   int P[12];
-  uint32_t other;
+  uint32_t live, fresh;             // AdjClWin's; fresh of the state psi_in
   uint32_t pos[kAdjClMax];          // AdjCl::pos of the window's clusters
   int64_t n_jobs;
   const float2* U;                  // [n_jobs][n_cl_total][256] cluster matrices
@@ -275,7 +278,7 @@ struct AdjClBuildArgs {
 };
 hipError_t launch_adj_cl_build(const AdjClBuildArgs& b, hipStream_t stream);
 // Workgroups per trajectory that fill the chip once (at most the window's tiles).
-int adj_cl_wpj(AdjClPass pass, int np, int n_cl, int64_t n_jobs, int n);
+int adj_cl_wpj(AdjClPass pass, int np, int n_cl, int64_t n_jobs, int tile_bits);
 hipError_t launch_adj_cl_pass(AdjClPass pass, const AdjClArgs& a, int np, hipStream_t stream);
 // Angle derivatives of a window's rotations from its sums: gop[n_jobs][n_ops_total].
 hipError_t launch_adj_cl_grad(const AdjClArgs& a, bool unitary, const AdjCl* cls, const AdjClOp* ops, int n_ops_total,

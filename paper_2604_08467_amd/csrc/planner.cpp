@@ -970,6 +970,7 @@ void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& S) {
   const uint32_t all = p.n >= 32 ? 0xFFFFFFFFu : ((1u << p.n) - 1u);
   std::vector<int> rest(p.sv_steps.size());
   for (size_t i = 0; i < rest.size(); ++i) rest[i] = (int)i;
+  uint32_t seen = 0;                 // qubits of the windows so far
   while (!rest.empty()) {
     std::vector<int> taken, left_out, Pv, order;
     std::vector<std::pair<int, int>> groups;
@@ -983,7 +984,10 @@ void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& S) {
       w.P[k] = Pv[(size_t)k];
       win |= 1u << Pv[(size_t)k];
     }
-    w.other = all & ~win;
+    w.live = seen & ~win;
+    for (int k = 0; k < w.np; ++k)
+      if (!(seen >> w.P[k] & 1u)) w.fresh |= 1u << k;
+    seen |= win;
     size_t done = 0;                 // steps of `order` taken into clusters
     for (const auto& gr : groups) {
       for (int s0 = gr.first; s0 < gr.first + gr.second; s0 += kAdjClOps) {
@@ -1025,6 +1029,15 @@ void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& S) {
     std::sort(left_out.begin(), left_out.end());
     S.wins.push_back(w);
     rest = left_out;
+  }
+  // qubits that no window holds stay |0>, but every state is written whole
+  if (seen != all) {
+    for (AdjClWin& w : S.wins) {
+      uint32_t win = 0;
+      for (int b = 0; b < w.np; ++b) win |= 1u << w.P[b];
+      w.live = all & ~win;
+      w.fresh = 0;
+    }
   }
   S.ok = true;
 }

@@ -99,3 +99,39 @@ def test_ragged_states_from_zero():
         shots = shots.reshape(len(shots), -1)[:, 0].astype(np.uint64)
         for i, p in enumerate(jb["psis"]):
             assert Z[i] == 0.0 or np.all(np.abs(p[shots[40 * i:40 * i + 40]]) ** 2 > 1e-9 * Z[i])
+
+
+@pytest.mark.parametrize("damped", [False, True])
+@pytest.mark.parametrize("n, idle", [(11, 0), (12, 0), (13, 0), (15, 0), (14, 2)])
+def test_gradients_from_zero(n, idle, damped):
+    """Value and gradient windows on a poisoned workspace; with idle qubits at the top the
+    states are written whole.  Tolerance as for the cluster gradients: under 60 cluster
+    products of 32 FP32 terms each way, 1e-5 between the worst and the random case."""
+    import ctypes as C
+
+    import paper_2604_08467_amd as P
+    from oracle import gradients as gr
+    from paper_2604_08467_amd import _lib
+    torch, dev = torch_dev()
+    rng = np.random.default_rng(n)
+    m, layers = n - idle, 3
+    theta = rng.uniform(0, 2 * np.pi, size=2 * m * layers)
+    inner = W.hea(m, layers, theta, [W.depolarizing(0.05)] + ([W.amplitude_damping(0.1)] if damped else []))
+    gp, ga = W.rotation_spec(inner)
+    circ = W.Circuit(**{**inner.__dict__, "n_qubits": n})
+    terms = W.zz_chain_terms(m)
+    plan = P.Plan(circ, [10, n - 10], method="statevector")
+    kr, mult, _, _ = plan.sample_trajectories(3, 3)
+    w = mult / mult.sum()
+    spec = P.GradSpec(len(theta), gp, ga, terms)
+    size = C.c_size_t()
+    _lib.check(plan._lib.ptsbe_expect_workspace_size(plan._h, C.byref(spec.struct), len(kr), C.byref(size)))
+    print(f"gradient n={n} idle={idle} damped={damped}", flush=True)
+    out = plan.expect_grad(spec, to_dev(torch, dev, kr), to_dev(torch, dev, w), to_dev(torch, dev, theta),
+                           workspace=_poisoned(torch, dev, size.value))
+    want = gr.adjoint_gradient(circ, kr, w, theta, gp, ga, terms)
+    assert abs(float(out["value"].item()) - gr.value(circ, kr, w, theta, gp, ga, terms)) <= 1e-5 * len(terms)
+    assert np.linalg.norm(out["grad"].cpu().numpy() - want) <= 1e-5 * np.linalg.norm(want)
+    only = plan.expect_grad(spec, to_dev(torch, dev, kr), to_dev(torch, dev, w), to_dev(torch, dev, theta),
+                            want_grad=False, workspace=_poisoned(torch, dev, size.value))
+    assert abs(float(only["value"].item()) - gr.value(circ, kr, w, theta, gp, ga, terms)) <= 1e-5 * len(terms)
