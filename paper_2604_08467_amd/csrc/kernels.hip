@@ -675,11 +675,14 @@ __global__ void __launch_bounds__(256) ketjoin_gemv_kernel(JoinArgs a) {
 // LDS), so that crossings of up to 12 wires (a sliced last batch keeps many) fit.
 constexpr int kGemvKChunk = 512;
 
-template <int ROWS>
+// JB < 16 (few elements): a workgroup takes JB of a tile's 16 values a thread and writes
+// them straight to their places, 16 / JB workgroups a tile.  Four elements of 8 tiles, T of
+// 512 MB each, left 224 of 256 CUs idle: 1735 us, 402 us with JB = 1 (bound by reading T).
+template <int ROWS, int JB>
 __global__ void __launch_bounds__(256) ketjoin_gemv_tiled_kernel(JoinArgs a, GemvTiling g) {
   __shared__ float2 Vs[ROWS][kGemvKChunk];
   __shared__ int64_t tk[kGemvKChunk];
-  __shared__ float outs[ROWS][4096];
+  __shared__ float outs[ROWS][JB == 16 ? 4096 : 1];
   const int nk = 1 << a.lk_bits;
   const int lo_b = a.xb_bits < 12 ? a.xb_bits : 12;
   const int lo_k = a.lk_bits < 12 ? a.lk_bits : 12;
@@ -699,17 +702,19 @@ __global__ void __launch_bounds__(256) ketjoin_gemv_tiled_kernel(JoinArgs a, Gem
   int64_t obr[ROWS];
 #pragma unroll
   for (int r = 0; r < ROWS; ++r) obr[r] = tab(a.tab, a.jd.ob_lo, a.jd.ob_hi, lo_b, (uint32_t)r);
-  for (int64_t bid = blockIdx.x; bid < a.n_elems * tiles; bid += gridDim.x) {
-    const int64_t e = bid >> g.n_hi;
-    const int64_t tile = bid & (tiles - 1);
+  constexpr int PARTS = 16 / JB;
+  for (int64_t bid = blockIdx.x; bid < a.n_elems * tiles * PARTS; bid += gridDim.x) {
+    const int64_t e = bid / PARTS >> g.n_hi;
+    const int64_t tile = bid / PARTS & (tiles - 1);
+    const int j0 = (int)(bid % PARTS) * JB;
     int64_t tbase = 0, obase = 0;
     for (int h = 0; h < g.n_hi; ++h)
       if ((tile >> h) & 1) { tbase += g.t_hi[h]; obase += g.o_hi[h]; }
     const int32_t ti = a.elem_traj[e] - a.traj_base;
     const float2* T = a.T + (int64_t)(a.tslot ? a.tslot[ti] : ti) * a.t_stride + tbase + t_lo;
-    float2 acc[16][ROWS];
+    float2 acc[JB][ROWS];
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
+    for (int j = 0; j < JB; ++j)
 #pragma unroll
       for (int r = 0; r < ROWS; ++r) acc[j][r] = make_float2(0.f, 0.f);
     for (int k0 = 0; k0 < nk; k0 += kGemvKChunk) {
@@ -722,17 +727,18 @@ __global__ void __launch_bounds__(256) ketjoin_gemv_tiled_kernel(JoinArgs a, Gem
       }
       for (int k = tid; k < kn; k += 256) tk[k] = tab(a.tab, a.jd.tk_lo, a.jd.tk_hi, lo_k, (uint32_t)(k0 + k));
       __syncthreads();
+#pragma unroll (JB == 16 ? 1 : 16 / JB)
       for (int k = 0; k < kn; ++k) {
         const float2* Tk = T + tk[k];
         float2 v[ROWS];
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) v[r] = Vs[r][k];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+        for (int j = 0; j < JB; ++j) {
           int64_t hj = 0;
 #pragma unroll
           for (int s = 0; s < 4; ++s)
-            if ((j >> s) & 1) hj += g.t_off[8 + s];
+            if (((j0 + j) >> s) & 1) hj += g.t_off[8 + s];
           const float2 t = Tk[hj];
 #pragma unroll
           for (int r = 0; r < ROWS; ++r) acc[j][r] = cfma(v[r], t, acc[j][r]);
@@ -740,28 +746,32 @@ __global__ void __launch_bounds__(256) ketjoin_gemv_tiled_kernel(JoinArgs a, Gem
       }
     }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
+    for (int j = 0; j < JB; ++j) {
       int li = l_lo;
       int64_t orj = or_lo;
 #pragma unroll
       for (int s = 0; s < 4; ++s)
-        if ((j >> s) & 1) { li += 1 << g.w_of[8 + s]; orj += g.o_read[8 + s]; }
+        if (((j0 + j) >> s) & 1) { li += 1 << g.w_of[8 + s]; orj += g.o_read[8 + s]; }
 #pragma unroll
       for (int r = 0; r < ROWS; ++r) {
-        outs[r][li] = acc[j][r].x * acc[j][r].x + acc[j][r].y * acc[j][r].y;
+        const float pi = acc[j][r].x * acc[j][r].x + acc[j][r].y * acc[j][r].y;
+        if constexpr (JB == 16) outs[r][li] = pi;
+        else if (a.pop) a.pop[e * nout + obase + orj + obr[r]] = pi;
         if (a.amp) a.amp[e * nout + obase + orj + obr[r]] = acc[j][r];
       }
     }
-    __syncthreads();
-    if (a.pop) {
+    if constexpr (JB == 16) {
+      __syncthreads();
+      if (a.pop) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        int64_t oj = w_lo;
+        for (int j = 0; j < 16; ++j) {
+          int64_t oj = w_lo;
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-          if ((j >> s) & 1) oj += g.o_off[8 + s];
+          for (int s = 0; s < 4; ++s)
+            if ((j >> s) & 1) oj += g.o_off[8 + s];
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) a.pop[e * nout + obase + oj + obr[r]] = outs[r][tid + 256 * j];
+          for (int r = 0; r < ROWS; ++r) a.pop[e * nout + obase + oj + obr[r]] = outs[r][tid + 256 * j];
+        }
       }
     }
   }
@@ -2253,9 +2263,19 @@ hipError_t launch_ketjoin_gemv_tiled(const JoinArgs& a, const GemvTiling& g, hip
   if (a.n_elems <= 0) return hipSuccess;
   if (a.doubled || a.xb_bits > 1 || a.lk_bits > 12 || a.xT_bits < 12 || g.n_hi != a.xT_bits - 12 || g.n_hi > 32)
     return hipErrorInvalidValue;
-  const dim3 grid(grid_blocks(a.n_elems << g.n_hi));
-  if (a.xb_bits == 0) hipLaunchKernelGGL(ketjoin_gemv_tiled_kernel<1>, grid, dim3(256), 0, stream, a, g);
-  else hipLaunchKernelGGL(ketjoin_gemv_tiled_kernel<2>, grid, dim3(256), 0, stream, a, g);
+  // whole tiles a workgroup from four workgroups a CU on (32 for 4 elements of 8 tiles took
+  // 1735 us, 512 of a sixteenth 402 us), else a quarter or a sixteenth
+  const int64_t tiles = a.n_elems << g.n_hi;
+  auto go = [&](auto kernel, int parts) {
+    hipLaunchKernelGGL(kernel, dim3(grid_blocks(tiles * parts)), dim3(256), 0, stream, a, g);
+  };
+  if (tiles >= 1024) {
+    if (a.xb_bits == 0) go(ketjoin_gemv_tiled_kernel<1, 16>, 1); else go(ketjoin_gemv_tiled_kernel<2, 16>, 1);
+  } else if (tiles >= 256) {
+    if (a.xb_bits == 0) go(ketjoin_gemv_tiled_kernel<1, 4>, 4); else go(ketjoin_gemv_tiled_kernel<2, 4>, 4);
+  } else {
+    if (a.xb_bits == 0) go(ketjoin_gemv_tiled_kernel<1, 1>, 16); else go(ketjoin_gemv_tiled_kernel<2, 1>, 16);
+  }
   return hipGetLastError();
 }
 
