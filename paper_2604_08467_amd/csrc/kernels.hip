@@ -191,7 +191,13 @@ __device__ inline uint32_t init_offset(const InitArgs& in, uint32_t m, const uin
 constexpr int kVmGateEntries = 512;
 constexpr int kVmMaxJobs = 64;        // jobs per workgroup (one wavefront assigns the trajectory slots)
 
-__global__ void __launch_bounds__(512) part_vm_kernel(const AbsorbStep* __restrict__ steps, int n_steps,
+// LS (one job a workgroup): the steps of a chunk are copied to LDS with their gates, so that
+// a step costs one round of LDS latency; as scalar loads its description, 424 bytes that no
+// cache holds for long, took two rounds to L2 (a step of 504: 1.67 us, 1.2 us now).
+constexpr int kVmLdsSteps = 16;
+
+template <bool LS>
+__global__ void __launch_bounds__(512, 4) part_vm_kernel(const AbsorbStep* __restrict__ steps, int n_steps,
                                                       int buf_elems, int J, GateCtx g, int64_t n_jobs,
                                                       const int32_t* __restrict__ job_traj, int32_t traj_base,
                                                       const uint64_t* __restrict__ job_prefix, int NW,
@@ -209,11 +215,15 @@ __global__ void __launch_bounds__(512) part_vm_kernel(const AbsorbStep* __restri
   float2* Gm = lds + 2 * (size_t)J * buf_elems;         // [chunk][slots][16] gates of a chunk of steps
   int4* stab = reinterpret_cast<int4*>(Gm + kVmGateEntries);   // [n_steps] gate | conj << 31, gperm
   uint64_t* pw = reinterpret_cast<uint64_t*>(stab + n_steps);  // [J][NW] prefixes
+  AbsorbStep* lsteps = reinterpret_cast<AbsorbStep*>(pw + (size_t)J * NW);   // [kVmLdsSteps], LS only
   const int tid = threadIdx.x, nt = blockDim.x;
-  // the step list's gate indices, once per workgroup (visible after the first barrier)
+  // the step list's gate indices and forms (legs, hyper or sliced, kept indices), once per
+  // workgroup (visible after the first barrier)
   for (int s = tid; s < n_steps; s += nt)
     stab[s] = make_int4(steps[s].gate | (steps[s].conj ? (int)0x80000000 : 0), (int)steps[s].gperm[0],
-                        (int)steps[s].gperm[1], 0);
+                        (int)steps[s].gperm[1],
+                        (steps[s].nK * 8 + steps[s].nN) | (steps[s].nH == 0 && steps[s].nS == 0 ? 64 : 0) |
+                            (steps[s].rC - steps[s].nN) << 8);
   const int64_t n_groups = (n_jobs + J - 1) / J;
   for (int64_t grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
     const int64_t job0 = grp * J;
@@ -233,12 +243,19 @@ __global__ void __launch_bounds__(512) part_vm_kernel(const AbsorbStep* __restri
     __syncthreads();
     const int n_slots = n_slots_s;
     const int per_step = 16 * n_slots;
-    const int chunk = kVmGateEntries / per_step > 1 ? kVmGateEntries / per_step : 1;
+    const int fit = LS ? kVmLdsSteps : kVmGateEntries / per_step;
+    const int chunk = fit > 1 ? fit : 1;
     // gates of the steps [c0, c1) in LDS, every (step, slot, entry) of the chunk
     // spread over all threads, two loads per thread in flight together
     // (unconditional, from a clamped valid entry), the bra conjugation applied at
     // the store
     auto stage = [&](int c0, int c1) {
+      if (LS) {
+        static_assert(sizeof(AbsorbStep) % 8 == 0, "steps are copied as 8-byte words");
+        const uint64_t* src = reinterpret_cast<const uint64_t*>(steps + c0);
+        for (int i = tid; i < (c1 - c0) * (int)(sizeof(AbsorbStep) / 8); i += nt)
+          reinterpret_cast<uint64_t*>(lsteps)[i] = src[i];
+      }
       const int E = (c1 - c0) * per_step;
       for (int e0 = 0; e0 < E; e0 += 2 * nt) {
         float2 v[2];
@@ -290,7 +307,6 @@ __global__ void __launch_bounds__(512) part_vm_kernel(const AbsorbStep* __restri
     int cs = 0;
     if (n_steps > 0) stage(0, n_steps < chunk ? n_steps : chunk);
     for (int s = 0; s < n_steps; ++s) {
-      const AbsorbStep& st = steps[s];
       if (s == cs + chunk) {
         cs = s;
         __syncthreads();   // every thread is done with the previous chunk's gates
@@ -298,15 +314,18 @@ __global__ void __launch_bounds__(512) part_vm_kernel(const AbsorbStep* __restri
       }
       const float2* G = Gm + (size_t)(s - cs) * per_step;
       __syncthreads();     // gates visible; previous step's C complete
-      const int lnm = st.rC - st.nN;
+      const AbsorbStep& st = LS ? lsteps[s - cs] : steps[s];
+      const int form = __builtin_amdgcn_readfirstlane(stab[s].w);
+      const int lnm = form >> 8;
+      const bool plain = form & 64;
       if (direct && s == n_steps - 1) {
         // the last step writes the output in HBM (its rank exceeds the LDS buffers)
         float2* Co = out + job0 * ((int64_t)1 << out_rank);
         const int64_t cst = (int64_t)1 << out_rank;
-        switch (st.nK * 8 + st.nN) {
+        switch (form & 63) {
 #define VM_OUT(K, N)                                                                       \
           case K * 8 + N:                                                                  \
-            if (st.nH == 0 && st.nS == 0)                                                  \
+            if (plain)                                                  \
               vm_step<K, N, true>(st, nj, lnm, buf_elems, bufA, Co, cst, G, slot, pw, NW); \
             else                                                                           \
               vm_step<K, N, false>(st, nj, lnm, buf_elems, bufA, Co, cst, G, slot, pw, NW); \
@@ -317,10 +336,10 @@ __global__ void __launch_bounds__(512) part_vm_kernel(const AbsorbStep* __restri
         }
         continue;
       }
-      switch (st.nK * 8 + st.nN) {    // uniform: every thread takes the same case
+      switch (form & 63) {    // uniform: every thread takes the same case
 #define VM_CASE(K, N)                                                                     \
         case K * 8 + N:                                                                   \
-          if (st.nH == 0 && st.nS == 0)                                                   \
+          if (plain)                                                   \
             vm_step<K, N, true>(st, nj, lnm, buf_elems, bufA, bufC, buf_elems, G, slot, pw, NW);  \
           else                                                                            \
             vm_step<K, N, false>(st, nj, lnm, buf_elems, bufA, bufC, buf_elems, G, slot, pw, NW); \
@@ -2149,9 +2168,14 @@ hipError_t launch_part_vm(const AbsorbStep* d_steps, int n_steps, int peak, Gate
   const int stride = J > 1 ? buf + 1 : buf;
   const size_t shmem = (size_t)(2 * J * stride + kVmGateEntries) * sizeof(float2) + (size_t)n_steps * sizeof(int4) +
                        (size_t)J * NW * sizeof(uint64_t);
-  hipLaunchKernelGGL(part_vm_kernel, dim3(grid_blocks((n_jobs + J - 1) / J)), dim3(threads), shmem, stream,
-                     d_steps, n_steps, stride, J, g, n_jobs, job_traj, traj_base, job_prefix, NW, init, out, out_rank,
-                     direct);
+  const dim3 grid(grid_blocks((n_jobs + J - 1) / J));
+  if (J == 1)
+    hipLaunchKernelGGL(part_vm_kernel<true>, grid, dim3(threads), shmem + kVmLdsSteps * sizeof(AbsorbStep), stream,
+                       d_steps, n_steps, stride, J, g, n_jobs, job_traj, traj_base, job_prefix, NW, init, out, out_rank,
+                       direct);
+  else
+    hipLaunchKernelGGL(part_vm_kernel<false>, grid, dim3(threads), shmem, stream, d_steps, n_steps, stride, J, g, n_jobs,
+                       job_traj, traj_base, job_prefix, NW, init, out, out_rank, direct);
   return hipGetLastError();
 }
 
