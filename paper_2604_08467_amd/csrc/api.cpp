@@ -374,7 +374,11 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
       }
     }
     if (sg.fused) {   // a run of in-place steps, one tile pass, in place
-      HIP_TRY(ptsbe::launch_fused(sg, p.d_fused, g, cur_n, cur_traj, traj_base, job_prefix, p.NW, A, s));
+      if (sg.win >= 0)
+        HIP_TRY(ptsbe::launch_part_window(p.part_wins[(size_t)sg.win], p.d_part_ops, g.merged, p.G, cur_n, cur_traj,
+                                          traj_base, A, sg.r, s));
+      else
+        HIP_TRY(ptsbe::launch_fused(sg, p.d_fused, g, cur_n, cur_traj, traj_base, job_prefix, p.NW, A, s));
       if (p.profile) p.fused_bytes += (double)cur_n * 16.0 * std::ldexp(1.0, sg.r);
       continue;
     }
@@ -1236,8 +1240,10 @@ ptsbe_status_t ptsbe_plan(const ptsbe_circuit_t* c, const ptsbe_plan_opts_t* o, 
     for (int i = 0; i < d * d; ++i) dg[g].def[i] = make_float2((float)m[i].real(), (float)m[i].imag());
   }
   for (auto& bp : p->batches)
-    for (ptsbe::PartPlan* pp : {&bp.left, &bp.right, &bp.left_resume})
+    for (ptsbe::PartPlan* pp : {&bp.left, &bp.right, &bp.left_resume}) {
       ptsbe::build_segments(pp->steps, pp->segs, p->fused);
+      ptsbe::build_part_windows(*p, *pp);
+    }
   if (p->method == PTSBE_METHOD_STATEVECTOR) {
     ptsbe::build_sv_schedule(*p);
     ptsbe::build_sv_ops(*p);
@@ -1292,6 +1298,11 @@ ptsbe_status_t ptsbe_plan(const ptsbe_circuit_t* c, const ptsbe_plan_opts_t* o, 
   if (!p->fused.empty()) {
     HIP_TRY(hipMalloc(&p->d_fused, p->fused.size() * sizeof(ptsbe::FusedStep)));
     HIP_TRY(hipMemcpy(p->d_fused, p->fused.data(), p->fused.size() * sizeof(ptsbe::FusedStep),
+                      hipMemcpyHostToDevice));
+  }
+  if (!p->part_ops.empty()) {
+    HIP_TRY(hipMalloc(&p->d_part_ops, p->part_ops.size() * sizeof(ptsbe::SvOp)));
+    HIP_TRY(hipMemcpy(p->d_part_ops, p->part_ops.data(), p->part_ops.size() * sizeof(ptsbe::SvOp),
                       hipMemcpyHostToDevice));
   }
   if (p->method == PTSBE_METHOD_STATEVECTOR) {
@@ -1361,6 +1372,7 @@ void ptsbe_plan_destroy(ptsbe_plan_t plan) {
   if (p->d_tables) (void)hipFree(p->d_tables);
   if (p->d_sv_steps) (void)hipFree(p->d_sv_steps);
   if (p->d_fused) (void)hipFree(p->d_fused);
+  if (p->d_part_ops) (void)hipFree(p->d_part_ops);
   for (auto* w : p->d_rg_win)
     if (w) (void)hipFree(w);
   for (auto* c : p->d_sv_cl)

@@ -306,6 +306,7 @@ struct Segment {
   int np = 0, r = 0;
   int P[kFuseMax] = {0};
   int64_t fused_off = 0;            // index of the first FusedStep on the device
+  int win = -1;                     // fused: Plan::part_wins entry that says the same, or -1
 };
 bool build_segments(const std::vector<AbsorbStep>& steps, std::vector<Segment>& segs,
                     std::vector<FusedStep>& fused);
@@ -418,6 +419,9 @@ struct Plan {
   std::vector<SvWin> sv_wins[3];
   std::vector<SvOp> sv_ops[3];
   SvOp* d_sv_ops[3] = {nullptr, nullptr, nullptr};
+  std::vector<SvWin> part_wins;     // fused segments of the network parts in compact form
+  std::vector<SvOp> part_ops;
+  SvOp* d_part_ops = nullptr;
   bool sv_covers[3] = {false, false, false};      // every qubit is in some window of the set
   // the same windows with every step a plain op (ragged sets), on the device
   std::vector<SvWin> sv_wins_plain[3];
@@ -475,6 +479,9 @@ void build_sv_schedule(Plan& p);
 // Compact ops of every statevector window set (p.sv_wins, p.sv_ops), from the
 // fused steps and clusters that build_sv_schedule made.
 void build_sv_ops(Plan& p);
+// The fused segments of a part that the window kernel can take: runs of one- and two-qubit
+// gates on positions with 0 among them.
+void build_part_windows(Plan& p, PartPlan& pp);
 // Windows of at most wmax qubits and max_ops steps for the adjoint pass: the
 // statevector schedule's steps packed as in build_sv_schedule, in circuit order,
 // every step a plain op.
@@ -767,6 +774,10 @@ hipError_t launch_state_init(float2* psi, int64_t n_jobs, int n, hipStream_t str
 hipError_t launch_sv_window(const SvWin& w, const SvOp* d_ops, const float2* merged, int G, const float2* Ucl,
                             int n_cl_total, int64_t n_jobs, int32_t traj_base, float2* psi, int n, int precision,
                             bool grow, hipStream_t stream);
+// The fused segment w of a network part in place over n_jobs tensors A of rank r: window
+// kernel without clusters, gates of trajectory job_traj[job] (null: traj_base + job).
+hipError_t launch_part_window(const SvWin& w, const SvOp* d_ops, const float2* merged, int G, int64_t n_jobs,
+                              const int32_t* job_traj, int32_t traj_base, float2* A, int r, hipStream_t stream);
 // LDS bytes the window kernel needs for a window (0 if it cannot take it).
 size_t sv_window_lds_bytes(const SvWin& w);
 hipError_t launch_copy(const float2* src, float2* dst, int64_t n, hipStream_t stream);

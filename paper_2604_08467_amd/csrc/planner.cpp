@@ -1132,7 +1132,53 @@ void group_sv_ops(const std::vector<SvOp>& in, int np, std::vector<SvOp>& out) {
   }
   close();
 }
+
+// A fused step as a window op of the given slot, or false if it is not a one- or two-qubit
+// gate on its own positions.
+bool plain_op(const FusedStep& f, int slot, SvOp& op) {
+  if (f.nH != 0 || f.nS != 0 || f.nK != f.nN || f.nK < 1 || f.nK > 2 || f.noff[1] != f.koff[1]) return false;
+  if (f.nK == 2 && (f.noff[2] != f.koff[2] || f.noff[3] != f.koff[3])) return false;
+  op.kind = f.nK == 1 ? kSvOpGate1 : kSvOpGate2;
+  op.p0 = (int8_t)f.kloc[0];
+  op.p1 = (int8_t)(f.nK == 2 ? f.kloc[1] : 0);
+  op.conj = (int8_t)f.conj;
+  op.gate = f.gate;
+  op.slot = slot;
+  const int d = 1 << f.nK;
+  for (int n = 0; n < d; ++n)
+    for (int k = 0; k < d; ++k) op.idx[n * d + k] = (int8_t)(f.nB[n] + f.kB[k]);
+  return true;
+}
 }  // namespace
+
+void build_part_windows(Plan& p, PartPlan& pp) {
+  for (Segment& sg : pp.segs) {
+    sg.win = -1;
+    if (!sg.fused || sg.np != kFuseMax || sg.P[0] != 0 || sg.r > 30) continue;
+    SvWin w{};
+    w.op_off = (int32_t)p.part_ops.size();
+    w.np = sg.np;
+    uint32_t win = 0;
+    for (int k = 0; k < kFuseMax; ++k) {
+      w.P[k] = sg.P[k];
+      if (k < sg.np) win |= 1u << sg.P[k];
+    }
+    w.other = w.live = ((1u << sg.r) - 1u) & ~win;
+    std::vector<SvOp> wo;
+    bool ok = true;
+    for (int s = 0; s < sg.count && ok; ++s) {
+      SvOp op{};
+      ok = plain_op(p.fused[(size_t)(sg.fused_off + s)], w.n_plain, op);
+      w.n_plain += ok;
+      wo.push_back(op);
+    }
+    if (!ok || sv_window_lds_bytes(w) == 0) continue;
+    group_sv_ops(wo, sg.np, p.part_ops);
+    w.n_ops = (int32_t)p.part_ops.size() - w.op_off;
+    sg.win = (int)p.part_wins.size();
+    p.part_wins.push_back(w);
+  }
+}
 
 void build_sv_ops(Plan& p) {
   const uint32_t all = p.n >= 32 ? 0xFFFFFFFFu : ((1u << p.n) - 1u);
@@ -1167,19 +1213,9 @@ void build_sv_ops(Plan& p) {
       std::vector<SvOp> wo;
       for (int s = 0; s < sg.count && pok; ++s) {
         const FusedStep& f = p.fused[(size_t)(sg.fused_off + s)];
-        const bool plain = f.nH == 0 && f.nS == 0 && f.nK == f.nN && f.nK >= 1 && f.nK <= 2 &&
-                           f.noff[1] == f.koff[1] && (f.nK == 1 || (f.noff[2] == f.koff[2] && f.noff[3] == f.koff[3]));
-        if (!plain) { pok = false; break; }
         SvOp op{};
-        op.kind = f.nK == 1 ? kSvOpGate1 : kSvOpGate2;
-        op.p0 = (int8_t)f.kloc[0];
-        op.p1 = (int8_t)(f.nK == 2 ? f.kloc[1] : 0);
-        op.conj = (int8_t)f.conj;
-        op.gate = f.gate;
-        op.slot = w.n_plain++;
-        const int d = 1 << f.nK;
-        for (int n = 0; n < d; ++n)
-          for (int k = 0; k < d; ++k) op.idx[n * d + k] = (int8_t)(f.nB[n] + f.kB[k]);
+        if (!plain_op(f, w.n_plain, op)) { pok = false; break; }
+        ++w.n_plain;
         wo.push_back(op);
       }
       if (!pok) break;
@@ -1221,18 +1257,8 @@ void build_sv_ops(Plan& p) {
           cl_hi = std::max(cl_hi, f.cl_id);
           s += f.cl_len;
         } else {
-          const bool plain = f.nH == 0 && f.nS == 0 && f.nK == f.nN && f.nK >= 1 && f.nK <= 2 &&
-                             f.noff[1] == f.koff[1] && (f.nK == 1 || (f.noff[2] == f.koff[2] && f.noff[3] == f.koff[3]));
-          if (!plain) { ok = false; break; }
-          op.kind = f.nK == 1 ? kSvOpGate1 : kSvOpGate2;
-          op.p0 = (int8_t)f.kloc[0];
-          op.p1 = (int8_t)(f.nK == 2 ? f.kloc[1] : 0);
-          op.conj = (int8_t)f.conj;
-          op.gate = f.gate;
-          op.slot = w.n_plain++;
-          const int d = 1 << f.nK;
-          for (int n = 0; n < d; ++n)
-            for (int k = 0; k < d; ++k) op.idx[n * d + k] = (int8_t)(f.nB[n] + f.kB[k]);
+          if (!plain_op(f, w.n_plain, op)) { ok = false; break; }
+          ++w.n_plain;
           ++s;
         }
         wo.push_back(op);

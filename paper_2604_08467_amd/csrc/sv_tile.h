@@ -41,6 +41,7 @@ struct SvwArgs {
   int P[kFuseMax];
   int64_t n_jobs;
   int32_t traj_base;
+  const int32_t* job_traj;   // trajectory of a job; null: traj_base + job
 };
 
 typedef __bf16 svw_bf16x8 __attribute__((ext_vector_type(8)));
@@ -544,10 +545,13 @@ __device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __res
 #pragma unroll
     for (int i = 0; i < PPT; ++i) lds_put_pair(tile4, pt2, i, v[i]);
   };
+  auto traj_of = [&](int64_t job) -> int64_t {
+    return a.job_traj ? (int64_t)__builtin_amdgcn_readfirstlane(a.job_traj[job]) : a.traj_base + job;
+  };
   auto stage = [&](int64_t job) {
     for (int i = tid; i < 256 * a.n_cl; i += kSvwThreads)
       Us[i] = Ucl[((int64_t)job * a.n_cl_total + a.cl_first) * 256 + i];
-    stage_gates(ops, a.n_ops, merged + (a.traj_base + job) * a.G * 16, Gs, forms);
+    stage_gates(ops, a.n_ops, merged + traj_of(job) * a.G * 16, Gs, forms);
   };
   load(b0);
   stage(b0 >> tb);
@@ -591,7 +595,8 @@ __device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __res
     // operations finish in order, so a wait for the loads after the stores would wait for
     // them too
     if (AHEAD) keep();
-    if (more && (bid + 1) >> tb != bid >> tb) stage((bid + 1) >> tb);   // the next trajectory's gates
+    // the next trajectory's gates
+    if (more && (bid + 1) >> tb != bid >> tb && traj_of((bid + 1) >> tb) != traj_of(bid >> tb)) stage((bid + 1) >> tb);
   }
   __syncthreads();
 }
