@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(kRgThreads, 4) rg_window_kernel(RgWave w, RgLe
     const RgPiece& pc = w.pieces[lv.piece[e]];
     const SvWin& sw = pc.swin[lv.level];
     const bool grow = uni(pc.grow) != 0;
-    SvwArgs a;
+    SvwArgs a{};
     a.n = uni(pc.n);
     a.n_ops = uni(sw.n_ops);
     a.n_plain = uni(sw.n_plain);
