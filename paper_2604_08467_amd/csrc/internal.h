@@ -117,17 +117,21 @@ struct ClusterDesc {
 // of gates on at most np - 8 positions follows a group record: 256 threads take the
 // tile's 2^np amplitudes over those positions into registers, 2^(np - 8) each, apply the
 // group's gates there in order, and put them back.
-enum { kSvOpGate1 = 1, kSvOpGate2 = 2, kSvOpCluster = 3, kSvOpGroup = 4 };
+// kSvOpHyper (network tensors): a gate on one position whose 2 x 2 matrix is picked by the
+// bits of one or two other positions.
+enum { kSvOpGate1 = 1, kSvOpGate2 = 2, kSvOpCluster = 3, kSvOpGroup = 4, kSvOpHyper = 5 };
 struct SvOp {
   int8_t kind;
   int8_t p0, p1;            // gate: tile positions of local index bits 0 and 1; group: p0 gates follow
   int8_t conj;              // gate: use the complex conjugate of the merged matrix
   int8_t cpos[4];           // cluster: tile position of cluster-local bit i; group: of register bit i;
-                            // gate: cpos[0] = register bit (one qubit) or bit pair (svg_pair)
+                            // gate: cpos[0] = register bit (one qubit) or bit pair (svg_pair);
+                            // hyper: cpos[1], cpos[2] = picking bits, tile position or 32 + position
   int32_t gate;             // gate: index into the trajectory's merged gates
   int32_t slot;             // gate: staged matrix slot; cluster: index within the window;
                             // group: gate and slot hold the tile positions of thread bits 0 .. 7, a byte each
   int8_t idx[16];           // gate: local entry (n, k), n * d + k, is merged entry idx[n * d + k];
+                            // hyper: entry (n, k) for picking bits h is idx[4 * h + 2 * n + k];
                             // cluster: idx[0 .. np - 5] the tile positions of its column's bits
 };
 // Number of the register bit pair i < j < 4 of a two-qubit gate in a group.
@@ -145,6 +149,7 @@ struct SvWin {
   // stay zero), `fresh` the tile positions that no earlier window held (entries with any
   // of these set are zero on entry; all of them in the first window).
   uint32_t live, fresh;
+  int32_t n_hyper;          // gates of kind kSvOpHyper (network tensors)
 };
 
 struct DeviceGate;
@@ -480,7 +485,7 @@ void build_sv_schedule(Plan& p);
 // fused steps and clusters that build_sv_schedule made.
 void build_sv_ops(Plan& p);
 // The fused segments of a part that the window kernel can take: runs of one- and two-qubit
-// gates on positions with 0 among them.
+// gates (and one-qubit gates picked by up to two hyper legs) on positions with 0 among them.
 void build_part_windows(Plan& p, PartPlan& pp);
 // Windows of at most wmax qubits and max_ops steps for the adjoint pass: the
 // statevector schedule's steps packed as in build_sv_schedule, in circuit order,

@@ -1083,13 +1083,22 @@ void group_sv_ops(const std::vector<SvOp>& in, int np, std::vector<SvOp>& out) {
   };
   std::vector<SvOp> gates;
   std::vector<int> order;            // positions of the open group, register bit order
+  // tile positions that pick gates of these ops: never register bits
+  auto picks_of = [](const std::vector<SvOp>& gs) {
+    std::set<int> h;
+    for (const SvOp& g : gs)
+      for (int i = 1; i <= 2 && g.kind == kSvOpHyper; ++i)
+        if (g.cpos[i] < 32) h.insert(g.cpos[i]);
+    return h;
+  };
   auto close = [&]() {
     if (gates.empty()) return;
     auto in_order = [&](int p) { return std::find(order.begin(), order.end(), p) != order.end(); };
     // unused register bits take the highest positions left: those of low index spread the
     // lanes of a quarter wavefront over the LDS banks
+    const std::set<int> picks = picks_of(gates);
     for (int p = np - 1; (int)order.size() < cap; --p)
-      if (!in_order(p)) order.push_back(p);
+      if (!in_order(p) && !picks.count(p)) order.push_back(p);
     const std::vector<int> lanes = spread_positions(order, np);
     SvOp h{};
     h.kind = kSvOpGroup;
@@ -1102,7 +1111,7 @@ void group_sv_ops(const std::vector<SvOp>& in, int np, std::vector<SvOp>& out) {
     out.push_back(h);
     auto at = [&](int p) { return (int)(std::find(order.begin(), order.end(), p) - order.begin()); };
     for (SvOp& g : gates) {
-      g.cpos[0] = (int8_t)(g.kind == kSvOpGate1 ? at(g.p0) : svg_pair(at(g.p0), at(g.p1)));
+      g.cpos[0] = (int8_t)(g.kind == kSvOpGate2 ? svg_pair(at(g.p0), at(g.p1)) : at(g.p0));
       out.push_back(g);
     }
     gates.clear();
@@ -1122,7 +1131,10 @@ void group_sv_ops(const std::vector<SvOp>& in, int np, std::vector<SvOp>& out) {
       for (int p : {(int)op.p0, op.kind == kSvOpGate2 ? (int)op.p1 : (int)op.p0})
         if (std::find(q.begin(), q.end(), p) == q.end()) q.push_back(p);
       gates.push_back(op);
-      if ((int)q.size() <= cap && (int)gates.size() <= 100 && order_of(q, gates, found)) {
+      const std::set<int> picks = picks_of(gates);
+      bool fits = (int)q.size() <= cap && (int)gates.size() <= 100 && (int)picks.size() <= np - cap;
+      for (int p : q) fits = fits && !picks.count(p);
+      if (fits && order_of(q, gates, found)) {
         order = found;
         break;
       }
@@ -1149,6 +1161,28 @@ bool plain_op(const FusedStep& f, int slot, SvOp& op) {
     for (int k = 0; k < d; ++k) op.idx[n * d + k] = (int8_t)(f.nB[n] + f.kB[k]);
   return true;
 }
+
+// A fused step on one position whose matrix is picked by one or two hyper legs, likewise.
+bool hyper_op(const FusedStep& f, int slot, SvOp& op) {
+  if (f.nH < 1 || f.nH > 2 || f.nS != 0 || f.nK != 1 || f.nN != 1 || f.noff[1] != f.koff[1]) return false;
+  op.kind = kSvOpHyper;
+  op.p0 = (int8_t)f.kloc[0];
+  op.conj = (int8_t)f.conj;
+  op.gate = f.gate;
+  op.slot = slot;
+  for (int i = 0; i < 2; ++i) {
+    const int h = i < f.nH ? i : 0;          // one leg: both picking bits are its own
+    op.cpos[1 + i] = (int8_t)(f.h_inP[h] ? f.h_pos[h] : 32 + f.h_pos[h]);
+  }
+  for (int h = 0; h < 4; ++h)
+    for (int n = 0; n < 2; ++n)
+      for (int k = 0; k < 2; ++k) {
+        int at = f.nB[n] + f.kB[k];
+        for (int i = 0; i < f.nH; ++i) at += (h >> i & 1) * f.hw[i];
+        op.idx[4 * h + 2 * n + k] = (int8_t)at;
+      }
+  return true;
+}
 }  // namespace
 
 void build_part_windows(Plan& p, PartPlan& pp) {
@@ -1168,7 +1202,12 @@ void build_part_windows(Plan& p, PartPlan& pp) {
     bool ok = true;
     for (int s = 0; s < sg.count && ok; ++s) {
       SvOp op{};
-      ok = plain_op(p.fused[(size_t)(sg.fused_off + s)], w.n_plain, op);
+      const FusedStep& f = p.fused[(size_t)(sg.fused_off + s)];
+      ok = plain_op(f, w.n_plain, op);
+      if (!ok && hyper_op(f, w.n_plain, op)) {
+        ok = true;
+        ++w.n_hyper;
+      }
       w.n_plain += ok;
       wo.push_back(op);
     }

@@ -28,6 +28,7 @@ constexpr int kSvwThreads = 256;
 __host__ __device__ inline uint32_t swz(uint32_t l) { return l ^ ((l >> 4) & 15u); }
 
 constexpr int kSvwPlain = -1;   // "precision" of a window without clusters
+constexpr int kSvwHyper = -2;   // and of one with gates picked by hyper legs
 
 __device__ inline uint32_t ins0(uint32_t m, int p) {   // zero bit inserted at position p
   const uint32_t lo = (1u << p) - 1u;
@@ -363,16 +364,37 @@ __device__ __forceinline__ void reg_gate2(float2 (&x)[1 << LB], const float2* G,
   }
 }
 
+// A gate on register bit B whose matrix g ([n][k]) is the thread's own.
+template <int LB, int B>
+__device__ __forceinline__ void reg_hyper(float2 (&x)[1 << LB], const float2 (&g)[4]) {
+  const float2 zero = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int l = 0; l < (1 << LB); ++l)
+    if (!(l >> B & 1)) {
+      const float2 a0 = x[l], a1 = x[l | 1 << B];
+      x[l] = cfma(a1, g[1], cfma(a0, g[0], zero));
+      x[l | 1 << B] = cfma(a1, g[3], cfma(a0, g[2], zero));
+    }
+}
+
 // The n gates after a group record (h: its first four dwords) on the tile: 2^(NP - 8)
 // amplitudes a thread in registers.  One LDS pass and one barrier for all of them: a pass
 // per gate cost 0.5 ms on a 12.9 GB set of states (25 qubits x 48), three times its own
 // arithmetic, and a window of 14 gates 12.1 ms where it takes 8.3 now (5.3 ms to read and
 // write the states).  group_sv_ops has which gates share a group.
-template <int NP>
+// HYPER: some gates' matrices are picked by bits of the thread's part of the tile position
+// or of the tile's own position `base`; such bits are never register bits, so that a thread
+// has one matrix for all its amplitudes.
+template <int NP, bool HYPER>
 __device__ __forceinline__ void apply_group(const uint4 h, const uint4* __restrict__ ops, int n, float2* tile,
-                                   const float2* Gs, const uint32_t* forms) {
+                                   const float2* Gs, const uint32_t* forms, uint32_t base) {
   constexpr int LB = NP - 8;
   const uint32_t tid = threadIdx.x;
+  uint32_t at_tid = 0;             // this thread's part of the tile position
+  if constexpr (HYPER) {
+#pragma unroll
+    for (int b = 0; b < 8; ++b) at_tid |= (tid >> b & 1u) << ((b < 4 ? h.z : h.w) >> (8 * (b & 3)) & 0xffu);
+  }
   uint32_t pt = 0;                 // this thread's part of the address, then the register bits'
 #pragma unroll
   for (int b = 0; b < 8; ++b) pt ^= (tid >> b & 1u) ? pos_bytes(b < 4 ? h.z : h.w, b & 3) : 0u;
@@ -392,6 +414,22 @@ __device__ __forceinline__ void apply_group(const uint4 h, const uint4* __restri
     const uint4 w = ops[2 * s];
     const int slot = (int)w.w;
     const float2* G = Gs + 16 * slot;
+    if constexpr (HYPER) {
+      if ((w.x & 0xffu) == (uint32_t)kSvOpHyper) {
+        const uint32_t c0 = w.y >> 8 & 0xffu, c1 = w.y >> 16 & 0xffu;
+        const uint32_t b0 = c0 < 32u ? at_tid >> c0 : base >> (c0 - 32u), b1 = c1 < 32u ? at_tid >> c1 : base >> (c1 - 32u);
+        float2 g[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) g[i] = G[4u * ((b0 & 1u) | (b1 & 1u) << 1) + i];
+        switch (w.y & 0xffu) {
+          case 0: reg_hyper<LB, 0>(x, g); break;
+          case 1: reg_hyper<LB, 1>(x, g); break;
+          case 2: if constexpr (LB > 2) reg_hyper<LB, 2>(x, g); break;
+          default: if constexpr (LB > 3) reg_hyper<LB, 3>(x, g); break;
+        }
+        continue;
+      }
+    }
     const uint32_t form = (uint32_t)__builtin_amdgcn_readfirstlane((int)forms[slot]);
     const uint32_t code = (w.x & 0xffu) == (uint32_t)kSvOpGate1 ? (w.y & 0xffu) : 4u + (w.y & 0xffu);
     switch (code) {
@@ -426,7 +464,7 @@ __device__ __forceinline__ void stage_gates(const SvOp* __restrict__ ops, int n_
   for (int i = threadIdx.x; i < 16 * n_ops; i += kSvwThreads) {
     const SvOp& op = ops[i >> 4];
     const int el = i & 15, d2 = op.kind == kSvOpGate1 ? 4 : 16;
-    if ((op.kind != kSvOpGate1 && op.kind != kSvOpGate2) || el >= d2) continue;
+    if ((op.kind != kSvOpGate1 && op.kind != kSvOpGate2 && op.kind != kSvOpHyper) || el >= d2) continue;
     float2 g = merged[(int64_t)op.gate * 16 + op.idx[el]];
     if (op.conj) g.y = -g.y;
     Gs[16 * op.slot + el] = g;
@@ -524,7 +562,7 @@ __device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __res
   float2* tile = reinterpret_cast<float2*>(lds);
   floatx4_t* tile4 = lds;
   constexpr int PPT = 1 << (NP - 9);     // pairs per thread
-  constexpr bool AHEAD = !FRESH && PREC != kSvwPlain;
+  constexpr bool AHEAD = !FRESH && PREC >= 0;
   float2* Gs = tile + (1 << NP);                   // [n_plain][16]
   float2* Us = Gs + 16 * a.n_plain;                // [n_cl][256]
   uint32_t* forms = reinterpret_cast<uint32_t*>(Us + 256 * a.n_cl);   // [n_plain]
@@ -565,11 +603,12 @@ __device__ __forceinline__ void window_tiles(const SvwArgs& a, const SvOp* __res
       const uint4 w = reinterpret_cast<const uint4*>(ops)[2 * s];
       if ((w.x & 0xffu) == (uint32_t)kSvOpGroup) {
         const int ng = (int)(w.x >> 8 & 0xffu);
-        apply_group<NP>(w, reinterpret_cast<const uint4*>(ops) + 2 * (s + 1), ng, tile, Gs, forms);
+        apply_group<NP, PREC == kSvwHyper>(w, reinterpret_cast<const uint4*>(ops) + 2 * (s + 1), ng, tile, Gs, forms,
+                                           PREC == kSvwHyper ? tile_base(bid) : 0u);
         s += 1 + ng;
       } else {
         ++s;
-        if constexpr (PREC != kSvwPlain) {
+        if constexpr (PREC >= 0) {
           const uint4 w2 = reinterpret_cast<const uint4*>(ops)[2 * s - 1];
           const ClusterAt<NP> at(w.y, make_uint2(w2.x, w2.y));
           if constexpr (PREC == PTSBE_C64) apply_cluster_f32<NP>(at, Us + 256 * (int)w.w, tile);

@@ -112,7 +112,9 @@ hipError_t launch_sv_window(const SvWin& w, const SvOp* d_ops, const float2* mer
 // Runs of gates on a network tensor of rank 13 and more: the plain windows' tiles and
 // register groups.  The generic pass over the same tile costs an LDS pass and a barrier a
 // gate.  A call of 4 amplitude rows of a 100-qubit chain (4 tensors of rank 22, 3 to 7
-// gates a run) took 2.95 ms with that pass and takes 2.38 ms.
+// gates a run) took about 2.9 ms with that pass and takes 2.4 ms; the runs of a 50-qubit
+// sampling call in batches of ten (384 tensors of rank 13 to 19, most runs with a gate
+// picked by hyper legs) 7.6 ms and 3.2 ms.
 hipError_t launch_part_window(const SvWin& w, const SvOp* d_ops, const float2* merged, int G, int64_t n_jobs,
                               const int32_t* job_traj, int32_t traj_base, float2* A, int r, hipStream_t stream) {
   if (n_jobs <= 0) return hipSuccess;
@@ -130,8 +132,10 @@ hipError_t launch_part_window(const SvWin& w, const SvOp* d_ops, const float2* m
   a.job_traj = job_traj;
   const int64_t total = n_jobs << __builtin_popcount(a.live);
   const float2* Ucl = nullptr;
-  return resident_launch(sv_window_kernel<kSvwPlain, kFuseMax, false>, total, lds, stream, a, d_ops + w.op_off, merged,
-                         Ucl, A);
+  auto go = [&](auto kernel) {
+    return resident_launch(kernel, total, lds, stream, a, d_ops + w.op_off, merged, Ucl, A);
+  };
+  return w.n_hyper ? go(sv_window_kernel<kSvwHyper, kFuseMax, false>) : go(sv_window_kernel<kSvwPlain, kFuseMax, false>);
 }
 
 }  // namespace ptsbe
