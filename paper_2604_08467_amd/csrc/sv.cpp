@@ -168,29 +168,34 @@ ptsbe_status_t sv_sample_shots(Plan& p, const uint8_t* d_kraus, int64_t E, const
   if (!ids[0] || !ids[1] || !shot_x || !d_base || !norms || !counters || !merged)
     return fail(PTSBE_ERR_OUT_OF_MEMORY, "workspace too small for the shot arrays and merged gates");
   // chunks of trajectories: at most NJ states and CE elements (elements of a
-  // batch never outnumber max(trajectories, shots) of the chunk)
+  // batch never outnumber max(trajectories, shots) of the chunk, and are its trajectories
+  // where one batch holds every qubit: 10 qubits, 64 trajectories x 100 shots are then one
+  // chunk and not two, 218 -> 170 us a call)
   const size_t state = (size_t)8 << p.n, tb = sv_traj_bytes(p);
   const size_t per_elem = sv_elem_bytes(p);
   const size_t fixed = (size_t)kSplitRows * Xmax * 8 + ((size_t)1 << 20);   // first-batch split sums + alignment
   const size_t avail = ar.left() > fixed ? ar.left() - fixed : 0;
   int64_t max_m = 0;
   for (int64_t t = 0; t < E; ++t) max_m = std::max(max_m, m[t]);
+  const bool one_batch = p.batches.size() == 1;
   int64_t CE = std::min<int64_t>(std::max<int64_t>(E, M), (int64_t)(avail / 2 / per_elem));
   CE = std::max<int64_t>(CE, max_m + 1);
   const size_t elem_bytes = (size_t)CE * per_elem + scan_scratch_bytes(CE);
   if (elem_bytes + tb > avail) return fail(PTSBE_ERR_OUT_OF_MEMORY, "workspace too small for one trajectory's state");
+  if (one_batch) CE = std::min(CE, E);
   const int64_t NJ = std::min<int64_t>({(int64_t)((avail - elem_bytes) / tb), 65535, CE});
   std::vector<int64_t> cuts = {0};
   {
     int64_t nj = 0, mc = 0;
     for (int64_t t = 0; t < E; ++t) {
-      if (nj + 1 > NJ || mc + m[t] > CE) {
+      const int64_t mt = one_batch ? 1 : m[t];
+      if (nj + 1 > NJ || mc + mt > CE) {
         cuts.push_back(t);
         nj = 0;
         mc = 0;
       }
       ++nj;
-      mc += m[t];
+      mc += mt;
     }
     cuts.push_back(E);
   }

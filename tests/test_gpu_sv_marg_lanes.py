@@ -36,3 +36,22 @@ def test_marginals_of_many_elements(bs, j, elems):
         ref = sampling.marginal_from_state(psi[traj[e]], n, start, bs[j], pre[e])
         # some 10^2 gates in FP32: 1e-5 of the element's probability
         assert np.abs(pop[e] - ref).max() <= 1e-5 * ref.sum(), (e, pre[e])
+
+
+@pytest.mark.parametrize("shots", [3, 40])
+def test_one_batch_in_chunks(shots):
+    """One batch of every qubit: a workspace for a few of the states gives the call's shots
+    in several chunks of trajectories, bit for bit those of one chunk."""
+    import paper_2604_08467_amd as P
+    torch, dev = torch_dev()
+    circ = W.random_brickwork(9, 4, np.random.default_rng(9), 0.05)
+    plan = P.Plan(circ, [9], method="statevector")
+    kr, mult, _, _ = plan.sample_trajectories(3, 400)
+    E = len(kr)
+    args = (to_dev(torch, dev, kr), torch.full((E,), shots, dtype=torch.int64, device=dev), 5)
+    size = plan.sample_workspace_size(E, E * shots)
+    print(f"{E} trajectories x {shots} shots, workspace {size}", flush=True)
+    want = plan.sample_shots(*args, mult_dev=to_dev(torch, dev, mult))["shots"].cpu()
+    ws = torch.empty(size - (size - (24 << 20)) * 3 // 4, dtype=torch.uint8, device=dev)
+    got = plan.sample_shots(*args, mult_dev=to_dev(torch, dev, mult), workspace=ws)["shots"].cpu()
+    assert torch.equal(want, got)
