@@ -28,7 +28,7 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0
 SWEEP_KERNEL_TAG = "absorb_global_kernel<NK> single HBM sweep steps, 4 kept indices per thread"
 JOIN_KERNEL_TAG = "qform_mfma_kernel<32,NC> bilinear slots"
 # the LDS-sweep kernel version that profiles/lds_sweep_counters_brickwork50_b5.txt must name
-VM_KERNEL_TAG = "part_vm_kernel 64-job groups, trajectory gate slots, product-order gates, last step to HBM"
+VM_KERNEL_TAG = "part_lanes_kernel from 32768 jobs of rank <= 6, part_vm_kernel with steps in LDS for one job a workgroup"
 
 
 def _oracle_shots_worker(circuit, kraus_row, traj, batch_sizes, seed, budget_s):
@@ -317,7 +317,8 @@ def main():
                 vm_traffic = per_step / (vm["launches"] / args.steps)
         vm_rec = {"bound": "alu", "achieved": vm_rate, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                   "frac": vm_rate / FP32_VECTOR_PEAK_TFLOPS, "traffic": vm_traffic,
-                  "kernel": "part_vm_kernel (whole per-element parts swept in LDS, one gate absorbed per step)",
+                  "kernel": "part_lanes_kernel and part_vm_kernel (whole per-element parts swept in registers or LDS, one "
+                            "gate absorbed per step)",
                   "flops": "8 real flops per complex multiply-add of each absorbed gate",
                   "launches": vm["launches"], "kernel_ms_per_step": vm["ms"] / args.steps}
     # the kernel with the most event time is the roofline's; the other is reported beside it
@@ -651,7 +652,7 @@ def bench_hea20(args):
                    "value_only_ms": value_only_ms},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "adj_window_kernel (forward windows: checkpoint read, next written, 16 B per "
+                     "kernel": "adj_cl_fwd_kernel, adj_cl_bwd_kernel (forward windows: checkpoint read, next written, 16 B per "
                                "amplitude; backward windows: state read, adjoint state read and written, 24 B)",
                      "launches": win["launches"], "avg_us": win["ms"] * 1e3 / max(win["launches"], 1),
                      "bytes_per_step": win["bytes"] / args.steps, "kernel_ms_per_step": win["ms"] / args.steps},
@@ -1036,13 +1037,25 @@ def bench_ragged(args):
     M = sum(int(np.sum(j["shots_per_traj"])) for j in jobs + net_jobs + big_jobs)
     lat_all = np.concatenate([np.concatenate([a, b]) for a, b in zip(lats, nlats)])   # ms
     lat_sv = np.concatenate(lats)
-    # algorithmic bytes of the gate windows: read + write of every state once per window
+    # algorithmic bytes of the gate windows: read + write of every state once per window, as
+    # far as the qubits of the windows before it and its own reach from |0...0>
+    def plan_window_bytes(plan, size):
+        wins = [set(int(q) for q in qs) for qs in plan.sv_schedule(size)[2]]
+        if set().union(*wins) != set(range(plan.n_qubits)):
+            return 16.0 * 2 ** plan.n_qubits * len(wins)
+        seen, total = set(), 0.0
+        for qs in wins:
+            written = 8.0 * 2 ** len(qs | seen)
+            total += written + (written / 2 ** len(qs - seen) if seen else 0.0)
+            seen |= qs
+        return total
+
     win_bytes = 0.0
     for jb, bw in zip(jobs, best):
         p = jb["plan"]
-        win_bytes += float(jb["kraus"].shape[0]) * 16.0 * (2 ** p.n_qubits) * p.sv_windows_for(int(bw))
+        win_bytes += float(jb["kraus"].shape[0]) * plan_window_bytes(p, int(bw))
     n_all = [j["n"] for j in jobs + net_jobs + big_jobs]
-    big_bytes = sum(float(j["kraus"].shape[0]) * 16.0 * (2 ** j["n"]) * j["plan"].sv_windows for j in big_jobs)
+    big_bytes = sum(float(j["kraus"].shape[0]) * plan_window_bytes(j["plan"], 12) for j in big_jobs)
     line = {
         "metric": "sampled shots/sec", "value": M * args.steps / dt, "unit": "shots/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": dt / args.steps * 1e3,
