@@ -182,7 +182,7 @@ ptsbe_status_t sv_sample_shots(Plan& p, const uint8_t* d_kraus, int64_t E, const
   CE = std::max<int64_t>(CE, max_m + 1);
   const size_t elem_bytes = (size_t)CE * per_elem + scan_scratch_bytes(CE);
   if (elem_bytes + tb > avail) return fail(PTSBE_ERR_OUT_OF_MEMORY, "workspace too small for one trajectory's state");
-  if (one_batch) CE = std::min(CE, E);
+  if (one_batch) CE = std::max<int64_t>(1, std::min(CE, E));
   const int64_t NJ = std::min<int64_t>({(int64_t)((avail - elem_bytes) / tb), 65535, CE});
   std::vector<int64_t> cuts = {0};
   {

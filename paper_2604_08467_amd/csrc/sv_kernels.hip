@@ -2,7 +2,7 @@
 // trajectory's statevector (Sec. II-B, the marginal of batch j given the prefix
 // is a sum of |psi|^2 over the later qubits), the last batch's amplitudes, and
 // per-chunk element initialisation.  All of them are HBM-bound streams over the
-// state; the gate windows themselves run in fused_inplace_kernel.
+// state; the gate windows themselves run in sv_window_kernel.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
