@@ -220,8 +220,8 @@ typedef struct {
                                    row and x                                     */
   double bytes_per_traj;        /* algorithmic HBM bytes of the per-traj part    */
   int32_t n_right_launches;     /* launches of the per-trajectory part: fused
-                                   in-place runs + single steps in HBM (0 when it
-                                   runs as one LDS sweep)                        */
+                                   in-place runs + single steps in HBM (0 when every
+                                   tensor fits LDS and it runs as LDS sweeps)    */
   int32_t n_right_fused_steps;  /* per-trajectory steps inside fused in-place runs */
   int32_t right_longest_run;    /* steps of the longest fused run                */
   int32_t kept_gates;           /* gates in the batch's network (all of them

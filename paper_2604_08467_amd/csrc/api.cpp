@@ -109,10 +109,15 @@ ptsbe::GateCtx gate_ctx(const Plan& p, const uint8_t* kraus, const float2* merge
 
 size_t merged_bytes(const Plan& p, int64_t E) { return (size_t)E * p.G * 16 * sizeof(float2); }
 
+// Every tensor of the part fits LDS: it runs as one LDS sweep, or as several where its
+// steps are too many for one, with its tensor in HBM between them.
 bool part_uses_vm(const ptsbe::PartPlan& pp) { return pp.peak <= ptsbe::kVmMaxRank; }
+bool part_is_one_sweep(const ptsbe::PartPlan& pp) {
+  return part_uses_vm(pp) && (int64_t)pp.steps.size() <= ptsbe::part_vm_max_steps(pp.peak);
+}
 
 size_t part_scratch_per_job(const ptsbe::PartPlan& pp) {
-  if (pp.steps.empty() || part_uses_vm(pp)) return 0;
+  if (pp.steps.empty() || part_is_one_sweep(pp)) return 0;
   return 2 * ((size_t)8 << pp.peak);
 }
 
@@ -262,7 +267,7 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
     else HIP_TRY(ptsbe::launch_fill_one(out, n_jobs, s));
     return PTSBE_OK;
   }
-  if (part_uses_vm(pp))
+  if (part_is_one_sweep(pp))
     return timed_part_vm(p, pp, d_steps, 0, (int)pp.steps.size(), pp.peak, g, n_jobs, job_traj, traj_base, job_prefix,
                          init, out, out_rank, s);
   const size_t mark = ar.used;
@@ -332,6 +337,28 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
     peak = pk;
     return si;
   };
+  // The steps [i0, i1) of such a run from `from` (in src, null for the part's start) to
+  // *res: `out` with to_out, else a scratch buffer.  A run of more steps than one launch
+  // takes is cut, its tensor in the scratch buffers between the launches.
+  auto sweep = [&](int i0, int i1, int peak, ptsbe::InitArgs from, float2* src, bool to_out,
+                   float2** res) -> ptsbe_status_t {
+    const int most = ptsbe::part_vm_max_steps(peak);
+    for (int i = i0; i < i1;) {
+      const int e = std::min(i1, i + most);
+      const int rank = pp.steps[(size_t)e - 1].rC;
+      float2* dst = e == i1 && to_out ? out : (src == b0 ? b1 : b0);
+      const ptsbe_status_t st = timed_part_vm(p, pp, d_steps, i, e - i, peak, g, cur_n, cur_traj, traj_base, job_prefix,
+                                              from, dst, rank, s);
+      if (st != PTSBE_OK) return st;
+      from = ptsbe::InitArgs();
+      from.Vprev = src = dst;
+      from.stride = (int64_t)1 << rank;
+      from.r0 = rank;
+      i = e;
+    }
+    *res = src;
+    return PTSBE_OK;
+  };
   int h = 0, hpeak = 0;
   size_t s0 = vm_run(0, h, hpeak);
   if (trie && s0 >= nseg) {          // with subtree reuse the last launch stands alone
@@ -353,8 +380,7 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
     if (st != PTSBE_OK) return st;
   }
   if (h >= 2) {
-    const ptsbe_status_t st = timed_part_vm(p, pp, d_steps, 0, h, hpeak, g, cur_n, cur_traj, traj_base, job_prefix,
-                                            init, A, pp.steps[(size_t)h - 1].rC, s);
+    const ptsbe_status_t st = sweep(0, h, hpeak, init, nullptr, last_nf == nseg, &A);
     if (st != PTSBE_OK) return st;
   } else {
     if (init.Vprev) HIP_TRY(ptsbe::launch_init_gather(init, cur_n, job_prefix, p.NW, A, s));
@@ -387,17 +413,13 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
       int end_step = 0, peak = 0;
       const size_t end = vm_run(si, end_step, peak);
       if (end_step - (int)i >= 2) {
-        float2* C = (last_nf >= si && last_nf < end) ? out : (A == b0 ? b1 : b0);
         ptsbe::InitArgs from;
         from.Vprev = A;
         from.stride = (int64_t)1 << cur_rank;
         from.r0 = cur_rank;
-        const int rank = pp.steps[(size_t)end_step - 1].rC;
-        const ptsbe_status_t st = timed_part_vm(p, pp, d_steps, (int)i, end_step - (int)i, peak, g, cur_n, cur_traj,
-                                                traj_base, job_prefix, from, C, rank, s);
+        const ptsbe_status_t st = sweep((int)i, end_step, peak, from, A, last_nf >= si && last_nf < end, &A);
         if (st != PTSBE_OK) return st;
-        A = C;
-        cur_rank = rank;
+        cur_rank = pp.steps[(size_t)end_step - 1].rC;
         si = end - 1;
         continue;
       }

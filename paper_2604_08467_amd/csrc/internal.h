@@ -533,7 +533,9 @@ hipError_t launch_part_lanes(const AbsorbStep* d_steps, int n_steps, int rank, b
 // jobs: traj of job = job_traj ? job_traj[job] : job0 + job; prefix words of job.
 // peak: largest rank held in LDS; direct = 1: the last step (contracted legs <= 1,
 // more new legs than contracted) writes its output to `out` in HBM, its rank may
-// exceed peak.
+// exceed peak.  n_steps is at most part_vm_max_steps(peak): the steps' table takes 16 bytes
+// of LDS each beside the tensors (5,520 steps at rank 12).
+int part_vm_max_steps(int peak);
 hipError_t launch_part_vm(const AbsorbStep* d_steps, int n_steps, int peak, GateCtx g,
                           int64_t n_jobs, const int32_t* job_traj, int32_t traj_base,
                           const uint64_t* job_prefix, int NW, const InitArgs& init, float2* out,

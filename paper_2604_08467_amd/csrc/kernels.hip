@@ -2152,31 +2152,50 @@ hipError_t launch_init_gather(const InitArgs& init, int64_t n_jobs, const uint64
   return hipGetLastError();
 }
 
-hipError_t launch_part_vm(const AbsorbStep* d_steps, int n_steps, int peak, GateCtx g, int64_t n_jobs,
-                          const int32_t* job_traj, int32_t traj_base, const uint64_t* job_prefix, int NW,
-                          const InitArgs& init, float2* out, int out_rank, int direct, hipStream_t stream) {
-  if (n_jobs <= 0) return hipSuccess;
+namespace {
+// Workgroup of an LDS sweep whose largest tensor in LDS has rank `peak`.
+struct VmShape { int J, stride, threads; size_t lds; };
+VmShape vm_shape(int peak, int n_steps, int NW) {
   const int buf = 1 << (peak > 0 ? peak : 0);
+  VmShape v;
   // small tensors: up to 64 jobs share a 256-thread workgroup (2048 entries of
   // tensors in the A and C buffers; peak is the largest rank held in LDS: with
   // direct, the last step's larger output goes to HBM); one job per workgroup of 512
   // threads from 2^11 entries on
-  const int J = buf >= 2048 ? 1 : (2048 / buf > kVmMaxJobs ? kVmMaxJobs : 2048 / buf);
-  const int threads = J > 1 ? 256 : 512;
+  v.J = buf >= 2048 ? 1 : (2048 / buf > kVmMaxJobs ? kVmMaxJobs : 2048 / buf);
+  v.threads = v.J > 1 ? 256 : 512;
   // jobs' tensors one entry apart beyond their size: the same index of
   // neighbouring jobs falls in different LDS banks
-  const int stride = J > 1 ? buf + 1 : buf;
-  const int gates = J == 1 ? 16 * kVmLdsSteps : kVmGateEntries;
-  const size_t shmem = (size_t)(2 * J * stride + gates) * sizeof(float2) + (size_t)n_steps * sizeof(int4) +
-                       (size_t)J * NW * sizeof(uint64_t);
-  const dim3 grid(grid_blocks((n_jobs + J - 1) / J));
-  if (J == 1)
-    hipLaunchKernelGGL(part_vm_kernel<true>, grid, dim3(threads), shmem + kVmLdsSteps * sizeof(AbsorbStep), stream,
-                       d_steps, n_steps, stride, J, g, n_jobs, job_traj, traj_base, job_prefix, NW, init, out, out_rank,
-                       direct);
+  v.stride = v.J > 1 ? buf + 1 : buf;
+  const int gates = v.J == 1 ? 16 * kVmLdsSteps : kVmGateEntries;
+  v.lds = (size_t)(2 * v.J * v.stride + gates) * sizeof(float2) + (size_t)n_steps * sizeof(int4) +
+          (size_t)v.J * NW * sizeof(uint64_t) + (v.J == 1 ? kVmLdsSteps * sizeof(AbsorbStep) : 0);
+  return v;
+}
+constexpr size_t kVmLdsMax = 160 * 1024 - 1024;   // of a workgroup, without the kernel's static arrays
+}  // namespace
+
+// With direct, the tensors in LDS may be smaller than peak says, but their workgroup (more
+// jobs) not: the fewest steps over all ranks up to it.
+int part_vm_max_steps(int peak) {
+  size_t most = 0;
+  for (int r = 0; r <= peak; ++r) most = std::max(most, vm_shape(r, 0, kMaxQubits / 64).lds);
+  return most < kVmLdsMax ? (int)((kVmLdsMax - most) / sizeof(int4)) : 0;
+}
+
+hipError_t launch_part_vm(const AbsorbStep* d_steps, int n_steps, int peak, GateCtx g, int64_t n_jobs,
+                          const int32_t* job_traj, int32_t traj_base, const uint64_t* job_prefix, int NW,
+                          const InitArgs& init, float2* out, int out_rank, int direct, hipStream_t stream) {
+  if (n_jobs <= 0) return hipSuccess;
+  const VmShape v = vm_shape(peak, n_steps, NW);
+  if (peak > kVmMaxRank || v.lds > kVmLdsMax) return hipErrorInvalidValue;
+  const dim3 grid(grid_blocks((n_jobs + v.J - 1) / v.J));
+  if (v.J == 1)
+    hipLaunchKernelGGL(part_vm_kernel<true>, grid, dim3(v.threads), v.lds, stream, d_steps, n_steps, v.stride, v.J, g,
+                       n_jobs, job_traj, traj_base, job_prefix, NW, init, out, out_rank, direct);
   else
-    hipLaunchKernelGGL(part_vm_kernel<false>, grid, dim3(threads), shmem, stream, d_steps, n_steps, stride, J, g, n_jobs,
-                       job_traj, traj_base, job_prefix, NW, init, out, out_rank, direct);
+    hipLaunchKernelGGL(part_vm_kernel<false>, grid, dim3(v.threads), v.lds, stream, d_steps, n_steps, v.stride, v.J, g,
+                       n_jobs, job_traj, traj_base, job_prefix, NW, init, out, out_rank, direct);
   return hipGetLastError();
 }
 
