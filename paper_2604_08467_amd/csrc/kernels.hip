@@ -189,8 +189,9 @@ __device__ inline uint32_t init_offset(const InitArgs& in, uint32_t m, const uin
 
 constexpr int kVmMaxJobs = 64;        // jobs per workgroup (one wavefront assigns the trajectory slots)
 // gate entries staged per chunk of steps: [chunk steps][trajectory slots][16] float2; one
-// step of jobs that are all of different trajectories has to fit
-constexpr int kVmGateEntries = 16 * kVmMaxJobs;
+// step of jobs that are all of different trajectories has to fit, and up to 32 jobs 512
+// entries do, with which four workgroups of rank 6 to 10 share a CU (1024: three)
+__host__ __device__ constexpr int vm_gate_entries(int J) { return J > 32 ? 16 * kVmMaxJobs : 512; }
 
 // LS (one job a workgroup): the steps of a chunk are copied to LDS with their gates, so that
 // a step costs one round of LDS latency; as scalar loads its description, 424 bytes that no
@@ -214,7 +215,7 @@ __global__ void __launch_bounds__(512, 4) part_vm_kernel(const AbsorbStep* __res
   float2* bufA = lds;                                   // [J][buf_elems]
   float2* bufC = lds + (size_t)J * buf_elems;           // [J][buf_elems]
   float2* Gm = lds + 2 * (size_t)J * buf_elems;         // [chunk][slots][16] gates of a chunk of steps
-  int4* stab = reinterpret_cast<int4*>(Gm + (LS ? 16 * kVmLdsSteps : kVmGateEntries));   // [n_steps] gate | conj << 31, gperm
+  int4* stab = reinterpret_cast<int4*>(Gm + (LS ? 16 * kVmLdsSteps : vm_gate_entries(J)));   // [n_steps] gate | conj << 31, gperm
   uint64_t* pw = reinterpret_cast<uint64_t*>(stab + n_steps);  // [J][NW] prefixes
   AbsorbStep* lsteps = reinterpret_cast<AbsorbStep*>(pw + (size_t)J * NW);   // [kVmLdsSteps], LS only
   const int tid = threadIdx.x, nt = blockDim.x;
@@ -244,7 +245,7 @@ __global__ void __launch_bounds__(512, 4) part_vm_kernel(const AbsorbStep* __res
     __syncthreads();
     const int n_slots = n_slots_s;
     const int per_step = 16 * n_slots;
-    const int chunk = LS ? kVmLdsSteps : kVmGateEntries / per_step;   // at least one step: n_slots <= kVmMaxJobs
+    const int chunk = LS ? kVmLdsSteps : vm_gate_entries(J) / per_step;   // at least one step: n_slots <= kVmMaxJobs
     // gates of the steps [c0, c1) in LDS, every (step, slot, entry) of the chunk
     // spread over all threads, two loads per thread in flight together
     // (unconditional, from a clamped valid entry), the bra conjugation applied at
@@ -2167,7 +2168,7 @@ VmShape vm_shape(int peak, int n_steps, int NW) {
   // jobs' tensors one entry apart beyond their size: the same index of
   // neighbouring jobs falls in different LDS banks
   v.stride = v.J > 1 ? buf + 1 : buf;
-  const int gates = v.J == 1 ? 16 * kVmLdsSteps : kVmGateEntries;
+  const int gates = v.J == 1 ? 16 * kVmLdsSteps : vm_gate_entries(v.J);
   v.lds = (size_t)(2 * v.J * v.stride + gates) * sizeof(float2) + (size_t)n_steps * sizeof(int4) +
           (size_t)v.J * NW * sizeof(uint64_t) + (v.J == 1 ? kVmLdsSteps * sizeof(AbsorbStep) : 0);
   return v;
