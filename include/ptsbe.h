@@ -136,7 +136,11 @@ typedef struct {
                                    c64, FP64 for sums, CDFs and weights */
   int32_t device;               /* HIP device ordinal; -1: host-only plan (path,
                                    query and pre-sampling only, no device calls) */
-  size_t device_budget_bytes;   /* 0: no limit; else plan constants must fit     */
+  size_t device_budget_bytes;   /* 0: no limit; else plan constants must fit; the
+                                   tables of faster forms (adjoint cluster windows,
+                                   in-place runs of network tensors) are left out
+                                   where they do not fit beside the rest, and the
+                                   general form runs                             */
   int32_t method;               /* PTSBE_METHOD_*                                 */
   int32_t light_cone;           /* 1: every doubled network (batches before the
                                    last) keeps only the gates in the past light

@@ -65,26 +65,6 @@ using ptsbe::Arena;
 }  // namespace
 
 namespace ptsbe {
-std::vector<double2> site_ops64(const Plan& p) {
-  std::vector<double2> out((size_t)std::max(1, p.S) * p.max_kraus * 16, make_double2(0.0, 0.0));
-  std::vector<cd> op(16), e(16);
-  for (int s = 0; s < p.S; ++s) {
-    const int g = p.site_gate[(size_t)s];
-    std::vector<int> gq = {p.qubits[(size_t)g][0]}, sq = {p.site_qubits[(size_t)s][0]};
-    if (p.arity[(size_t)g] == 2) gq.push_back(p.qubits[(size_t)g][1]);
-    if (p.site_qubits[(size_t)s][1] >= 0) sq.push_back(p.site_qubits[(size_t)s][1]);
-    const auto& ops = p.ch_ops[(size_t)p.site_channel[(size_t)s]];
-    const int d = 1 << gq.size(), dk = 1 << sq.size();
-    for (size_t k = 0; k < ops.size(); ++k) {
-      for (int i = 0; i < dk * dk; ++i) op[(size_t)i] = cd(ops[k][2 * i], ops[k][2 * i + 1]);
-      embed_op(op.data(), sq, gq, e.data());
-      for (int i = 0; i < d * d; ++i)
-        out[((size_t)s * p.max_kraus + k) * 16 + i] = make_double2(e[(size_t)i].real(), e[(size_t)i].imag());
-    }
-  }
-  return out;
-}
-
 thread_local std::string g_last_error;
 ptsbe_status_t fail(ptsbe_status_t s, const std::string& msg) {
   g_last_error = msg;
@@ -1228,6 +1208,14 @@ ptsbe_status_t ptsbe_plan(const ptsbe_circuit_t* c, const ptsbe_plan_opts_t* o, 
   std::vector<ptsbe::DeviceGate> dg(p->G);
   std::vector<int32_t> site_list;
   std::vector<float2> site_ops((size_t)std::max(1, p->S) * p->max_kraus * 16, make_float2(0.f, 0.f));
+  // cluster schedule of the adjoint passes; with non-unitary operators three tiles and both
+  // forms of the matrices share 64 KB of LDS
+  ptsbe::AdjClSchedule& acl = p->adj_cl;
+  ptsbe::build_adj_clusters(*p, p->inserted_unitary ? ptsbe::kAdjWindowQubits : ptsbe::kAdjWindowQubits - 1, acl);
+  if (acl.ok) {
+    acl.mats.assign((size_t)p->G * 16, make_double2(0.0, 0.0));
+    acl.site_ops.assign(site_ops.size(), make_double2(0.0, 0.0));
+  }
   for (int g = 0; g < p->G; ++g) {
     const int ar = p->arity[g], d = 1 << ar;
     std::vector<int> gq = {p->qubits[g][0]};
@@ -1235,7 +1223,10 @@ ptsbe_status_t ptsbe_plan(const ptsbe_circuit_t* c, const ptsbe_plan_opts_t* o, 
     std::vector<cd> m(d * d), t(d * d), e(d * d);
     for (int i = 0; i < d * d; ++i) m[i] = cd(p->mats[g][2 * i], p->mats[g][2 * i + 1]);
     for (int i = 0; i < 16; ++i) dg[g].raw[i] = make_float2(0.f, 0.f);
-    for (int i = 0; i < d * d; ++i) dg[g].raw[i] = make_float2((float)m[i].real(), (float)m[i].imag());
+    for (int i = 0; i < d * d; ++i) {
+      dg[g].raw[i] = make_float2((float)m[i].real(), (float)m[i].imag());
+      if (acl.ok) acl.mats[(size_t)g * 16 + i] = make_double2(m[i].real(), m[i].imag());
+    }
     dg[g].site_begin = (int)site_list.size();
     for (int s : p->gate_sites[g]) {
       site_list.push_back(s);
@@ -1248,8 +1239,11 @@ ptsbe_status_t ptsbe_plan(const ptsbe_circuit_t* c, const ptsbe_plan_opts_t* o, 
         std::vector<cd> op(dk * dk);
         for (int i = 0; i < dk * dk; ++i) op[i] = cd(p->ch_ops[ch][k][2 * i], p->ch_ops[ch][k][2 * i + 1]);
         embed_op(op.data(), sq, gq, e.data());
-        for (int i = 0; i < d * d; ++i)
-          site_ops[((size_t)s * p->max_kraus + k) * 16 + i] = make_float2((float)e[i].real(), (float)e[i].imag());
+        for (int i = 0; i < d * d; ++i) {
+          const size_t at = ((size_t)s * p->max_kraus + k) * 16 + i;
+          site_ops[at] = make_float2((float)e[i].real(), (float)e[i].imag());
+          if (acl.ok) acl.site_ops[at] = make_double2(e[i].real(), e[i].imag());
+        }
         if (k == 0) {   // default branch: every site at Kraus index 0, later sites on the left
           matmul(e.data(), m.data(), t.data(), d);
           m = t;
@@ -1304,9 +1298,21 @@ ptsbe_status_t ptsbe_plan(const ptsbe_circuit_t* c, const ptsbe_plan_opts_t* o, 
   size_t bytes = dg.size() * sizeof(ptsbe::DeviceGate) + site_list.size() * 4 + site_ops.size() * sizeof(float2) +
                  steps.size() * sizeof(ptsbe::AbsorbStep) + tables.size() * 8 +
                  p->fused.size() * sizeof(ptsbe::FusedStep);
+  const size_t budget = o->device_budget_bytes ? o->device_budget_bytes : SIZE_MAX;
+  if (bytes > budget) return fail(PTSBE_ERR_OUT_OF_MEMORY, "plan constants exceed device_budget_bytes");
+  // constants of the faster forms, left out where they do not fit the budget beside the rest:
+  // network runs then take the generic tile pass, adjoint calls the windows of single gates
+  if (bytes + p->part_ops.size() * sizeof(ptsbe::SvOp) <= budget) {
+    bytes += p->part_ops.size() * sizeof(ptsbe::SvOp);
+  } else {
+    p->part_ops.clear();
+    for (auto& bp : p->batches)
+      for (ptsbe::PartPlan* pp : {&bp.left, &bp.right, &bp.left_resume})
+        for (ptsbe::Segment& sg : pp->segs) sg.win = -1;
+  }
+  if (acl.ok && bytes + acl.offsets().bytes <= budget) bytes += acl.offsets().bytes;
+  else acl = ptsbe::AdjClSchedule();
   p->device_bytes = (int64_t)bytes;
-  if (o->device_budget_bytes && bytes > o->device_budget_bytes)
-    return fail(PTSBE_ERR_OUT_OF_MEMORY, "plan constants exceed device_budget_bytes");
   if (p->device < 0) {   // host-only plan: path and pre-sampling only, no device constants
     *out = reinterpret_cast<ptsbe_plan_t>(guard.release());
     return PTSBE_OK;
@@ -1326,6 +1332,16 @@ ptsbe_status_t ptsbe_plan(const ptsbe_circuit_t* c, const ptsbe_plan_opts_t* o, 
     HIP_TRY(hipMalloc(&p->d_part_ops, p->part_ops.size() * sizeof(ptsbe::SvOp)));
     HIP_TRY(hipMemcpy(p->d_part_ops, p->part_ops.data(), p->part_ops.size() * sizeof(ptsbe::SvOp),
                       hipMemcpyHostToDevice));
+  }
+  if (acl.ok) {
+    const auto at = acl.offsets();
+    std::vector<char> all(at.bytes, 0);
+    std::memcpy(all.data() + at.cls, acl.cls.data(), acl.cls.size() * sizeof(ptsbe::AdjCl));
+    std::memcpy(all.data() + at.ops, acl.ops.data(), acl.ops.size() * sizeof(ptsbe::AdjClOp));
+    std::memcpy(all.data() + at.mats, acl.mats.data(), acl.mats.size() * sizeof(double2));
+    std::memcpy(all.data() + at.site_ops, acl.site_ops.data(), acl.site_ops.size() * sizeof(double2));
+    HIP_TRY(hipMalloc(&acl.d_base, at.bytes));
+    HIP_TRY(hipMemcpy(acl.d_base, all.data(), at.bytes, hipMemcpyHostToDevice));
   }
   if (p->method == PTSBE_METHOD_STATEVECTOR) {
     for (int i = 0; i < 3; ++i) {
@@ -1405,10 +1421,7 @@ void ptsbe_plan_destroy(ptsbe_plan_t plan) {
     if (o) (void)hipFree(o);
   for (auto* o : p->d_sv_wins_plain)
     if (o) (void)hipFree(o);
-  if (p->adj_cl.d_cls) (void)hipFree(p->adj_cl.d_cls);
-  if (p->adj_cl.d_ops) (void)hipFree(p->adj_cl.d_ops);
-  if (p->d_mats64) (void)hipFree(p->d_mats64);
-  if (p->d_site_ops64) (void)hipFree(p->d_site_ops64);
+  if (p->adj_cl.d_base) (void)hipFree(p->adj_cl.d_base);
   delete p;
 }
 

@@ -20,9 +20,7 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
-#include <mutex>
 #include <string>
-#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -30,10 +28,10 @@
 using ptsbe::Arena;
 using ptsbe::fail;
 using ptsbe::Plan;
+using ptsbe::kAdjWindowQubits;
 
 namespace {
 
-constexpr int kAdjWindowQubits = 11;   // two (three when recomputing) 16 KB tiles per workgroup
 constexpr int64_t kAdjChunkMax = 1024;
 
 struct AdjSpec {
@@ -121,40 +119,6 @@ size_t adj_fixed_bytes(const Plan& p, int64_t E, size_t n_ops, size_t width_tota
 // Angle gradients and values of circuits of at least 8 qubits run on the cluster
 // windows (adj_cluster.hip); gate-tensor adjoints, which need every gate's own
 // amplitudes, and smaller circuits on the per-gate windows below.
-// The plan's cluster schedule, made by the first call on the host; with `device`, also
-// its device copy and the 64-bit gate operands.
-ptsbe_status_t cluster_schedule(Plan& p, bool device, const ptsbe::AdjClSchedule** out) {
-  std::lock_guard<std::mutex> lock(p.adj_mu);
-  ptsbe::AdjClSchedule& S = p.adj_cl;
-  if (!p.adj_cl_made) {
-    // with non-unitary operators three tiles and both forms of the matrices share 64 KB of LDS
-    ptsbe::build_adj_clusters(p, p.inserted_unitary ? kAdjWindowQubits : kAdjWindowQubits - 1, S);
-    p.adj_cl_made = true;
-  }
-  *out = &S;
-  if (!device || !S.ok) return PTSBE_OK;
-  auto put = [](auto** d, const auto& v) -> hipError_t {
-    if (*d) return hipSuccess;
-    void* m = nullptr;
-    hipError_t e = hipMalloc(&m, std::max<size_t>(v.size(), 1) * sizeof(v[0]));
-    if (e == hipSuccess) e = hipMemcpy(m, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice);
-    if (e == hipSuccess) *d = static_cast<std::remove_reference_t<decltype(**d)>*>(m);
-    else if (m) (void)hipFree(m);
-    return e;
-  };
-  HIP_TRY(put(&S.d_cls, S.cls));
-  HIP_TRY(put(&S.d_ops, S.ops));
-  if (!p.d_mats64) {
-    std::vector<double2> m((size_t)p.G * 16, make_double2(0.0, 0.0));
-    for (int g = 0; g < p.G; ++g)
-      for (int i = 0; i < (1 << (2 * p.arity[(size_t)g])); ++i)
-        m[(size_t)g * 16 + i] = make_double2(p.mats[(size_t)g][2 * i], p.mats[(size_t)g][2 * i + 1]);
-    HIP_TRY(put(&p.d_mats64, m));
-  }
-  if (!p.d_site_ops64) HIP_TRY(put(&p.d_site_ops64, ptsbe::site_ops64(p)));
-  return PTSBE_OK;
-}
-
 // Device bytes per trajectory of a chunk: states (every window's, and lambda), merged
 // gates, cluster matrices, and for a gradient one workgroup's sums and the derivatives.
 size_t cluster_per_traj(const Plan& p, const ptsbe::AdjClSchedule& S, bool grad) {
@@ -267,16 +231,16 @@ ptsbe_status_t run_clusters(Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedul
     ba.g.S = p.S;
     ba.g.max_kraus = p.max_kraus;
     ba.g.G = G;
-    ba.mats = p.d_mats64;
-    ba.site_ops = p.d_site_ops64;
+    ba.mats = sched.d_mats();
+    ba.site_ops = sched.d_site_ops();
     ba.gate_param = d_gp;
     ba.gate_axis = d_ga;
     ba.theta = d_theta;
     ba.n_jobs = nj;
     ba.traj_base = (int32_t)t0;
     ba.A = A;
-    ba.cls = sched.d_cls;
-    ba.ops = sched.d_ops;
+    ba.cls = sched.d_cls();
+    ba.ops = sched.d_ops();
     ba.n_cl = n_cl;
     ba.n_ops = n_ops;
     ba.U = grad ? (float2*)U : nullptr;
@@ -335,7 +299,7 @@ ptsbe_status_t run_clusters(Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedul
         const ptsbe_status_t st = timed((double)nj * 24.0 * std::ldexp(1.0, wd.np + tb),
                                         [&] { return ptsbe::launch_adj_cl_pass(pass, a, wd.np, s); });
         if (st != PTSBE_OK) return st;
-        HIP_TRY(ptsbe::launch_adj_cl_grad(a, !recompute, sched.d_cls, sched.d_ops, n_ops, A, d_gp, d_ga, gop, s));
+        HIP_TRY(ptsbe::launch_adj_cl_grad(a, !recompute, sched.d_cls(), sched.d_ops(), n_ops, A, d_gp, d_ga, gop, s));
       }
       HIP_TRY(ptsbe::launch_adj_cl_params(gop, nj, n_ops, d_poff, d_pops, S.n_params, t0 > 0, d_grad, s));
     }
@@ -364,13 +328,11 @@ ptsbe_status_t ptsbe_adjoint_workspace_size(ptsbe_plan_t plan, const ptsbe_adjoi
   for (const auto& w : wins) max_ops = std::max<size_t>(max_ops, (size_t)w.n_ops);
   *bytes = adj_fixed_bytes(*p, E, ops.size(), ops.size() * 33, max_ops * 33) +
            (size_t)std::min<int64_t>(E, 256) * adj_per_traj(*p, wins.size(), true);
-  const ptsbe::AdjClSchedule* cl = nullptr;
-  st = cluster_schedule(*p, false, &cl);
-  if (st != PTSBE_OK) return st;
-  if (cl->ok) {
+  const ptsbe::AdjClSchedule& cl = p->adj_cl;
+  if (cl.ok) {
     // sums of up to 2048 workgroups beside the chunk's arrays
-    const size_t b = cluster_fixed_bytes(*p, S, E, cl->ops.size()) + (size_t)2048 * ptsbe::kAdjClMax * 4096 +
-                     (size_t)std::min<int64_t>(E, 256) * cluster_per_traj(*p, *cl, true);
+    const size_t b = cluster_fixed_bytes(*p, S, E, cl.ops.size()) + (size_t)2048 * ptsbe::kAdjClMax * 4096 +
+                     (size_t)std::min<int64_t>(E, 256) * cluster_per_traj(*p, cl, true);
     *bytes = std::max(*bytes, b);
   }
   return PTSBE_OK;
@@ -401,14 +363,9 @@ ptsbe_status_t ptsbe_contract_adjoint(ptsbe_plan_t plan, const ptsbe_adjoint_spe
   const bool want_grad = d_grad != nullptr && S.n_params > 0;
   const bool want_adj = d_gate_adj != nullptr;
   const bool backward = want_grad || want_adj;
-  if (!want_adj) {
-    const ptsbe::AdjClSchedule* cl = nullptr;
-    st = cluster_schedule(*p, true, &cl);
-    if (st != PTSBE_OK) return st;
-    if (cl->ok)
-      return run_clusters(*p, S, *cl, d_kraus_idx, E, d_weights, d_theta, d_psi_bar, d_traj_value, d_value, d_grad,
-                          d_workspace, workspace_bytes, s);
-  }
+  if (!want_adj && p->adj_cl.ok)
+    return run_clusters(*p, S, p->adj_cl, d_kraus_idx, E, d_weights, d_theta, d_psi_bar, d_traj_value, d_value, d_grad,
+                        d_workspace, workspace_bytes, s);
   // windows and their ops (host, once per call)
   const bool recompute = !p->inserted_unitary;
   std::vector<ptsbe::AdjWin> wins;

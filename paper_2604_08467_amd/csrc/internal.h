@@ -6,7 +6,6 @@
 
 #include <array>
 #include <cstdint>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -238,15 +237,29 @@ struct AdjClWin {
   // are zero on entry (as SvWin's).  The backward pass needs lambda no further than that.
   uint32_t live, fresh;
 };
-// One schedule of a plan (host and device copies), made by the first call that needs
-// it and kept with the plan.
+// The plan's schedule and its constants on the device (one allocation of the plan).
 struct AdjClSchedule {
   bool ok = false;                  // every step is a plain gate and the circuit has at least 8 qubits
   std::vector<AdjClWin> wins;
   std::vector<AdjCl> cls;
   std::vector<AdjClOp> ops;
-  AdjCl* d_cls = nullptr;
-  AdjClOp* d_ops = nullptr;
+  std::vector<double2> mats;        // [G][16] bare gates
+  std::vector<double2> site_ops;    // [S][max_kraus][16] inserted operators of every site in its gate's space
+  char* d_base = nullptr;           // cls, ops, mats, site_ops, as offsets() has them
+  struct Offsets { size_t cls, ops, mats, site_ops, bytes; };
+  Offsets offsets() const {
+    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    Offsets o{};
+    o.ops = up(cls.size() * sizeof(AdjCl));
+    o.mats = o.ops + up(ops.size() * sizeof(AdjClOp));
+    o.site_ops = o.mats + up(mats.size() * sizeof(double2));
+    o.bytes = o.site_ops + up(site_ops.size() * sizeof(double2));
+    return o;
+  }
+  const AdjCl* d_cls() const { return reinterpret_cast<const AdjCl*>(d_base); }
+  const AdjClOp* d_ops() const { return reinterpret_cast<const AdjClOp*>(d_base + offsets().ops); }
+  const double2* d_mats() const { return reinterpret_cast<const double2*>(d_base + offsets().mats); }
+  const double2* d_site_ops() const { return reinterpret_cast<const double2*>(d_base + offsets().site_ops); }
 };
 struct AdjClArgs {
   int n, cl_off, n_cl, n_cl_total, wpj;
@@ -447,12 +460,7 @@ struct Plan {
   bool subtree_reuse = false;
   int sample_kernel = 0;               // 0: automatic lane-per-element sampling, 1: wavefront per element
 
-  // cluster schedule of the adjoint passes and the 64-bit gate operands it is built from
-  std::mutex adj_mu;
-  AdjClSchedule adj_cl;
-  bool adj_cl_made = false;
-  double2* d_mats64 = nullptr;
-  double2* d_site_ops64 = nullptr;
+  AdjClSchedule adj_cl;                // cluster schedule of the adjoint passes
 
   // measurement
   int profile = 0;                                // 1: time the MFMA join; 2: also single HBM sweep steps
@@ -500,9 +508,8 @@ void build_adj_groups(std::vector<AdjWin>& wins, std::vector<AdjOp>& ops, std::v
 // The same packing with each window's gates in clusters of at most kAdjClOps gates on at
 // most four positions, at most kAdjClMax clusters per window.  Leaves s.ok false when a
 // step is not a plain gate or the circuit has fewer than 8 qubits.
+constexpr int kAdjWindowQubits = 11;  // two (three when recomputing) 16 KB tiles per workgroup
 void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& s);
-// Inserted operators of every site in its gate's space, 64 bits: [S][max_kraus][16].
-std::vector<double2> site_ops64(const Plan& p);
 
 // kernels.hip: launchers (all asynchronous on `stream`)
 // UPV merge (error injection) of every (trajectory, gate): merged[t][g] =

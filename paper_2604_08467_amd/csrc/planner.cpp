@@ -705,6 +705,14 @@ bool plain_step(const AbsorbStep& st) {
   return true;
 }
 
+// Qubits of a statevector step (n <= kSvMaxQubits) as a bit mask.
+static_assert(kSvMaxQubits <= 32, "masks of qubits are 32 bits");
+uint32_t step_qubits(const AbsorbStep& st) {
+  uint32_t on = 0;
+  for (int k = 0; k < st.nK; ++k) on |= 1u << st.kpos[k];
+  return on;
+}
+
 // Relative VALU cost of one step in the window pass (a dense two-qubit gate = 1);
 // a 16 x 16 cluster on MFMA costs about 1.6 plus its build.
 double step_cost(const Plan& p, const AbsorbStep& st) {
@@ -735,27 +743,23 @@ void cluster_order(const Plan& p, const std::vector<int>& steps, std::vector<int
   order.clear();
   groups.clear();
   while (order.size() < steps.size()) {
-    std::set<int> Q, blocked;
+    uint32_t Q = 0, blocked = 0;                       // bit masks of qubits
     const int start = (int)order.size();
     bool closed = false;
     for (size_t i = 0; i < steps.size(); ++i) {
       if (used[i]) continue;
       const AbsorbStep& st = p.sv_steps[(size_t)steps[i]];
+      const uint32_t on = step_qubits(st);
       const bool first = (int)order.size() == start;   // the first unused step: nothing blocks it
-      bool ok = !closed;
-      std::set<int> Q2 = Q;
-      for (int k = 0; k < st.nK; ++k) {
-        ok = ok && !blocked.count(st.kpos[k]);
-        Q2.insert(st.kpos[k]);
-      }
-      if (!first) ok = ok && plain_step(st) && Q2.size() <= 4;
+      bool ok = !closed && !(on & blocked);
+      if (!first) ok = ok && plain_step(st) && __builtin_popcount(Q | on) <= 4;
       if (ok) {
         used[i] = 1;
         order.push_back(steps[i]);
-        Q = Q2;
+        Q |= on;
         if (first && !plain_step(st)) closed = true;   // a step the cluster pass cannot take stands alone
       } else {
-        for (int k = 0; k < st.nK; ++k) blocked.insert(st.kpos[k]);
+        blocked |= on;
       }
     }
     groups.push_back({start, (int)order.size() - start});
@@ -771,27 +775,24 @@ void pack_window(const Plan& p, const std::vector<int>& rest, int wmax, std::vec
   const int n = p.n;
   const int cap = std::min(wmax, n);
   const int low = std::min(4, n);
-  std::set<int> P, blocked;
-  for (int q = 0; q < low; ++q) P.insert(q);
+  uint32_t P = (1u << low) - 1u, blocked = 0;           // bit masks of qubits
   taken.clear();
   left_out.clear();
   for (int g : rest) {
-    const AbsorbStep& st = p.sv_steps[g];
-    bool free = true;
-    for (int k = 0; k < st.nK; ++k) free = free && !blocked.count(st.kpos[k]);
-    std::set<int> P2 = P;
-    for (int k = 0; k < st.nK; ++k) P2.insert(st.kpos[k]);
-    if (free && (int)P2.size() <= cap && taken.size() < max_steps) {
-      P = P2;
+    const uint32_t on = step_qubits(p.sv_steps[(size_t)g]);
+    if (!(on & blocked) && __builtin_popcount(P | on) <= cap && taken.size() < max_steps) {
+      P |= on;
       taken.push_back(g);
     } else {
-      for (int k = 0; k < st.nK; ++k) blocked.insert(st.kpos[k]);
+      blocked |= on;
       left_out.push_back(g);
     }
   }
   // pad the window with the lowest qubits not yet in it
-  for (int q = 0; (int)P.size() < cap && q < n; ++q) P.insert(q);
-  Pv.assign(P.begin(), P.end());
+  for (int q = 0; __builtin_popcount(P) < cap && q < n; ++q) P |= 1u << q;
+  Pv.clear();
+  for (int q = 0; q < n; ++q)
+    if (P >> q & 1u) Pv.push_back(q);
 }
 
 std::vector<Segment> sv_windows(Plan& p, int wmax, std::vector<AbsorbStep>* run, std::vector<ClusterDesc>& cls) {
@@ -961,9 +962,6 @@ void build_adj_groups(std::vector<AdjWin>& wins, std::vector<AdjOp>& ops, std::v
 
 void build_adj_clusters(const Plan& p, int wmax, AdjClSchedule& S) {
   S.ok = false;
-  S.wins.clear();
-  S.cls.clear();
-  S.ops.clear();
   if (p.n < 8 || p.sv_steps.empty()) return;
   for (const AbsorbStep& st : p.sv_steps)
     if (!plain_step(st)) return;
