@@ -127,6 +127,8 @@ size_t cluster_per_traj(const Plan& p, const ptsbe::AdjClSchedule& S, bool grad)
   return b + 2048;                     // alignment of the chunk's arrays
 }
 
+constexpr size_t kClusterSlack = (size_t)64 << 10;   // a chunk's arrays rounded up
+
 size_t cluster_table_bytes(const Plan& p, const AdjSpec& S, size_t n_ops) {
   return align256(((size_t)2 * p.G + (size_t)S.n_params + 1 + n_ops + S.zq.size()) * 4 + S.zc.size() * 8 + 64);
 }
@@ -134,6 +136,16 @@ size_t cluster_table_bytes(const Plan& p, const AdjSpec& S, size_t n_ops) {
 size_t cluster_fixed_bytes(const Plan& p, const AdjSpec& S, int64_t E, size_t n_ops) {
   return cluster_table_bytes(p, S, n_ops) + align256((size_t)E * 8) + align256((size_t)8 << p.n) +
          align256((size_t)std::min<int64_t>(E, kAdjChunkMax) * 64 * 8) + ((size_t)1 << 20);
+}
+
+// The least workspace of a call: one trajectory a chunk.  The cluster form keeps up to one
+// checkpoint more than the windows of single gates; a smaller workspace goes to those.
+size_t cluster_min_bytes(const Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedule& sched, int64_t E, bool grad,
+                         bool own_values) {
+  return cluster_table_bytes(p, S, sched.ops.size()) + (own_values ? 0 : align256((size_t)E * 8)) +
+         (S.obs_diag ? 0 : align256((size_t)8 << p.n)) +
+         align256((size_t)std::min<int64_t>(E, kAdjChunkMax) * 64 * 8) + kClusterSlack +
+         cluster_per_traj(p, sched, grad);
 }
 
 ptsbe_status_t run_clusters(Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedule& sched, const uint8_t* d_kraus,
@@ -186,7 +198,7 @@ ptsbe_status_t run_clusters(Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedul
   HIP_TRY(hipMemcpyAsync(d_tab, tab.data(), at, hipMemcpyHostToDevice, s));
   if (!S.obs_diag) HIP_TRY(ptsbe::launch_adj_zz_diag(n, d_zq, d_zc, S.has_obs ? (int)S.zc.size() : 0, d_diag, s));
   const size_t per = cluster_per_traj(p, sched, grad);
-  const size_t avail = ar.left() > ((size_t)64 << 10) ? ar.left() - ((size_t)64 << 10) : 0;
+  const size_t avail = ar.left() > kClusterSlack ? ar.left() - kClusterSlack : 0;
   const int64_t Ec = std::min<int64_t>({E, (int64_t)(avail / per), kAdjChunkMax});
   if (Ec < 1) return fail(PTSBE_ERR_OUT_OF_MEMORY, "workspace too small for one trajectory's checkpoints");
   const size_t SZ = (size_t)1 << n;
@@ -333,7 +345,9 @@ ptsbe_status_t ptsbe_adjoint_workspace_size(ptsbe_plan_t plan, const ptsbe_adjoi
     // sums of up to 2048 workgroups beside the chunk's arrays
     const size_t b = cluster_fixed_bytes(*p, S, E, cl.ops.size()) + (size_t)2048 * ptsbe::kAdjClMax * 4096 +
                      (size_t)std::min<int64_t>(E, 256) * cluster_per_traj(*p, cl, true);
-    *bytes = std::max(*bytes, b);
+    // one more checkpoint must not ask for more than the card has where the windows of
+    // single gates, which smaller workspaces go to, did not
+    if (b <= ((size_t)256 << 30)) *bytes = std::max(*bytes, b);
   }
   return PTSBE_OK;
 }
@@ -363,7 +377,8 @@ ptsbe_status_t ptsbe_contract_adjoint(ptsbe_plan_t plan, const ptsbe_adjoint_spe
   const bool want_grad = d_grad != nullptr && S.n_params > 0;
   const bool want_adj = d_gate_adj != nullptr;
   const bool backward = want_grad || want_adj;
-  if (!want_adj && p->adj_cl.ok)
+  if (!want_adj && p->adj_cl.ok &&
+      workspace_bytes >= cluster_min_bytes(*p, S, p->adj_cl, E, want_grad, d_traj_value != nullptr))
     return run_clusters(*p, S, p->adj_cl, d_kraus_idx, E, d_weights, d_theta, d_psi_bar, d_traj_value, d_value, d_grad,
                         d_workspace, workspace_bytes, s);
   // windows and their ops (host, once per call)
