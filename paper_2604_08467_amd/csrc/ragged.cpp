@@ -331,11 +331,9 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
     int maxf = 0;
   };
   std::vector<WaveLaunch> wl(waves.size());
-  Arena tb;
-  tb.base = tables;
-  tb.cap = table_bytes;
-  // the tables are laid out here and copied at once: a blocking copy each (29 in a wave of
-  // six window launches) took 0.8 ms of an 8.4 ms call of 12 jobs
+  // the tables are laid out here, each on a 16-byte boundary (a wave of one trajectory has
+  // some of 4 to 16 bytes for each of its window levels), and copied at once: a blocking copy
+  // each (29 in a wave of six window launches) took 0.8 ms of an 8.4 ms call of 12 jobs
   std::vector<char> staged;
   std::vector<int64_t> key = {n_jobs, flags, (int64_t)(intptr_t)d_workspace, (int64_t)workspace_bytes,
                               (int64_t)(intptr_t)d_done_ticks};
@@ -442,13 +440,11 @@ ptsbe_status_t ptsbe_ragged_sample_shots(ptsbe_ragged_t set, const ptsbe_ragged_
     if (!ok) return fail(PTSBE_ERR_OUT_OF_MEMORY, "wave arena too small (elements)");
     // tables
     auto put = [&](const void* src, size_t bytes) -> void* {
-      char* d = (char*)tb.take(std::max<size_t>(bytes, 8));
-      if (d && bytes) {
-        const size_t off = (size_t)(d - tables);
-        if (staged.size() < off + bytes) staged.resize(off + bytes);
-        std::memcpy(staged.data() + off, src, bytes);
-      }
-      return d;
+      const size_t off = (staged.size() + 15) & ~(size_t)15;
+      if (off + std::max<size_t>(bytes, 8) > table_bytes) return nullptr;
+      staged.resize(off + std::max<size_t>(bytes, 8));
+      if (bytes) std::memcpy(staged.data() + off, src, bytes);
+      return tables + off;
     };
     w.pieces = (const RgPiece*)put(pcs.data(), pcs.size() * sizeof(RgPiece));
     w.traj_piece = (const int32_t*)put(traj_piece.data(), traj_piece.size() * 4);
