@@ -421,11 +421,11 @@ __global__ void __launch_bounds__(kSvwThreads) adj_bwd_tile_kernel(AdjArgs a, co
 }
 
 // ---------------------------------------------------------------------------
-// Group passes of the forward windows: the ops of one group (at most kAdjGroupMax
-// consecutive ops on at most two tile positions, build_adj_groups) are applied in one
-// pass over the tile, each thread holding its pairs (one position) or quads (two
-// positions) in registers from one LDS read to one LDS write, with one barrier per
-// group instead of one per op.
+// Group passes: the ops of one group (at most kAdjGroupMax consecutive ops on at
+// most two tile positions, build_adj_groups) are applied in one pass over the
+// tile, each thread holding its pairs (one position) or quads (two positions)
+// in registers from one LDS read to one LDS write, with one barrier per group
+// instead of one per op.
 
 // 2 x 2 matrix (g00 g01; g10 g11) on the pair (x0, x1).
 __device__ inline void adj_g2(float2 g00, float2 g01, float2 g10, float2 g11, float2& x0, float2& x1) {
@@ -570,6 +570,180 @@ __global__ void __launch_bounds__(kSvwThreads) adj_fwd_group_kernel(AdjArgs a, c
   }
 }
 
+// Backward window with unitary inserted operators, one group pass per group (in
+// reverse): each thread holds psi and lambda at its pairs or quads, applies the
+// group's A_k^dag last op first, and sums each rotation's
+// Im <lambda_{k-1}|P|psi_{k-1}> over its amplitudes, then over the wavefront
+// (shuffles, no barrier); after the group's barrier the four wavefronts' sums are
+// added in a fixed order (staging double-buffered by group parity).
+template <int NP>
+__global__ void __launch_bounds__(kSvwThreads) adj_bwd_group_kernel(AdjArgs a, const AdjOp* __restrict__ ops) {
+  constexpr int PPT = 1 << (NP - 9);
+  constexpr uint32_t nt = 1u << NP;
+  constexpr int NPR = (nt >> 1) / kSvwThreads, NQD = (nt >> 2) / kSvwThreads;
+  extern __shared__ floatx4_t adj_lds4[];
+  float2* T0 = reinterpret_cast<float2*>(adj_lds4);      // psi
+  float2* T1 = T0 + nt;                                  // lambda
+  float2* Gb = T1 + nt;                                  // [n_ops][16] adjoint matrices
+  double* red = reinterpret_cast<double*>(Gb + 16 * a.n_ops);   // [2][4][kAdjGroupMax]
+  double* acc = red + 2 * 4 * 33;                        // [n_ops] (the same layout bound as the per-op kernel)
+  floatx4_t* T04 = reinterpret_cast<floatx4_t*>(T0);
+  floatx4_t* T14 = reinterpret_cast<floatx4_t*>(T1);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tb = a.n - NP;
+  const int64_t total = a.n_jobs << tb;
+  const int64_t per = (total + gridDim.x - 1) / gridDim.x;
+  const int64_t b0 = (int64_t)blockIdx.x * per, b1 = b0 + per < total ? b0 + per : total;
+  for (int i = tid; i < a.n_ops; i += kSvwThreads) acc[i] = 0.0;
+  const uint32_t lo = pair_lo(a.P), pt2 = swz(2u * tid);
+  int64_t last_job = -1;
+  for (int64_t bid = b0; bid < b1; ++bid) {
+    const int64_t job = bid >> tb;
+    if (job != last_job) {
+      const int traj = a.traj_base + (int)job;
+      for (int i = tid; i < 16 * a.n_ops; i += kSvwThreads) {
+        const AdjOp& op = ops[i >> 4];
+        const int e = i & 15, d2 = op.kind == kSvOpGate1 ? 4 : 16;
+        Gb[i] = e < d2 ? a.Ad[((int64_t)traj * a.G + op.gate) * 16 + op.idx[e]] : make_float2(0.f, 0.f);
+      }
+      last_job = job;
+    }
+    const uint32_t base = deposit_other((uint32_t)(bid & (((int64_t)1 << tb) - 1)), a.other);
+    float2* Lg = a.lam + (job << a.n) + base;
+    {
+      floatx4_t v[PPT], w[PPT];
+      load_pairs<NP>(a.psi_in + (job << a.n) + base, a.P, lo, v);
+      load_pairs<NP>(Lg, a.P, lo, w);
+#pragma unroll
+      for (int i = 0; i < PPT; ++i) {
+        lds_put_pair(T04, pt2, i, v[i]);
+        lds_put_pair(T14, pt2, i, w[i]);
+      }
+    }
+    __syncthreads();
+    for (int gi = a.n_groups - 1; gi >= 0; --gi) {
+      const uint4 gd = reinterpret_cast<const uint4*>(a.groups)[gi];
+      const int nq = (int)(gd.x & 0xffu), pa = (int)((gd.x >> 8) & 0xffu), pb = (int)((gd.x >> 16) & 0xffu);
+      const int cnt = (int)((gd.x >> 24) & 0xffu), first = (int)gd.y;
+      double* rs = red + (gi & 1) * 4 * kAdjGroupMax + wave * kAdjGroupMax;   // wavefront sums, by op
+      if (nq == 1) {
+        const uint32_t pt = swz(ins0(tid, pa)), so = swz(1u << pa);
+        float2 S0[NPR], S1[NPR], L0[NPR], L1[NPR];
+#pragma unroll
+        for (int i = 0; i < NPR; ++i) {
+          const uint32_t l0 = pt ^ swz(ins0(kSvwThreads * i, pa));
+          S0[i] = T0[l0];
+          S1[i] = T0[l0 ^ so];
+          L0[i] = T1[l0];
+          L1[i] = T1[l0 ^ so];
+        }
+#pragma unroll 1
+        for (int j = cnt - 1; j >= 0; --j) {
+          const int k = first + j;
+          const uint4 w = reinterpret_cast<const uint4*>(ops)[2 * k];
+          const int axis = (int)(int8_t)((w.x >> 24) & 0xffu);
+          const float2* g = Gb + 16 * k;
+          const float2 g00 = g[0], g01 = g[1], g10 = g[2], g11 = g[3];
+          float rot = 0.f;
+#pragma unroll
+          for (int i = 0; i < NPR; ++i) {
+            adj_g2(g00, g01, g10, g11, S0[i], S1[i]);
+            adj_g2(g00, g01, g10, g11, L0[i], L1[i]);
+            if (axis >= 0) rot += adj_rot_term(axis, L0[i], L1[i], S0[i], S1[i]);
+          }
+          if (axis >= 0) {
+            const float t = adj_wave_sum(rot);
+            if (lane == 0) rs[j] = (double)t;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < NPR; ++i) {
+          const uint32_t l0 = pt ^ swz(ins0(kSvwThreads * i, pa));
+          T0[l0] = S0[i];
+          T0[l0 ^ so] = S1[i];
+          T1[l0] = L0[i];
+          T1[l0 ^ so] = L1[i];
+        }
+      } else {
+        const uint32_t pt = swz(ins0(ins0(tid, pa), pb)), s1 = swz(1u << pa), s2 = swz(1u << pb);
+        float2 S[NQD][4], L[NQD][4];
+#pragma unroll
+        for (int i = 0; i < NQD; ++i) {
+          const uint32_t lb = pt ^ swz(ins0(ins0(kSvwThreads * i, pa), pb));
+          const uint32_t off[4] = {lb, lb ^ s1, lb ^ s2, lb ^ s1 ^ s2};
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            S[i][x] = T0[off[x]];
+            L[i][x] = T1[off[x]];
+          }
+        }
+#pragma unroll 1
+        for (int j = cnt - 1; j >= 0; --j) {
+          const int k = first + j;
+          const uint4 w = reinterpret_cast<const uint4*>(ops)[2 * k];
+          const int kind = (int)(w.x & 0xffu), p0 = (int)((w.x >> 8) & 0xffu);
+          const int axis = (int)(int8_t)((w.x >> 24) & 0xffu);
+          const float2* g = Gb + 16 * k;
+          if (kind == kSvOpGate1) {
+            const float2 g00 = g[0], g01 = g[1], g10 = g[2], g11 = g[3];
+            const bool hi = p0 != pa;   // the op's qubit is quad bit 1
+            float rot = 0.f;
+#pragma unroll
+            for (int i = 0; i < NQD; ++i) {
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                // pair h: quad entries (2h, 2h + 1) on bit 0, (h, h + 2) on bit 1
+                const int e0 = hi ? h : 2 * h, e1 = hi ? h + 2 : 2 * h + 1;
+                adj_g2(g00, g01, g10, g11, S[i][e0], S[i][e1]);
+                adj_g2(g00, g01, g10, g11, L[i][e0], L[i][e1]);
+                if (axis >= 0) rot += adj_rot_term(axis, L[i][e0], L[i][e1], S[i][e0], S[i][e1]);
+              }
+            }
+            if (axis >= 0) {
+              const float t = adj_wave_sum(rot);
+              if (lane == 0) rs[j] = (double)t;
+            }
+          } else {
+            float2 gm[4][4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+              for (int c = 0; c < 4; ++c) gm[r][c] = g[r * 4 + c];
+            const bool sw = p0 != pa;
+#pragma unroll
+            for (int i = 0; i < NQD; ++i) {
+              adj_g4(gm, sw, S[i]);
+              adj_g4(gm, sw, L[i]);
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < NQD; ++i) {
+          const uint32_t lb = pt ^ swz(ins0(ins0(kSvwThreads * i, pa), pb));
+          const uint32_t off[4] = {lb, lb ^ s1, lb ^ s2, lb ^ s1 ^ s2};
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+            T0[off[x]] = S[i][x];
+            T1[off[x]] = L[i][x];
+          }
+        }
+      }
+      __syncthreads();   // the group's tiles and wavefront sums are complete
+      if (tid < cnt && ((gd.z >> tid) & 1u)) {
+        const double* r0 = red + (gi & 1) * 4 * kAdjGroupMax;
+        acc[first + tid] += r0[tid] + r0[kAdjGroupMax + tid] + r0[2 * kAdjGroupMax + tid] + r0[3 * kAdjGroupMax + tid];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PPT; ++i)
+      *reinterpret_cast<floatx4_t*>(Lg + (lo | pair_hi<NP>(a.P, i))) = lds_get_pair(T14, pt2, i);
+    __syncthreads();   // every thread has read its part of lambda, and acc is complete
+  }
+  __syncthreads();
+  double* out = a.wg_acc + (int64_t)blockIdx.x * a.n_ops;
+  for (int i = tid; i < a.n_ops; i += kSvwThreads) out[i] = acc[i];
+}
+
 // The diagonal of O = sum_t c_t Z_a Z_b over the 2^n basis states (once per call).
 __global__ void adj_zz_diag_kernel(int n, const int32_t* __restrict__ zq, const double* __restrict__ zc, int n_terms,
                                    double* __restrict__ diag) {
@@ -668,10 +842,10 @@ AdjKernel adj_kernel(int mode, const AdjArgs& a) {
   if (!tile) return mode == 0 ? adj_window_kernel<0> : (mode == 1 ? adj_window_kernel<1> : adj_window_kernel<2>);
   if (mode == 0)
     return a.np == 10 ? adj_fwd_group_kernel<10> : (a.np == 11 ? adj_fwd_group_kernel<11> : adj_fwd_group_kernel<12>);
-  // gate adjoints: one op per pass (the N sums need every op's own amplitudes); gradients of
-  // circuits of these sizes run on the cluster windows
-  return a.np == 10 ? adj_bwd_tile_kernel<10, true>
-                    : (a.np == 11 ? adj_bwd_tile_kernel<11, true> : adj_bwd_tile_kernel<12, true>);
+  if (a.want_n)   // gate adjoints: one op per pass (the N sums need every op's own amplitudes)
+    return a.np == 10 ? adj_bwd_tile_kernel<10, true>
+                      : (a.np == 11 ? adj_bwd_tile_kernel<11, true> : adj_bwd_tile_kernel<12, true>);
+  return a.np == 10 ? adj_bwd_group_kernel<10> : (a.np == 11 ? adj_bwd_group_kernel<11> : adj_bwd_group_kernel<12>);
 }
 }  // namespace
 

@@ -138,6 +138,28 @@ size_t cluster_fixed_bytes(const Plan& p, const AdjSpec& S, int64_t E, size_t n_
          align256((size_t)std::min<int64_t>(E, kAdjChunkMax) * 64 * 8) + ((size_t)1 << 20);
 }
 
+// From this many trajectories on small circuits take the windows of single gates: their
+// states are a tile or less, and a cluster's 16 x 16 product and derivatives in 64 bits, once
+// per trajectory, cost more than its gates one by one; clusters have fewer launches, so that
+// the lines lie at numbers of trajectories.  Time of windows over that of clusters, ansatz of
+// L layers (3 L gates a qubit):
+//   values, 3072 / 8192 trajectories: 8 qubits L = 1 1.02 / 0.86, 11 qubits L = 4 1.06 / 0.92,
+//     L = 8 8 qubits 1.11 / 0.94, 11 qubits 1.32 / 1.10; 12 qubits L = 1 1.20 / 1.12
+//   gradients, 1536 / 2048 / 8192: 8 qubits L = 1 1.11 / 1.00 / 0.73, 9 qubits L = 4 1.11 / 1.00
+//     / 0.87, 10 qubits L = 2 0.97 / 0.91 / 0.73, L = 8 1.14 / 1.09 / 0.88, 11 qubits L = 2 1.07
+//     / 1.01 / 0.90, L = 4 1.15 / 1.11 / 0.99, 12 qubits L = 1 1.43 / 1.38 / 1.24
+//   with damping the windows of a gradient recompute the states gate by gate: 2048 / 8192: 8
+//     qubits L = 1 1.03 / 0.82, L = 2 1.55 / 1.42, 9 qubits L = 1 (4096) 1.08 / 1.01
+int64_t windows_from(const Plan& p, bool grad) {
+  constexpr int64_t never = INT64_MAX;
+  if (p.n > 11) return never;
+  const size_t per_qubit = p.adj_cl.ops.size() / (size_t)p.n;     // gates
+  if (!grad) return per_qubit < 16 ? 3072 : (p.n < 11 ? 6144 : never);
+  if (!p.inserted_unitary) return p.n == 8 && per_qubit < 4 ? 2560 : never;
+  if (p.n == 11) return per_qubit < 8 ? 2560 : never;
+  return p.n < 10 ? 1920 : (per_qubit < 16 ? 1536 : 3072);
+}
+
 // The least workspace of a call: one trajectory a chunk.  The cluster form keeps up to one
 // checkpoint more than the windows of single gates; a smaller workspace goes to those.
 size_t cluster_min_bytes(const Plan& p, const AdjSpec& S, const ptsbe::AdjClSchedule& sched, int64_t E, bool grad,
@@ -377,7 +399,7 @@ ptsbe_status_t ptsbe_contract_adjoint(ptsbe_plan_t plan, const ptsbe_adjoint_spe
   const bool want_grad = d_grad != nullptr && S.n_params > 0;
   const bool want_adj = d_gate_adj != nullptr;
   const bool backward = want_grad || want_adj;
-  if (!want_adj && p->adj_cl.ok &&
+  if (!want_adj && p->adj_cl.ok && E < windows_from(*p, want_grad) &&
       workspace_bytes >= cluster_min_bytes(*p, S, p->adj_cl, E, want_grad, d_traj_value != nullptr))
     return run_clusters(*p, S, p->adj_cl, d_kraus_idx, E, d_weights, d_theta, d_psi_bar, d_traj_value, d_value, d_grad,
                         d_workspace, workspace_bytes, s);
@@ -397,6 +419,12 @@ ptsbe_status_t ptsbe_contract_adjoint(ptsbe_plan_t plan, const ptsbe_adjoint_spe
       ptsbe::AdjOp& op = ops[(size_t)(wd.op_off + k)];
       op.axis = (int8_t)(want_grad && S.gate_param[(size_t)op.gate] >= 0 ? S.gate_axis[(size_t)op.gate] : -1);
       op.nslot = want_adj ? k : -1;
+    }
+    for (int gi = 0; gi < wd.n_groups; ++gi) {
+      ptsbe::AdjGroup& gr = groups[(size_t)(wd.group_off + gi)];
+      gr.rot_mask = 0;
+      for (int j = 0; j < gr.n; ++j)
+        if (ops[(size_t)(wd.op_off + gr.first + j)].axis >= 0) gr.rot_mask |= 1u << j;
     }
     width[(size_t)w] = wd.n_ops + (want_adj ? 32 * wd.n_ops : 0);
     tot_off[(size_t)w + 1] = tot_off[(size_t)w] + width[(size_t)w];

@@ -185,7 +185,8 @@ constexpr int kAdjGroupMax = 8;
 struct AdjGroup {
   int8_t nq, pa, pb, n;           // positions used, the group's tile positions, op count
   int32_t first;                  // index of the group's first op in the window
-  int32_t pad[2];
+  uint32_t rot_mask;              // bit j: op first + j is a differentiated rotation
+  int32_t pad;
 };
 static_assert(sizeof(AdjGroup) == 16, "AdjGroup is read as four dwords");
 struct AdjArgs {
