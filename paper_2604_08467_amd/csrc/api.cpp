@@ -96,6 +96,27 @@ bool part_is_one_sweep(const ptsbe::PartPlan& pp) {
   return part_uses_vm(pp) && (int64_t)pp.steps.size() <= ptsbe::part_vm_max_steps(pp.peak);
 }
 
+// A last step of an LDS sweep that raises the rank may write its output straight to HBM.
+bool direct_step(const ptsbe::AbsorbStep& st) { return st.nK <= 1 && st.nN > st.nK && st.nK + st.nN <= 4; }
+
+// Steps before the tail of a sweep that comes to rank 12 only at its end, by a step that can
+// write its output to HBM.  With many jobs those are a launch of their own, beside four or
+// more other workgroups a CU; in one launch with the tail they have the LDS of rank 12
+// throughout, two workgroups a CU.  0: no such tail, or fewer than 24 steps before it (the
+// tensors' way through HBM costs as much as about 17).  A call of 76 steps, one after the cut, in
+// one launch and in two: 2029 jobs 1.10 and 0.98 ms, 2672 jobs 1.49 and 1.32; of 70 steps, four
+// after the cut: 777 jobs 0.47 and 0.49, 1126 jobs 0.66 and 0.64, 2903 jobs 1.50 and 1.44.
+constexpr int64_t kVmTailJobs = 1024;
+int vm_tail(const ptsbe::PartPlan& pp) {
+  const int n = (int)pp.steps.size();
+  int k = 0;
+  while (k < n && pp.steps[(size_t)k].rC < ptsbe::kVmMaxRank) ++k;
+  if (k + 1 >= n || k < 24 || !direct_step(pp.steps[(size_t)k])) return 0;
+  for (int i = k + 1; i < n; ++i)
+    if (pp.steps[(size_t)i].rA != ptsbe::kVmMaxRank || pp.steps[(size_t)i].rC != ptsbe::kVmMaxRank) return 0;
+  return k + 1;
+}
+
 size_t part_scratch_per_job(const ptsbe::PartPlan& pp) {
   if (pp.steps.empty() || part_is_one_sweep(pp)) return 0;
   return 2 * ((size_t)8 << pp.peak);
@@ -110,9 +131,6 @@ size_t join_traj_bytes(const ptsbe::BatchPlan& bp) {
     layout = std::max(layout, ptsbe::qform_theta_bytes((int)bp.xT.size(), lkb));
   return ((size_t)8 << bp.right.labels.size()) + layout + part_scratch_per_job(bp.right);
 }
-
-// A last step of an LDS sweep that raises the rank may write its output straight to HBM.
-bool direct_step(const ptsbe::AbsorbStep& st) { return st.nK <= 1 && st.nN > st.nK && st.nK + st.nN <= 4; }
 
 // Sweeps with a job a lane pay from this many jobs on: 15 steps take them 30 us and 0.2 us
 // a thousand jobs, part_vm_kernel 30 us and 0.55 us; below, their wavefronts leave SIMDs
@@ -167,6 +185,26 @@ ptsbe_status_t timed_part_vm(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::Ab
     }
     p.vm_flops += f * (double)n_jobs;
   }
+  return PTSBE_OK;
+}
+
+// One step in HBM, with profiling as for the sweeps: bytes, and at level 2 its time.
+ptsbe_status_t timed_absorb(Plan& p, const ptsbe::AbsorbStep& st, const ptsbe::AbsorbStep* d_step,
+                            const ptsbe::GateCtx& g, int64_t n_jobs, const int32_t* job_traj, int32_t traj_base,
+                            const uint64_t* job_prefix, const float2* A, float2* C, hipStream_t s) {
+  std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
+  if (p.profile >= 2) {
+    HIP_TRY(hipEventCreate(&ev.first));
+    HIP_TRY(hipEventCreate(&ev.second));
+    HIP_TRY(hipEventRecord(ev.first, s));
+  }
+  HIP_TRY(ptsbe::launch_absorb_global(st, d_step, g, n_jobs, job_traj, traj_base, job_prefix, p.NW, A, C, s));
+  if (p.profile >= 2) {
+    HIP_TRY(hipEventRecord(ev.second, s));
+    p.sweep_evs.push_back(ev);
+    ++p.sweep_launches;
+  }
+  if (p.profile) p.sweep_bytes += (double)n_jobs * 8.0 * (std::ldexp(1.0, st.rA) + std::ldexp(1.0, st.rC));
   return PTSBE_OK;
 }
 
@@ -247,9 +285,26 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
     else HIP_TRY(ptsbe::launch_fill_one(out, n_jobs, s));
     return PTSBE_OK;
   }
-  if (part_is_one_sweep(pp))
+  if (part_is_one_sweep(pp)) {
+    const int cut = n_jobs >= kVmTailJobs ? vm_tail(pp) : 0;
+    if (cut > 0) {
+      const ptsbe_status_t st = timed_part_vm(p, pp, d_steps, 0, cut, ptsbe::kVmMaxRank, g, n_jobs, job_traj, traj_base,
+                                              job_prefix, init, out, out_rank, s);
+      if (st != PTSBE_OK) return st;
+      const ptsbe::AbsorbStep& last = pp.steps.back();
+      if (cut + 1 == (int)pp.steps.size() && last.nK == last.nN && std::equal(last.kpos, last.kpos + last.nK, last.npos)) {
+        return timed_absorb(p, last, d_steps + cut, g, n_jobs, job_traj, traj_base, job_prefix, out, out, s);
+      }
+      ptsbe::InitArgs from;            // each workgroup has its tensor in LDS before it writes it
+      from.Vprev = out;
+      from.stride = (int64_t)1 << out_rank;
+      from.r0 = out_rank;
+      return timed_part_vm(p, pp, d_steps, cut, (int)pp.steps.size() - cut, pp.peak, g, n_jobs, job_traj, traj_base,
+                           job_prefix, from, out, out_rank, s);
+    }
     return timed_part_vm(p, pp, d_steps, 0, (int)pp.steps.size(), pp.peak, g, n_jobs, job_traj, traj_base, job_prefix,
                          init, out, out_rank, s);
+  }
   const size_t mark = ar.used;
   float2* b0 = (float2*)ar.take((size_t)n_jobs * ((size_t)8 << pp.peak));
   float2* b1 = (float2*)ar.take((size_t)n_jobs * ((size_t)8 << pp.peak));
@@ -405,23 +460,10 @@ ptsbe_status_t run_part(Plan& p, const ptsbe::PartPlan& pp, const ptsbe::AbsorbS
       }
     }
     float2* C = (si == last_nf) ? out : (A == b0 ? b1 : b0);
-    std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
-    if (p.profile >= 2) {
-      HIP_TRY(hipEventCreate(&ev.first));
-      HIP_TRY(hipEventCreate(&ev.second));
-      HIP_TRY(hipEventRecord(ev.first, s));
-    }
-    HIP_TRY(ptsbe::launch_absorb_global(pp.steps[i], d_steps + i, g, cur_n, cur_traj, traj_base, job_prefix,
-                                        p.NW, A, C, s));
-    if (p.profile >= 2) {
-      HIP_TRY(hipEventRecord(ev.second, s));
-      p.sweep_evs.push_back(ev);
-      ++p.sweep_launches;
-    }
+    const ptsbe_status_t st = timed_absorb(p, pp.steps[i], d_steps + i, g, cur_n, cur_traj, traj_base, job_prefix, A, C, s);
+    if (st != PTSBE_OK) return st;
     A = C;
     cur_rank = pp.steps[i].rC;
-    if (p.profile) p.sweep_bytes += (double)cur_n * 8.0 *
-                                    (std::ldexp(1.0, pp.steps[i].rA) + std::ldexp(1.0, pp.steps[i].rC));
   }
   if (cur_n != n_jobs) return fail(PTSBE_ERR_DEVICE, "subtree reuse: the last level does not hold every job");
   if (A != out) HIP_TRY(ptsbe::launch_copy(A, out, n_jobs << out_rank, s));

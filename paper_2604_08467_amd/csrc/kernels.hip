@@ -199,7 +199,7 @@ __host__ __device__ constexpr int vm_gate_entries(int J) { return J > 32 ? 16 * 
 constexpr int kVmLdsSteps = 16;
 
 template <bool LS>
-__global__ void __launch_bounds__(512, 4) part_vm_kernel(const AbsorbStep* __restrict__ steps, int n_steps,
+__global__ void __launch_bounds__(LS ? 512 : 256, 4) part_vm_kernel(const AbsorbStep* __restrict__ steps, int n_steps,
                                                       int buf_elems, int J, GateCtx g, int64_t n_jobs,
                                                       const int32_t* __restrict__ job_traj, int32_t traj_base,
                                                       const uint64_t* __restrict__ job_prefix, int NW,
@@ -2155,22 +2155,28 @@ hipError_t launch_init_gather(const InitArgs& init, int64_t n_jobs, const uint64
 
 namespace {
 // Workgroup of an LDS sweep whose largest tensor in LDS has rank `peak`.
-struct VmShape { int J, stride, threads; size_t lds; };
-VmShape vm_shape(int peak, int n_steps, int NW) {
+// Jobs of rank 11 up to which 512 threads take one, with its steps' descriptions in LDS (LS):
+// two such workgroups a CU.  Beyond, four of 256 threads are the better use of a CU: 56 steps of
+// 512 jobs 82 and 89 us, of 1024 129 and 94, of 4096 373 and 265.  At rank 12 LDS holds two
+// workgroups either way and LS is faster at every number (76 steps, 4096 jobs: 566 and 633).
+constexpr int kVmFewJobs = 512;
+struct VmShape { int J, stride, threads; bool ls; size_t lds; };
+VmShape vm_shape(int peak, int n_steps, int64_t n_jobs, int NW) {
   const int buf = 1 << (peak > 0 ? peak : 0);
   VmShape v;
   // small tensors: up to 64 jobs share a 256-thread workgroup (2048 entries of
   // tensors in the A and C buffers; peak is the largest rank held in LDS: with
-  // direct, the last step's larger output goes to HBM); one job per workgroup of 512
-  // threads from 2^11 entries on
+  // direct, the last step's larger output goes to HBM); one job per workgroup from
+  // 2^11 entries on
   v.J = buf >= 2048 ? 1 : (2048 / buf > kVmMaxJobs ? kVmMaxJobs : 2048 / buf);
-  v.threads = v.J > 1 ? 256 : 512;
+  v.ls = peak >= 12 || (v.J == 1 && n_jobs <= kVmFewJobs);
+  v.threads = v.ls ? 512 : 256;
   // jobs' tensors one entry apart beyond their size: the same index of
   // neighbouring jobs falls in different LDS banks
   v.stride = v.J > 1 ? buf + 1 : buf;
-  const int gates = v.J == 1 ? 16 * kVmLdsSteps : vm_gate_entries(v.J);
+  const int gates = v.ls ? 16 * kVmLdsSteps : vm_gate_entries(v.J);
   v.lds = (size_t)(2 * v.J * v.stride + gates) * sizeof(float2) + (size_t)n_steps * sizeof(int4) +
-          (size_t)v.J * NW * sizeof(uint64_t) + (v.J == 1 ? kVmLdsSteps * sizeof(AbsorbStep) : 0);
+          (size_t)v.J * NW * sizeof(uint64_t) + (v.ls ? kVmLdsSteps * sizeof(AbsorbStep) : 0);
   return v;
 }
 constexpr size_t kVmLdsMax = 160 * 1024 - 1024;   // of a workgroup, without the kernel's static arrays
@@ -2180,7 +2186,7 @@ constexpr size_t kVmLdsMax = 160 * 1024 - 1024;   // of a workgroup, without the
 // jobs) not: the fewest steps over all ranks up to it.
 int part_vm_max_steps(int peak) {
   size_t most = 0;
-  for (int r = 0; r <= peak; ++r) most = std::max(most, vm_shape(r, 0, kMaxQubits / 64).lds);
+  for (int r = 0; r <= peak; ++r) most = std::max(most, vm_shape(r, 0, 1, kMaxQubits / 64).lds);
   return most < kVmLdsMax ? (int)((kVmLdsMax - most) / sizeof(int4)) : 0;
 }
 
@@ -2188,10 +2194,10 @@ hipError_t launch_part_vm(const AbsorbStep* d_steps, int n_steps, int peak, Gate
                           const int32_t* job_traj, int32_t traj_base, const uint64_t* job_prefix, int NW,
                           const InitArgs& init, float2* out, int out_rank, int direct, hipStream_t stream) {
   if (n_jobs <= 0) return hipSuccess;
-  const VmShape v = vm_shape(peak, n_steps, NW);
+  const VmShape v = vm_shape(peak, n_steps, n_jobs, NW);
   if (peak > kVmMaxRank || v.lds > kVmLdsMax) return hipErrorInvalidValue;
   const dim3 grid(grid_blocks((n_jobs + v.J - 1) / v.J));
-  if (v.J == 1)
+  if (v.ls)
     hipLaunchKernelGGL(part_vm_kernel<true>, grid, dim3(v.threads), v.lds, stream, d_steps, n_steps, v.stride, v.J, g,
                        n_jobs, job_traj, traj_base, job_prefix, NW, init, out, out_rank, direct);
   else
