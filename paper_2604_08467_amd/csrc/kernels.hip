@@ -774,7 +774,8 @@ __global__ void __launch_bounds__(256) ketjoin_gemv_tiled_kernel(JoinArgs a, Gem
         if (((j0 + j) >> s) & 1) { li += 1 << g.w_of[8 + s]; orj += g.o_read[8 + s]; }
 #pragma unroll
       for (int r = 0; r < ROWS; ++r) {
-        const float pi = acc[j][r].x * acc[j][r].x + acc[j][r].y * acc[j][r].y;
+        // the roundings spelled out: the same for every JB
+        const float pi = fmaf(acc[j][r].x, acc[j][r].x, __fmul_rn(acc[j][r].y, acc[j][r].y));
         if constexpr (JB == 16) outs[r][li] = pi;
         else if (a.pop) a.pop[e * nout + obase + orj + obr[r]] = pi;
         if (a.amp) a.amp[e * nout + obase + orj + obr[r]] = acc[j][r];
