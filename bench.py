@@ -26,9 +26,9 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3
 BF16_MFMA_PEAK_TFLOPS = 2500.0
 # the join kernel version that profiles/join_traffic.txt must name to be used
 SWEEP_KERNEL_TAG = "absorb_global_kernel<NK> single HBM sweep steps, 4 kept indices per thread"
-JOIN_KERNEL_TAG = "qform_mfma_kernel<32,NC> bilinear slots"
+JOIN_KERNEL_TAG = "qform_mfma_kernel<32,NC> bilinear slots, unrolled chunks"
 # the LDS-sweep kernel version that profiles/lds_sweep_counters_brickwork50_b5.txt must name
-VM_KERNEL_TAG = "part_lanes_kernel from 32768 jobs of rank <= 6, part_vm_kernel with steps in LDS for one job a workgroup"
+VM_KERNEL_TAG = "part_lanes_kernel from 32768 jobs of rank 4 and 5, part_vm_kernel with steps in LDS for one job a workgroup"
 
 
 def _oracle_shots_worker(circuit, kraus_row, traj, batch_sizes, seed, budget_s):

@@ -1,4 +1,4 @@
-// Cluster form of the adjoint passes (tiles of 8..12 qubits with qubit 0 at tile bit
+// Cluster form of the adjoint passes (tiles of 8..11 qubits with qubit 0 at tile bit
 // 0, windows from build_adj_clusters).  A window's gates run as a few clusters, each
 // the product of up to 13 gates on four tile positions: a 16 x 16 complex matrix per
 // trajectory, built once per call in 64 bits and rounded once, applied to the LDS tile
@@ -453,9 +453,11 @@ __device__ inline void cl_range(const AdjClArgs& a, int64_t& job, uint32_t& b0, 
 
 // Forward window: psi_out = U_C .. U_1 psi_in per tile.  T double (value-only calls): the
 // window's arithmetic and tile in 64 bits, the states between windows in 32, so that the
-// value's rounding error is the windows' stores alone (a value near zero, the usual one of
-// a deep circuit, is a difference of large terms: in FP32 its relative error reached 1e-5
-// where the gate-by-gate pass had 4e-6; now below 1e-6).
+// value's rounding error is the windows' stores alone.  Calls with a gradient take T float and
+// return that pass's value.  Ansatz circuits of 8 to 16 qubits and 2 to 8 layers, error of the
+// value per ZZ term (root mean square, worst of 252): gate by gate 9.6e-8 and 2.4e-7, float
+// 7.0e-9 and 2.8e-8, double 7.3e-10; a value near zero, the usual one of a deep circuit, is a
+// difference of large terms: relative error 1.0e-5 gate by gate, 1.3e-6 float.
 template <int NP, typename T>
 __global__ void __launch_bounds__(256) adj_cl_fwd_kernel(AdjClArgs a, const typename ClNum<T>::C* __restrict__ Uall) {
   typedef typename ClNum<T>::C C;

@@ -256,11 +256,11 @@ __device__ inline float adj_rot_term(int axis, float2 l0, float2 l1, float2 s0, 
 // unitary): per tile, psi (the state after the window) and lambda in LDS; for each
 // op, last first, one pass applies A_k^dag to both at the op's pairs or quads and
 // accumulates, in registers, the rotation derivative Im <lambda_{k-1}|P|psi_{k-1}>
-// and (WN) the gate adjoint N_ab = sum lambda_{k-1,a} conj(psi_{k-1,b}) from the
+// and (ops with a slot for it) the gate adjoint N_ab = sum lambda_{k-1,a} conj(psi_{k-1,b}) from the
 // same amplitudes.  Per op the thread sums are reduced over each wavefront with
 // shuffles, the four wavefronts' sums are added in a fixed order after the op's
 // barrier (double-buffered by op parity) into FP64 workgroup accumulators.
-template <int NP, bool WN>
+template <int NP>
 __global__ void __launch_bounds__(kSvwThreads) adj_bwd_tile_kernel(AdjArgs a, const AdjOp* __restrict__ ops) {
   constexpr int PPT = 1 << (NP - 9);
   constexpr uint32_t nt = 1u << NP;
@@ -310,14 +310,12 @@ __global__ void __launch_bounds__(kSvwThreads) adj_bwd_tile_kernel(AdjArgs a, co
       const uint4 wd = reinterpret_cast<const uint4*>(ops)[2 * k];
       const int kind = (int)(wd.x & 0xffu), p0 = (int)((wd.x >> 8) & 0xffu), p1 = (int)((wd.x >> 16) & 0xffu);
       const int axis = (int)(int8_t)((wd.x >> 24) & 0xffu), nslot = (int)wd.z;
-      const bool take_n = WN && nslot >= 0;
+      const bool take_n = nslot >= 0;
       const float2* g = Gb + 16 * k;
       float rot = 0.f;
       float nac[32];
-      if (WN) {
 #pragma unroll
-        for (int i = 0; i < 32; ++i) nac[i] = 0.f;
-      }
+      for (int i = 0; i < 32; ++i) nac[i] = 0.f;
       int cnt = 0;   // sums this op reduces: rotation first, then 2 d^2 entries of N
       if (kind == kSvOpGate1) {
         const float2 g00 = g[0], g01 = g[1], g10 = g[2], g11 = g[3];
@@ -843,8 +841,8 @@ AdjKernel adj_kernel(int mode, const AdjArgs& a) {
   if (mode == 0)
     return a.np == 10 ? adj_fwd_group_kernel<10> : (a.np == 11 ? adj_fwd_group_kernel<11> : adj_fwd_group_kernel<12>);
   if (a.want_n)   // gate adjoints: one op per pass (the N sums need every op's own amplitudes)
-    return a.np == 10 ? adj_bwd_tile_kernel<10, true>
-                      : (a.np == 11 ? adj_bwd_tile_kernel<11, true> : adj_bwd_tile_kernel<12, true>);
+    return a.np == 10 ? adj_bwd_tile_kernel<10>
+                      : (a.np == 11 ? adj_bwd_tile_kernel<11> : adj_bwd_tile_kernel<12>);
   return a.np == 10 ? adj_bwd_group_kernel<10> : (a.np == 11 ? adj_bwd_group_kernel<11> : adj_bwd_group_kernel<12>);
 }
 }  // namespace

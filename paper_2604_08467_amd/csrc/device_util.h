@@ -48,10 +48,12 @@ __device__ inline uint32_t deposit_tile(uint32_t t, const int* P, int np, int r)
   return out;
 }
 
-// UPV merge of one (trajectory, gate): entry `lane` (< 16) of the merged matrix, by 16
-// neighbouring lanes together (FP32 products, each entry's terms in ascending order).  A
-// lane per matrix held two of them in scratch: 48 trajectories of a 25-qubit grid (240
-// gates) 57 us, 64 of a 10-qubit chain (36 gates) 29 us, now 5 us; bound by
+// UPV merge of one (trajectory, gate): entry `lane` = threadIdx.x & 15 of the merged matrix
+// (FP32 products, each entry's terms in ascending order).  The 16 lanes of a group exchange
+// entries: all of them have to be active, with the same trajectory and gate.  A lane per
+// matrix held two of them in scratch: 48 trajectories of a 25-qubit grid (240 gates) 57 us,
+// 64 of a 10-qubit chain (36 gates) 29 us, now 5 us: the chain of dependent reads of sites,
+// choices and operators.
 __device__ inline float2 merge_gate(const GateCtx& g, int gate, int traj, int lane) {
   const DeviceGate* G = g.gates + gate;
   const int sb = G->site_begin, se = G->site_end;

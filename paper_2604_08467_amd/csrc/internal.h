@@ -50,7 +50,8 @@ inline unsigned grid_blocks(int64_t blocks) {
 constexpr int kMaxQubits = 1024;
 constexpr int kSvMaxQubits = 30;   // statevector method and adjoint pass
 // Runs of steps whose tensors fit 2^12 c64 are swept in LDS by one launch (two 32 KB
-// buffers, two workgroups of 512 threads per CU).  With 2^11, and only a part's leading
+// buffers; two workgroups of 512 threads per CU for up to some 430 steps, whose table is in
+// LDS too, one beyond).  With 2^11, and only a part's leading
 // steps, the per-trajectory parts of the 50-qubit chain, which move between ranks 10 and
 // 12, went step by step through HBM: 928 launches of 10 us per call at batches of 5 qubits,
 // now 104 of 17 us and 1 ms more in the sweeps (62.2 -> 55.4 ms); at batches of 10 qubits

@@ -225,6 +225,9 @@ __global__ void __launch_bounds__(64, 3) part_lanes_kernel(const AbsorbStep* __r
 
 }  // namespace
 
+// Ranks 4 and 5, those of the per-element parts of chains of depth 5 and 6.  At rank 6 the
+// tensor alone would take 128 of a lane's 168 registers (three wavefronts a SIMD); rank 3 and
+// below were not tried.
 int lane_sweep_rank(const AbsorbStep* st, int n, int r0, bool* raise) {
   if (r0 < 4 || r0 > 5 || n < 1) return 0;
   *raise = false;
