@@ -6,7 +6,8 @@
 // statevector through LDS gate windows of at most 11 qubits; the state after
 // every window is kept as a checkpoint.  Values and angle gradients of circuits of
 // at least 8 qubits run on windows of gate clusters (run_clusters); gate-tensor
-// adjoints and smaller circuits on windows of single gates.  The backward pass starts from
+// adjoints, smaller circuits, small ones with thousands of trajectories (windows_from)
+// and calls without room for clusters on windows of single gates.  The backward pass starts from
 // lambda = w O psi (O diagonal: ZZ terms or the caller's array) or from the
 // caller's seed psi-bar = dL/d conj(psi), and walks the windows in reverse,
 // propagating lambda_{k-1} = A_k^dag lambda_k and accumulating per gate
