@@ -198,6 +198,11 @@ __host__ __device__ constexpr int vm_gate_entries(int J) { return J > 32 ? 16 * 
 // cache holds for long, took two rounds to L2 (a step of 504: 1.67 us, 1.2 us now).
 constexpr int kVmLdsSteps = 16;
 
+// Contracted and new legs of a step, whether its gate is in product order, its kept legs.
+__device__ inline int vm_form(const AbsorbStep& st) {
+  return (st.nK * 8 + st.nN) | (st.nH == 0 && st.nS == 0 ? 64 : 0) | (st.rC - st.nN) << 8;
+}
+
 template <bool LS>
 __global__ void __launch_bounds__(LS ? 512 : 256, 4) part_vm_kernel(const AbsorbStep* __restrict__ steps, int n_steps,
                                                       int buf_elems, int J, GateCtx g, int64_t n_jobs,
@@ -219,13 +224,12 @@ __global__ void __launch_bounds__(LS ? 512 : 256, 4) part_vm_kernel(const Absorb
   uint64_t* pw = reinterpret_cast<uint64_t*>(stab + n_steps);  // [J][NW] prefixes
   AbsorbStep* lsteps = reinterpret_cast<AbsorbStep*>(pw + (size_t)J * NW);   // [kVmLdsSteps], LS only
   const int tid = threadIdx.x, nt = blockDim.x;
-  // the step list's gate indices and forms (legs, hyper or sliced, kept indices), once per
-  // workgroup (visible after the first barrier)
+  // the step list's gate indices, and with LS forms (legs, hyper or sliced, kept indices), once
+  // per workgroup (visible after the first barrier); without LS a step's form comes with its
+  // other scalar loads (32,768 elements x 36 steps of rank 8: 368 us with the table, 350)
   for (int s = tid; s < n_steps; s += nt)
     stab[s] = make_int4(steps[s].gate | (steps[s].conj ? (int)0x80000000 : 0), (int)steps[s].gperm[0],
-                        (int)steps[s].gperm[1],
-                        (steps[s].nK * 8 + steps[s].nN) | (steps[s].nH == 0 && steps[s].nS == 0 ? 64 : 0) |
-                            (steps[s].rC - steps[s].nN) << 8);
+                        (int)steps[s].gperm[1], LS ? vm_form(steps[s]) : 0);
   const int64_t n_groups = (n_jobs + J - 1) / J;
   for (int64_t grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
     const int64_t job0 = grp * J;
@@ -316,7 +320,7 @@ __global__ void __launch_bounds__(LS ? 512 : 256, 4) part_vm_kernel(const Absorb
       const float2* G = Gm + (size_t)(s - cs) * per_step;
       __syncthreads();     // gates visible; previous step's C complete
       const AbsorbStep& st = LS ? lsteps[s - cs] : steps[s];
-      const int form = __builtin_amdgcn_readfirstlane(stab[s].w);
+      const int form = LS ? __builtin_amdgcn_readfirstlane(stab[s].w) : vm_form(st);
       const int lnm = form >> 8;
       const bool plain = form & 64;
       if (direct && s == n_steps - 1) {
